@@ -31,7 +31,7 @@ hipError_t launch_warp(const PairDesc* dpairs, int pair, const PairDesc& hp, con
 hipError_t launch_similarity(const float* F, const float* W, const uint8_t* mask, long long N,
                              int sim, double* slots, int nslots, float* value, uint32_t* flag,
                              hipStream_t s);
-int dense_blocks(int dim, const int* n);
+int dense_blocks(int dim, const int* n, int zc);
 hipError_t launch_adam_dev(float* th, const float* g, float* m, float* v, long long n,
                            const float* coef, float b1, float b2, float eps, hipStream_t s);
 hipError_t launch_adam(float* th, const float* g, float* m, float* v, long long n, float lr_bc1,
@@ -133,6 +133,7 @@ struct air_plan {
     size_t lds_fused = 0, lds_reg = 0;
     int max_ctrl = 0;
     int max_dense_blk = 0;
+    int dense_zc = 0;  // walk length of the dense passes' blocks (dense_walk)
     int variant = 0;
     std::mutex mu;
     DeviceTables dev[kMaxDevices];
@@ -334,8 +335,31 @@ static air_status validate_problem(const air_problem& p) {
     return AIR_OK;
 }
 
-static air_status build_tables(air_plan* P) {
+// Walk length of the dense passes' blocks: the longest (3D 32, 16, 8 planes;
+// 2D 8, 4, 2, 1 row groups) whose launch still has kDenseFill blocks, which
+// is what the 256 CUs hold at eight 256-thread blocks each; else the
+// shortest. With 32 planes always, one 128^3 pair had 256 blocks, one wave
+// per SIMD: dense NCC at 149 x 181 x 127 95.5 -> 81.1 us, 163 x 104 x 82 MSE
+// 54.3 -> 34.4 us, 128^3 Wendland NCC 132 -> 97.7 us, a 2683 x 90 image 24.7
+// -> 19.9 us. Shorter walks cost more than they fill: four planes 102.6 us
+// for the Wendland pair, and 256^3 (2048 blocks with 32 planes, 265 us) runs
+// at 276 us with 16 planes and 294 us with eight. The results do not depend
+// on it beyond the order of the partial sums.
+static int dense_walk(const air_plan* P) {
+    const int longest = P->dim == 3 ? kDenseZc : kDenseRows2;
+    const int shortest = P->dim == 3 ? kDenseMinZc : 1;
+    int zc = longest;
+    for (; zc > shortest; zc /= 2) {
+        long long blocks = 0;
+        for (const air_problem& p : P->probs) blocks += dense_blocks(P->dim, p.n, zc);
+        if (blocks >= kDenseFill) break;
+    }
+    return zc;
+}
+
+static air_status build_tables(air_plan* P, int dense_zc) {
     const int d = P->dim;
+    P->dense_zc = dense_zc;
     const bool bs = P->transform == AIR_TF_BSPLINE3;
     const bool wend = P->transform == AIR_TF_WENDLAND;
     const TileCfg cfg = (d == 3) ? kCfg3[P->tiling] : kCfg2[P->tiling];
@@ -477,7 +501,7 @@ static air_status build_tables(air_plan* P) {
             (void)bspline_cell_tables(d, D, P->consts);
         // dense passes: dense models, and the objective at exp(v) or with LCC
         if (!bs || P->field_route()) {
-            D.dense_nblk = dense_blocks(d, D.n);
+            D.dense_nblk = dense_blocks(d, D.n, P->dense_zc);
             D.dense_blk_off = (int)dense_n;
             dense_n += D.dense_nblk;
             max_dense = std::max(max_dense, D.dense_nblk);
@@ -536,6 +560,28 @@ static air_status build_tables(air_plan* P) {
     }
     L.total = off;
     return AIR_OK;
+}
+
+static air_status build_tables(air_plan* P) {
+    const int zc = dense_walk(P);
+    air_status st = build_tables(P, zc);
+    // more blocks need more partial sums: a plan that fits the scratch array
+    // of air_objective_and_grad_noalloc with the longest walk keeps that walk
+    // when the shorter one takes it past the array
+    const int longest = P->dim == 3 ? kDenseZc : kDenseRows2;
+    if (st == AIR_OK && zc < longest && P->L.total > AIR_NOALLOC_SCRATCH_BYTES) {
+        size_t now = 0, then = 0;
+        for (const PairDesc& D : P->pd) {
+            now += D.dense_nblk;
+            if (D.dense_nblk > 0) then += dense_blocks(P->dim, D.n, longest);
+        }
+        auto stats = [](size_t n) {
+            return align256(std::max<size_t>(n, 1) * kStatWords * sizeof(double));
+        };
+        if (P->L.total - stats(now) + stats(then) <= AIR_NOALLOC_SCRATCH_BYTES)
+            st = build_tables(P, longest);
+    }
+    return st;
 }
 
 static void release_device(air_plan* P) {
@@ -704,14 +750,14 @@ static hipError_t run_diffeo(const air_plan* P, const DeviceTables* T, void* ws,
     double* tvp = reinterpret_cast<double*>(w + P->L.tvpart);
     if (reg_only) {
         if (P->reg == AIR_REG_DIFFUSION)
-            e = launch_reg_dense(C, hp.dense_nblk, kDenseZc, g, value, s);
+            e = launch_reg_dense(C, hp.dense_nblk, P->dense_zc, g, value, s);
         else
             e = launch_tv(hp, P->dim, P->reg, uK, 1.f, g, false, tvp, 1.f, value, false, s);
     } else if (P->sim == AIR_SIM_LCC) {
         // the diffusion term first (value = R, g = dR/du), then the LCC
         // passes add S and dS/du with R and dR/du weighted by lambda
         const bool diff = P->reg == AIR_REG_DIFFUSION && P->probs[0].lambda_diff != 0.f;
-        if (diff) e = launch_reg_dense(C, hp.dense_nblk, kDenseZc, g, value, s);
+        if (diff) e = launch_reg_dense(C, hp.dense_nblk, P->dense_zc, g, value, s);
         if (e == hipSuccess)
             e = launch_lcc(hp, P->dim, P->lcc_radius, fixed, moving, uK,
                            reinterpret_cast<float*>(w + P->L.lcc_w), w + P->L.lcc_mask,
@@ -730,7 +776,7 @@ static hipError_t run_diffeo(const air_plan* P, const DeviceTables* T, void* ws,
         C.moving0 = moving;
         C.grad0 = g;
         C.value0 = value;
-        e = launch_dense(C, kDenseZc, P->max_dense_blk, s, nullptr, nullptr);
+        e = launch_dense(C, P->dense_zc, P->max_dense_blk, s, nullptr, nullptr);
         if (e == hipSuccess && P->reg != AIR_REG_DIFFUSION)
             e = launch_tv(hp, P->dim, P->reg, uK, P->reg_weight, g, true, tvp, P->reg_weight,
                           value, true, s);
@@ -802,7 +848,7 @@ static air_status run_objective(const air_plan* cP, LaunchCtx& C, hipStream_t s)
         e = launch_bspline(C, P->variant, P->lds_fused, P->max_ctrl, s, e0, e1);
     } else {
         TraceRange r("air.stage.dense_passes");
-        e = launch_dense(C, kDenseZc, P->max_dense_blk, s, e0, e1);
+        e = launch_dense(C, P->dense_zc, P->max_dense_blk, s, e0, e1);
     }
     if (e == hipSuccess && P->reg != AIR_REG_DIFFUSION) {
         TraceRange r("air.stage.tv");
@@ -1147,7 +1193,7 @@ air_status air_regulariser(const air_plan* plan, int32_t pair, const float* thet
         C.npairs = 1;
         C.theta0 = theta;
         // the sub-context sees this pair at index 0; its slots keep their offsets
-        e = launch_reg_dense(C, hp.dense_nblk, kDenseZc, grad, value, (hipStream_t)stream);
+        e = launch_reg_dense(C, hp.dense_nblk, plan->dense_zc, grad, value, (hipStream_t)stream);
     }
     return e == hipSuccess ? AIR_OK : AIR_ERR_LAUNCH;
 }

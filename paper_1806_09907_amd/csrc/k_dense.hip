@@ -22,21 +22,21 @@ struct DenseTile {
     bool act;
 };
 
-// A 2D block covers DTX x (DTY * kDenseRows2) pixels: lane row ly takes rows
-// y0 + ly + DTY r, r < kDenseRows2 (the "z" range of its tile), so a large
-// image does not become tens of thousands of tiny blocks whose partial sums
-// the single-block reductions then walk.
-constexpr int kDenseRows2 = 8;
+// `zc` is the length of a block's walk (dense_walk): 3D blocks take zc planes
+// of z; a 2D block covers DTX x (DTY * zc) pixels, lane row ly taking rows
+// y0 + ly + DTY r, r < zc (the "z" range of its tile), so a large image does
+// not become tens of thousands of tiny blocks whose partial sums the
+// single-block reductions then walk.
 
 // Dense-pass blocks of one pair (host and device).
-__host__ __device__ inline int dense_blocks_of(int dim, const int* n) {
+__host__ __device__ inline int dense_blocks_of(int dim, const int* n, int zc) {
     const int nbx = cdiv(n[0], DTX);
-    if (dim == 3) return nbx * cdiv(n[1], DTY) * cdiv(n[2], kDenseZc);
-    return nbx * cdiv(n[1], DTY * kDenseRows2);
+    if (dim == 3) return nbx * cdiv(n[1], DTY) * cdiv(n[2], zc);
+    return nbx * cdiv(n[1], DTY * zc);
 }
 
 __device__ inline DenseTile dense_tile(const PairDesc& P, int blk, int zc, int dim) {
-    const int ty = dim == 3 ? DTY : DTY * kDenseRows2;   // rows of a block
+    const int ty = dim == 3 ? DTY : DTY * zc;   // rows of a block
     const int nbx = cdiv(P.n[0], DTX), nby = cdiv(P.n[1], ty);
     const int bx = blk % nbx;
     const int rest = blk / nbx;
@@ -50,7 +50,7 @@ __device__ inline DenseTile dense_tile(const PairDesc& P, int blk, int zc, int d
         T.z1 = min(T.z0 + zc, P.n[2]);
     } else {
         T.z0 = 0;
-        T.z1 = kDenseRows2;   // row groups; rows at or past n[1] are skipped
+        T.z1 = zc;   // row groups; rows at or past n[1] are skipped
     }
     T.act = (T.x < P.n[0]) && (T.y < P.n[1]);
     return T;
@@ -596,7 +596,7 @@ hipError_t launch_dense(const LaunchCtx& C, int zc, int max_blk, hipStream_t s, 
 }
 
 // Regulariser of a dense field for one pair (context holds that pair only).
-int dense_blocks(int dim, const int* n) { return dense_blocks_of(dim, n); }
+int dense_blocks(int dim, const int* n, int zc) { return dense_blocks_of(dim, n, zc); }
 
 hipError_t launch_reg_dense(const LaunchCtx& C, int pair_blocks, int zc, float* grad_out,
                             float* value_out, hipStream_t s) {

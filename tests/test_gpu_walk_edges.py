@@ -1,0 +1,74 @@
+"""Objective and gradient against the FP64 oracle at the sizes where the
+kernels' work splits change: remainders of a block's walk, the shortest and
+longest walks, tile edges. Tolerances are the parity bars of every GPU test
+(parity.py): 1e-5 for the value, 1e-4 for the gradient (norm- and
+element-wise)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_1806_09907_amd import api, synth
+from parity import VAL_TOL, check_grad
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def gpu(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+
+
+def inputs(n, seed, blobs=10):
+    rng = np.random.default_rng(seed)
+    F = synth.blobs(tuple(reversed(n)), blobs, rng) + rng.normal(0, 0.01, tuple(reversed(n)))
+    M = synth.blobs(tuple(reversed(n)), blobs, rng) + rng.normal(0, 0.01, tuple(reversed(n)))
+    return F.astype(np.float32), (0.5 * M + 0.5 * F).astype(np.float32)
+
+
+def check(p, F, M, th, what):
+    print(f"case {what}", flush=True)
+    plan = api.Plan(p)
+    v, g = api.objective_and_grad(plan, gpu(F), gpu(M), gpu(th))
+    torch.cuda.synchronize()
+    op = O.Problem(n=p.n, transform=p.transform, spacing=p.spacing, similarity=p.similarity,
+                   lambda_diff=p.lambda_diff, diffeo_steps=p.diffeo_steps,
+                   regulariser=p.regulariser, sigma=p.sigma, lcc_radius=p.lcc_radius)
+    vo, go, _ = O.objective_and_grad(op, F, M, th)
+    assert abs(float(v) - vo) <= VAL_TOL * abs(vo), (float(v), vo)
+    check_grad(g.double().cpu().numpy(), go, what)
+
+
+# dense passes: walks of 8, 16 and 32 planes (1, 2, .. 8 row groups in 2D) and
+# their remainders
+@pytest.mark.parametrize("n", [(70, 9, 7), (66, 5, 8), (64, 4, 9), (65, 6, 17), (256, 256, 150),
+                               (256, 256, 254), (64, 3), (65, 301), (700, 1100)])
+@pytest.mark.parametrize("sim", [api.SIM_MSE, api.SIM_NCC])
+def test_dense_walks(n, sim):
+    p = api.Problem(n=n, transform=api.TF_DENSE, spacing=(1,) * len(n), similarity=sim,
+                    lambda_diff=0.5)
+    F, M = inputs(n, 7)
+    rng = np.random.default_rng(8)
+    th = rng.normal(0.0, 1.5, (len(n),) + tuple(reversed(n)))
+    for a in range(len(n)):
+        th[a] *= 2.0 / (n[a] - 1)
+    check(p, F, M, th.astype(np.float32), f"dense walk {n} sim={sim}")
+
+
+def test_dense_batch_uneven_walks():
+    """Pairs of one batch share the walk length; each keeps its own blocks."""
+    sizes = [(33, 12, 9), (70, 5, 31), (64, 8, 8)]
+    probs = [api.Problem(n=n, transform=api.TF_DENSE, spacing=(1, 1, 1), similarity=api.SIM_NCC,
+                         lambda_diff=0.2) for n in sizes]
+    data = [inputs(n, 20 + i) for i, n in enumerate(sizes)]
+    ths = [synth.random_dense(n, 1.0, 30 + i) for i, n in enumerate(sizes)]
+    vals, grads, _ = api.objective_and_grad_batched(
+        api.Plan(probs), [gpu(f) for f, _ in data], [gpu(m) for _, m in data],
+        [gpu(t) for t in ths])
+    torch.cuda.synchronize()
+    for i, n in enumerate(sizes):
+        op = O.Problem(n=n, transform=O.TF_DENSE, spacing=(1, 1, 1), similarity=O.SIM_NCC,
+                       lambda_diff=0.2)
+        vo, go, _ = O.objective_and_grad(op, data[i][0], data[i][1], ths[i])
+        assert abs(float(vals[i]) - vo) <= VAL_TOL * abs(vo)
+        check_grad(grads[i].double().cpu().numpy(), go, f"dense batch pair {i}")
