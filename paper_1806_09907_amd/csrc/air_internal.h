@@ -93,9 +93,9 @@ struct WsLayout {
                          // (Wendland: the padded, scaled controls)
     size_t bsadj2;       // float [d][nz][ncy][ncx]: after y
                          // (Wendland: per-cell sums H [d][cells][K^d])
-    size_t reach;        // uint32 [K + 3]: largest displacement of each u_k, then two
-                         // slots for the largest |gradient| entering and leaving a
-                         // squaring's adjoint (float bits)
+    size_t reach;        // uint32 [2 K + 1]: largest displacement of u_0 .. u_(K-1), then
+                         // the largest |gradient| entering each squaring's adjoint and
+                         // leaving the last (float bits)
     size_t tvpart;       // double [TV blocks]: partial sums of a TV term
     // LCC passes (similarity AIR_SIM_LCC)
     size_t lcc_w;        // float [N]: warped image
@@ -135,6 +135,8 @@ struct LaunchCtx {
     float* values;
     unsigned char* ws;
     WsLayout L;
+    unsigned int* gmax;        // nullable: the dense main pass leaves max |gradient| there
+                               // (float bits; zero before the launch)
 };
 
 __host__ __device__ inline int cdiv(int a, int b) { return (a + b - 1) / b; }

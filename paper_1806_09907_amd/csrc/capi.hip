@@ -39,13 +39,16 @@ hipError_t launch_adam(float* th, const float* g, float* m, float* v, long long 
 hipError_t launch_scale(float* x, const float* s, long long n, hipStream_t st);
 hipError_t launch_velocity(const PairDesc& P, const float* consts_dev, int transform, int dim,
                            const float* theta, float scale, float* out, hipStream_t s);
-hipError_t launch_compose(const PairDesc& P, int dim, const float* u, float* out,
-                          unsigned int* dmax, hipStream_t s);
+hipError_t launch_compose(const PairDesc& P, int dim, const float* u, float us, float* out,
+                          unsigned int* reach_in, bool first, unsigned int* reach_out,
+                          hipStream_t s);
+hipError_t launch_field_absmax(const PairDesc& P, int dim, const float* g, unsigned int* out,
+                               hipStream_t s);
 hipError_t launch_zero_u32(unsigned int* p, int n, hipStream_t s);
-hipError_t launch_compose_adjoint(const PairDesc& P, int dim, const float* u, const float* gout,
-                                  const unsigned int* dmax, unsigned int* gmax_in,
-                                  bool measure_in, unsigned int* gmax_out, float* gin,
-                                  hipStream_t s);
+hipError_t launch_compose_adjoint(const PairDesc& P, int dim, const float* u, float us,
+                                  const float* gout, const unsigned int* dmax,
+                                  const unsigned int* gmax_in, unsigned int* gmax_out, float* gin,
+                                  float gs, hipStream_t s);
 hipError_t launch_velocity_adjoint(const PairDesc& P, const float* consts_dev, int transform,
                                    int dim, const float* g, float scale, float* t1, float* t2,
                                    float* grad, hipStream_t s, bool accumulate);
@@ -541,7 +544,7 @@ static air_status build_tables(air_plan* P, int dense_zc) {
         }
         L.bsadj1 = off;  off = align256(off + t1 * 4);
         L.bsadj2 = off;  off = align256(off + t2 * 4);
-        L.reach = off;   off = align256(off + (size_t)(P->diffeo + 3) * 4);  // + 2 max|grad|
+        L.reach = off;   off = align256(off + (size_t)(2 * P->diffeo + 1) * 4);  // + K + 1 max|grad|
     }
     if (P->reg != AIR_REG_DIFFUSION) {
         L.tvpart = off;  off = align256(off + (size_t)tv_partials() * 8);
@@ -708,20 +711,41 @@ static hipError_t field_adjoint(const air_plan* P, const DeviceTables* T, unsign
                                    accumulate);
 }
 
-// u_K = exp(v) into the workspace fields u_0 .. u_K (Sec. III-D); with K = 0
-// u_0 is the field itself. Returns u_K.
+// The field u_k of the exponential as pointer and power-of-two factor: a
+// dense velocity is read from theta itself with the factor 2^-K (exact), so
+// u_0 is never copied; u_0 of an interpolating basis and u_1 .. u_K are in
+// the workspace.
+struct ScaledField {
+    const float* u;
+    float scale;
+};
+static ScaledField diffeo_field(const air_plan* P, unsigned char* w, const float* theta, int k) {
+    if (k == 0 && P->transform == AIR_TF_DENSE) return {theta, ldexpf(1.f, -P->diffeo)};
+    return {reinterpret_cast<const float*>(w + P->L.fields) +
+                k * ((long long)P->dim * P->pd[0].nvox),
+            1.f};
+}
+
+// u_K = exp(v) into the workspace fields (Sec. III-D); with K = 0 u_0 is the
+// field itself (theta for a dense one). Returns u_K.
 static hipError_t diffeo_forward(const air_plan* P, const DeviceTables* T, unsigned char* w,
-                                 const float* theta, hipStream_t s, float** uK) {
+                                 const float* theta, hipStream_t s, const float** uK) {
     const PairDesc& hp = P->pd[0];
     const long long dN = (long long)P->dim * hp.nvox;
     float* U = reinterpret_cast<float*>(w + P->L.fields);
-    // each squaring also measures its input's reach for the adjoint
+    // reach[k], that of u_k, is measured by the squaring that makes u_k (u_0:
+    // that reads it); the slots after hold the max |gradient| of the adjoints
     unsigned int* reach = reinterpret_cast<unsigned int*>(w + P->L.reach);
-    hipError_t e = expand_field(P, T, w, theta, ldexpf(1.f, -P->diffeo), U, s);
-    if (e == hipSuccess && P->diffeo > 0) e = launch_zero_u32(reach, P->diffeo, s);
-    for (int k = 0; k < P->diffeo && e == hipSuccess; ++k)
-        e = launch_compose(hp, P->dim, U + k * dN, U + (k + 1) * dN, reach + k, s);
-    *uK = U + P->diffeo * dN;
+    hipError_t e = hipSuccess;
+    if (P->transform != AIR_TF_DENSE)
+        e = expand_field(P, T, w, theta, ldexpf(1.f, -P->diffeo), U, s);
+    if (e == hipSuccess && P->diffeo > 0) e = launch_zero_u32(reach, 2 * P->diffeo + 1, s);
+    for (int k = 0; k < P->diffeo && e == hipSuccess; ++k) {
+        const ScaledField f = diffeo_field(P, w, theta, k);
+        e = launch_compose(hp, P->dim, f.u, f.scale, U + (k + 1) * dN, reach + k, k == 0,
+                           k + 1 < P->diffeo ? reach + k + 1 : nullptr, s);
+    }
+    *uK = diffeo_field(P, w, theta, P->diffeo).u;
     return e;
 }
 
@@ -735,7 +759,7 @@ static hipError_t run_diffeo(const air_plan* P, const DeviceTables* T, void* ws,
     unsigned char* w = static_cast<unsigned char*>(ws);
     const PairDesc& hp = P->pd[0];
     const long long dN = (long long)P->dim * hp.nvox;
-    float* uK = nullptr;
+    const float* uK = nullptr;
     hipError_t e;
     {
         TraceRange r("air.stage.expand_and_squarings");
@@ -743,8 +767,14 @@ static hipError_t run_diffeo(const air_plan* P, const DeviceTables* T, void* ws,
     }
     if (e != hipSuccess) return e;
     TraceRange r_eval("air.stage.field_evaluation");
+    // dL/du_K; for a dense field without the exponential that is the gradient
+    const bool plain_dense = P->transform == AIR_TF_DENSE && P->diffeo == 0;
     float* g = reinterpret_cast<float*>(w + P->L.gfield);
     float* o = g + dN;
+    if (plain_dense && grad) g = grad;
+    unsigned int* reach = reinterpret_cast<unsigned int*>(w + P->L.reach);   // from the forward pass
+    unsigned int* gmax = reach + P->diffeo;   // gmax[j]: max |gradient| entering adjoint j
+    bool measured = false;                    // gmax[0] left by the dense main pass
     LaunchCtx C = base_ctx(P, T, ws);
     C.theta0 = uK;
     double* tvp = reinterpret_cast<double*>(w + P->L.tvpart);
@@ -776,28 +806,33 @@ static hipError_t run_diffeo(const air_plan* P, const DeviceTables* T, void* ws,
         C.moving0 = moving;
         C.grad0 = g;
         C.value0 = value;
+        // the scale of the first adjoint, unless a TV term still changes g
+        if (P->diffeo > 0 && P->reg == AIR_REG_DIFFUSION) {
+            C.gmax = gmax;
+            measured = true;
+        }
         e = launch_dense(C, P->dense_zc, P->max_dense_blk, s, nullptr, nullptr);
         if (e == hipSuccess && P->reg != AIR_REG_DIFFUSION)
             e = launch_tv(hp, P->dim, P->reg, uK, P->reg_weight, g, true, tvp, P->reg_weight,
                           value, true, s);
     }
-    if (e != hipSuccess || !grad) return e;
+    if (e != hipSuccess || !grad || plain_dense) return e;
     TraceRange r_adj("air.stage.squaring_adjoints_and_field_adjoint");
-    const float* U = reinterpret_cast<const float*>(w + P->L.fields);
-    unsigned int* reach = reinterpret_cast<unsigned int*>(w + P->L.reach);   // from the forward pass
-    for (int k = P->diffeo - 1; k >= 0 && e == hipSuccess; --k) {
-        // the max |gradient| slots alternate: each call measures its output
-        // for the next one
-        unsigned int* gm_in = reach + P->diffeo + 1 + ((P->diffeo - 1 - k) & 1);
-        unsigned int* gm_out = reach + P->diffeo + 1 + ((P->diffeo - k) & 1);
-        e = launch_compose_adjoint(hp, P->dim, U + k * dN, g, reach + k, gm_in,
-                                   k == P->diffeo - 1, gm_out, o, s);
+    const bool dense = P->transform == AIR_TF_DENSE;
+    const float vscale = ldexpf(1.f, -P->diffeo);
+    if (P->diffeo > 0 && !measured) e = launch_field_absmax(hp, P->dim, g, gmax, s);
+    for (int k = P->diffeo - 1, j = 0; k >= 0 && e == hipSuccess; --k, ++j) {
+        // the last adjoint of a dense velocity writes dL/dtheta = 2^-K dL/du_0
+        const bool last = dense && k == 0;
+        const ScaledField f = diffeo_field(P, w, theta, k);
+        e = launch_compose_adjoint(hp, P->dim, f.u, f.scale, g, reach + k, gmax + j, gmax + j + 1,
+                                   last ? grad : o, last ? vscale : 1.f, s);
         float* t = g;
         g = o;
         o = t;
     }
-    if (e != hipSuccess) return e;
-    return field_adjoint(P, T, w, g, ldexpf(1.f, -P->diffeo), grad, false, s);
+    if (e != hipSuccess || dense) return e;
+    return field_adjoint(P, T, w, g, vscale, grad, false, s);
 }
 
 // TV term of a plan without the exponential, after the similarity pass:
@@ -1127,7 +1162,7 @@ air_status air_displacement(const air_plan* plan, int32_t pair, const float* the
     if (!plan->expanded()) {
         e = launch_velocity(hp, T->consts, plan->transform, plan->dim, theta, 1.f, u, s);
     } else {
-        float* uK = nullptr;
+        const float* uK = nullptr;
         e = diffeo_forward(plan, T, static_cast<unsigned char*>(ws), theta, s, &uK);
         if (e == hipSuccess)
             e = launch_velocity(hp, T->consts, AIR_TF_DENSE, plan->dim, uK, 1.f, u, s);

@@ -21,6 +21,11 @@ __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t by
     return __builtin_amdgcn_make_buffer_rsrc(q, (short)0, (int)nb, 0x00020000);
 }
 
+// One float at byte offset voff + soff (dword aligned; zero past the buffer).
+__device__ inline float load1(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
+}
+
 // Two consecutive floats at byte offset voff + soff (dword aligned).
 __device__ inline v2f load2(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
     return __builtin_bit_cast(v2f, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
@@ -93,6 +98,26 @@ __device__ inline void block_sum(double (&v)[K], double* scratch) {
         v[k] = s;
     }
     __syncthreads();
+}
+
+// A running maximum that keeps a NaN.
+__device__ inline float max_or_nan(float m, float t) { return (t > m || !(t == t)) ? t : m; }
+
+// Maximum over the block of non-negative floats as bits (ordered like
+// unsigned integers, NaN above every finite value), then into *out, which
+// was zero before the launch. red: one word of LDS per wave.
+__device__ inline void block_max_to(float m, unsigned int* red, unsigned int* out) {
+    unsigned int b = __float_as_uint(m) & 0x7fffffffu;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) b = max(b, (unsigned int)__shfl_xor((int)b, o, 64));
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = b;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned int r = red[0];
+        for (int w = 1; w < (int)blockDim.x / 64; ++w) r = max(r, red[w]);
+        atomicMax(out, r);
+    }
 }
 
 // Index of the pair owning global work item `item` (binary search on begin).

@@ -260,6 +260,7 @@ k_dense_main(const LaunchCtx C, int zc, int reg_only, float* reg_grad_out) {
     const __amdgpu_buffer_rsrc_t rM = make_rsrc(M, (uint32_t)(N * 4));
     // per-lane sums over the z chunk in FP32, widened once per chunk
     float sq = 0.f, rr = 0.f;   // MSE sum of squares, regulariser sum
+    float gm = 0.f;             // largest |gradient| (only where C.gmax asks for it)
     if (T.act) {
         const int x = T.x;
         int y = T.y;
@@ -349,12 +350,15 @@ k_dense_main(const LaunchCtx C, int zc, int reg_only, float* reg_grad_out) {
             }
 #pragma unroll
             for (int c = 0; c < DIM; ++c) {
-                grad[c * N + vi] = gi[c] + gr[c];
+                const float gv = gi[c] + gr[c];
+                grad[c * N + vi] = gv;
+                if (C.gmax) gm = max_or_nan(gm, fabsf(gv));
                 um[c] = u0[c];
                 u0[c] = up[c];
             }
         }
     }
+    if (C.gmax) block_max_to(gm, reinterpret_cast<unsigned int*>(red), C.gmax);
     double acc[2] = {(double)sq, (double)rr};
     block_sum<NT, 2>(acc, red);
     if (threadIdx.x == 0) {
@@ -456,6 +460,7 @@ k_dense_main3(const LaunchCtx C, int zc, int reg_only, float* reg_grad_out) {
         G = sample3_issue(rM, x, y, z0, disp_of(u0[0], s0), disp_of(u0[1], s1),
                           disp_of(u0[2], s2), nx, ny, nz);
     float sq = 0.f, rr = 0.f;   // per-lane MSE and regulariser sums over the chunk
+    float gm = 0.f;             // largest |gradient| (only where C.gmax asks for it)
     for (int z = z0; z < z1; ++z) {
         const int bsel = (z - z0) & 1;
 #pragma unroll
@@ -509,7 +514,11 @@ k_dense_main3(const LaunchCtx C, int zc, int reg_only, float* reg_grad_out) {
                 for (int c = 0; c < 3; ++c) gi[c] = e * s3.d[c] * P.s[c];
             }
 #pragma unroll
-            for (int c = 0; c < 3; ++c) grad[c * N + vi] = gi[c] + gr[c];
+            for (int c = 0; c < 3; ++c) {
+                const float gv = gi[c] + gr[c];
+                grad[c * N + vi] = gv;
+                if (C.gmax) gm = max_or_nan(gm, fabsf(gv));
+            }
         }
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
@@ -521,6 +530,7 @@ k_dense_main3(const LaunchCtx C, int zc, int reg_only, float* reg_grad_out) {
         G = Gn;
         Fv = Fn;
     }
+    if (C.gmax) block_max_to(gm, reinterpret_cast<unsigned int*>(red), C.gmax);
     double acc[2] = {(double)sq, (double)rr};
     block_sum<NT, 2>(acc, red);
     if (tid == 0) {

@@ -27,16 +27,16 @@ __host__ inline int grid_for(long long total) {
     return (int)(b < kDiffeoBlocks ? (b < 1 ? 1 : b) : kDiffeoBlocks);
 }
 
-// Zero-padded multilinear sample of the DIM components of field u at the
-// point x + d + e of a voxel (voxel units, see axis_cell); with DERIV also
+// Zero-padded multilinear sample of the DIM components of the field us * u
+// (us a power of two) at the point x + d + e of a voxel (voxel units, see axis_cell); with DERIV also
 // dval[c][a] = d sample_c / d p_a on that point's cell (right-sided at an
 // integer point). Returns false for a non-finite point (the values are then
 // NaN). The value does not depend on the cell taken at an integer point, so
 // the forward squaring passes e = 0.
 template <int DIM, bool DERIV>
-__device__ inline bool field_sample(const float* __restrict__ u, long long N, const PairDesc& P,
-                                    const int* x, const Disp* q, float* val, float (*dval)[3],
-                                    int* j, float* f) {
+__device__ inline bool field_sample(const float* __restrict__ u, float us, long long N,
+                                    const PairDesc& P, const int* x, const Disp* q, float* val,
+                                    float (*dval)[3], int* j, float* f) {
     bool finite = true;
 #pragma unroll
     for (int a = 0; a < DIM; ++a) {
@@ -79,7 +79,7 @@ __device__ inline bool field_sample(const float* __restrict__ u, long long N, co
 #pragma unroll
         for (int c = 0; c < DIM; ++c) {
             const __amdgpu_buffer_rsrc_t r = make_rsrc(u + c * N, (uint32_t)(N * 4));
-            const v2f a00 = load2(r, off, 0), a10 = load2(r, off, sx4);
+            const v2f a00 = load2(r, off, 0) * us, a10 = load2(r, off, sx4) * us;
             const float c00 = fmaf(fx, a00.y - a00.x, a00.x), c10 = fmaf(fx, a10.y - a10.x, a10.x);
             const float c0 = fmaf(fy, c10 - c00, c00);
             if (DIM == 2) {
@@ -89,7 +89,7 @@ __device__ inline bool field_sample(const float* __restrict__ u, long long N, co
                     dval[c][1] = c10 - c00;
                 }
             } else {
-                const v2f a01 = load2(r, off, sxy4), a11 = load2(r, off, sxy4 + sx4);
+                const v2f a01 = load2(r, off, sxy4) * us, a11 = load2(r, off, sxy4 + sx4) * us;
                 const float c01 = fmaf(fx, a01.y - a01.x, a01.x),
                             c11 = fmaf(fx, a11.y - a11.x, a11.x);
                 const float c1 = fmaf(fy, c11 - c01, c01);
@@ -132,7 +132,7 @@ __device__ inline bool field_sample(const float* __restrict__ u, long long N, co
         }
 #pragma unroll
         for (int c = 0; c < DIM; ++c) {
-            const float uv = u[c * N + idx];
+            const float uv = us * u[c * N + idx];
             val[c] += w * uv;
             if (DERIV)
 #pragma unroll
@@ -193,91 +193,269 @@ k_scale_copy(const float* __restrict__ in, float scale, long long n, int accumul
         out[i] = accumulate ? out[i] + scale * in[i] : scale * in[i];
 }
 
-// One squaring: out(x) = u(x) + u(x + u(x)). It also measures the largest
-// displacement of its input u in voxels (max over voxels and axes of
-// |u_a| (n_a - 1)/2) into dmax, as the bits of a non-negative float (ordered
-// like unsigned integers; NaN compares above every finite value): the reach
-// of this squaring's adjoint. dmax must be zero before the launch.
-// A block owns kCompTX x kCompTY voxels of (x, y) and takes kCompSteps steps
-// along the last axis (3D: planes z; 2D: groups of kCompTY rows), so the
-// coordinates need no division and the next step's displacement loads are
-// issued before this step's gathers are used. Work items are XCD-contiguous,
-// so the gathers of neighbouring columns share an L2.
-constexpr int kCompTX = 64, kCompTY = 4, kCompSteps = 16;
-static_assert(kCompTX * kCompTY == kBlock, "one thread per (x, y) of a block");
+// Squarings whose samples move less than one voxel along every axis ("near")
+// read their neighbourhood from LDS in both directions; the others gather
+// from memory, and their adjoint scans (a NaN reach among them).
+__device__ inline bool near_reach(float dmax) { return dmax < 1.f; }
+
+// The work split of the near kernels: a block owns 32 x 8 columns (2D: 256
+// columns) and walks `walk` planes (2D: rows) of the last axis; each plane,
+// with a one-voxel halo that is zero outside the volume, passes through a
+// ring of four LDS slots, so it is read from memory once (with the halo, 1.33
+// times), coalesced and a step ahead of its use. Items are XCD-contiguous.
+constexpr int kNearWalk = 32, kNearMinWalk = 8;
+constexpr int kNearFill = 1024;    // blocks that fill the chip
 template <int DIM>
-__host__ __device__ inline int compose_items(const PairDesc& P) {
-    const int nbx = cdiv(P.n[0], kCompTX);
-    if (DIM == 3) return nbx * cdiv(P.n[1], kCompTY) * cdiv(P.n[2], kCompSteps);
-    return nbx * cdiv(P.n[1], kCompTY * kCompSteps);
-}
+struct Near {
+    static constexpr int TX = DIM == 3 ? 32 : kBlock, TY = kBlock / TX;
+    static constexpr int HX = TX + 2, HY = DIM == 3 ? TY + 2 : 1, PL = HX * HY;
+    static constexpr int NE = (PL + kBlock - 1) / kBlock;   // halo-plane cells per thread
+    static constexpr int LA = DIM - 1;
+
+    int l0, l1;      // planes of the block
+    int x, y, own;   // this thread's column and its cell of a staged plane
+    int plane;       // voxels per plane
+    bool act;
+    int eo[NE];      // byte offsets of the cells it stages; a cell outside the
+                     // volume reads past the buffer, which gives zero
+
+    __host__ __device__ static int cols(const PairDesc& P) {
+        return cdiv(P.n[0], TX) * (DIM == 3 ? cdiv(P.n[1], TY) : 1);
+    }
+    __host__ __device__ static int items(const PairDesc& P, int walk) {
+        return cols(P) * cdiv(P.n[LA], walk);
+    }
+    // false for an idle block
+    __device__ bool init(const PairDesc& P, int walk) {
+        const int item = xcd_item(blockIdx.x, items(P, walk), 0);
+        if (item < 0) return false;
+        const int tid = threadIdx.x, nx = P.n[0], ny = P.n[1];
+        const int ncol = cols(P), col = item % ncol, nbx = cdiv(nx, TX);
+        const int x0 = (col % nbx) * TX, y0 = DIM == 3 ? (col / nbx) * TY : 0;
+        l0 = (item / ncol) * walk;
+        l1 = min(l0 + walk, P.n[LA]);
+        const int lx = tid % TX, ly = tid / TX;
+        x = x0 + lx;
+        y = y0 + ly;
+        own = DIM == 3 ? (ly + 1) * HX + lx + 1 : lx + 1;
+        act = x < nx && (DIM == 2 || y < ny);
+        plane = DIM == 3 ? nx * ny : nx;
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            const int i = tid + e * kBlock;
+            const int cx = i % HX, cy = i / HX;
+            const int gx = x0 - 1 + cx, gy = DIM == 3 ? y0 - 1 + cy : 0;
+            const bool ok = i < PL && gx >= 0 && gx < nx && gy >= 0 && (DIM == 2 || gy < ny);
+            eo[e] = ok ? (gy * nx + gx) * 4 : 0x7ffffff0;
+        }
+        return true;
+    }
+    // plane l of one component into registers
+    __device__ void fetch(__amdgpu_buffer_rsrc_t r, int l, int nl, float* st) const {
+        if (l < 0 || l >= nl) {
+#pragma unroll
+            for (int e = 0; e < NE; ++e) st[e] = 0.f;
+            return;
+        }
+#pragma unroll
+        for (int e = 0; e < NE; ++e) st[e] = load1(r, eo[e], l * plane * 4);
+    }
+};
+
+// The work split of the gathering squaring: a block owns 64 x 4 voxels of
+// (x, y) and takes 16 steps along the last axis (3D: planes; 2D: groups of
+// four rows). Lanes of a wave lie along x, whose gathers share lines.
+template <int DIM>
+struct Far {
+    static constexpr int TX = 64, TY = 4, STEPS = 16;
+    static_assert(TX * TY == kBlock, "one thread per (x, y) of a block");
+    __host__ __device__ static int items(const PairDesc& P) {
+        const int nbx = cdiv(P.n[0], TX);
+        if (DIM == 3) return nbx * cdiv(P.n[1], TY) * cdiv(P.n[2], STEPS);
+        return nbx * cdiv(P.n[1], TY * STEPS);
+    }
+    // this thread's column (x, y) and its steps [t, t1) by dt of the last
+    // axis (2D: y is the first row); false for an idle block
+    __device__ static bool column(const PairDesc& P, int* x, int* y, int* t, int* t1, int* dt) {
+        const int item = xcd_item(blockIdx.x, items(P), 0);
+        if (item < 0) return false;
+        const int nbx = cdiv(P.n[0], TX), ly = (int)threadIdx.x / TX;
+        *x = (item % nbx) * TX + (int)threadIdx.x % TX;
+        if (DIM == 3) {
+            const int nby = cdiv(P.n[1], TY);
+            *y = ((item / nbx) % nby) * TY + ly;
+            *t = (item / (nbx * nby)) * STEPS;
+            *t1 = min(*t + STEPS, P.n[2]);
+            *dt = 1;
+        } else {
+            *y = *t = (item / nbx) * (TY * STEPS) + ly;
+            *t1 = min(*t + TY * STEPS - ly, P.n[1]);
+            *dt = TY;
+        }
+        return true;
+    }
+};
+
+// One squaring of the field us * u: out(x) = us (u(x) + u(x + us u(x))), us a
+// power of two (the 2^-K of the first squaring of a dense field, applied
+// where a value is loaded; else 1). Reaches (the largest displacement in
+// voxels of a field, max over voxels and axes of |u_a| (n_a - 1)/2) are bits
+// of non-negative floats (ordered like unsigned integers; NaN compares above
+// every finite value), zero before their launch: reach_in is that of the
+// input, measured here when `first` and left by the previous squaring
+// otherwise; reach_out (nullable) receives that of the output.
+//
+// A near field's samples come from the LDS ring (Near). Gathering them (12
+// scattered 8-byte loads per voxel, each 16 clocks of a CU's vector-memory
+// path or more) took 247-262 us per squaring at 256^3, the ring 120-135 us;
+// reading and writing the field once is 80 us. The first squaring does not
+// know its reach: it takes the ring and gathers the samples that leave it.
+// Both ways the same operations in the same order.
 template <int DIM>
 __global__ void __launch_bounds__(kBlock)
-k_compose(const PairDesc P, const float* __restrict__ u, float* __restrict__ out,
-          unsigned int* __restrict__ dmax) {
+k_compose(const PairDesc P, const float* __restrict__ u, float us, float* __restrict__ out,
+          unsigned int* __restrict__ reach_in, int first, unsigned int* __restrict__ reach_out,
+          int walk) {
+    using T = Near<DIM>;
+    constexpr int HX = T::HX, PL = T::PL, NE = T::NE, LA = T::LA, SL = DIM * PL;
+    __shared__ float ring[4 * SL];
     __shared__ unsigned int red[kBlock / 64];
+    const int tid = threadIdx.x;
     const long long N = P.nvox;
-    const int nx = P.n[0], ny = P.n[1];
-    const int nbx = cdiv(nx, kCompTX);
-    const int item = xcd_item(blockIdx.x, compose_items<DIM>(P), 0);
-    float m = 0.f;
-    if (item >= 0) {
-        const int x = (item % nbx) * kCompTX + (int)threadIdx.x % kCompTX;
-        const int ly = (int)threadIdx.x / kCompTX;
-        int y, z0, cnt;
-        long long step;
-        if (DIM == 3) {
-            const int nby = cdiv(ny, kCompTY);
-            y = ((item / nbx) % nby) * kCompTY + ly;
-            z0 = (item / (nbx * nby)) * kCompSteps;
-            cnt = min(kCompSteps, P.n[2] - z0);
-            step = (long long)nx * ny;
-        } else {
-            y = (item / nbx) * (kCompTY * kCompSteps) + ly;   // rows y + kCompTY k
-            z0 = 0;
-            cnt = y < ny ? min(kCompSteps, cdiv(ny - y, kCompTY)) : 0;
-            step = (long long)nx * kCompTY;
+    const int nl = P.n[LA];
+    float mi = 0.f, mo = 0.f;
+    int x, y;   // this thread's column
+    // far samples of voxel t of the column: from memory
+    auto gather = [&](int t, const float* w, float* val) {
+        const int idx[3] = {x, DIM == 3 ? y : t, DIM == 3 ? t : 0};
+        float f[3];
+        Disp q[3];
+        int j[3];
+#pragma unroll
+        for (int a = 0; a < DIM; ++a) q[a] = Disp{w[a] * P.s[a], 0.f};
+        field_sample<DIM, false>(u, us, N, P, idx, q, val, nullptr, j, f);
+    };
+    auto store = [&](int v, const float* w, const float* val) {
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) {
+            const float o = w[c] + val[c];
+            out[c * N + v] = o;
+            mo = max_or_nan(mo, fabsf(o * P.s[c]));
         }
-        if (x < nx && y < ny && cnt > 0) {
-            long long v = x + (long long)nx * (y + (DIM == 3 ? (long long)ny * z0 : 0));
-            float uc[3] = {0.f, 0.f, 0.f}, un[3] = {0.f, 0.f, 0.f};
+    };
+    if (!first && !near_reach(__uint_as_float(*reach_in))) {
+        int t, t1, dt;
+        if (!Far<DIM>::column(P, &x, &y, &t, &t1, &dt)) return;
+        if (x < P.n[0] && y < P.n[1] && t < t1) {
+            const int dv = dt * (DIM == 3 ? P.n[0] * P.n[1] : P.n[0]);
+            int v = x + (DIM == 3 ? P.n[0] * (y + P.n[1] * t) : P.n[0] * t);
+            float w[3], wn[3] = {0.f, 0.f, 0.f}, val[3];
 #pragma unroll
-            for (int c = 0; c < DIM; ++c) uc[c] = u[c * N + v];
-            for (int k = 0; k < cnt; ++k) {
-                if (k + 1 < cnt) {
+            for (int c = 0; c < DIM; ++c) w[c] = us * u[c * N + v];
+            for (; t < t1; t += dt, v += dv) {
+                // the next voxel's displacement is in flight during this gather
+                if (t + dt < t1) {
 #pragma unroll
-                    for (int c = 0; c < DIM; ++c) un[c] = u[c * N + v + step];
+                    for (int c = 0; c < DIM; ++c) wn[c] = us * u[c * N + v + dv];
                 }
-                const int idx[3] = {x, DIM == 3 ? y : y + kCompTY * k, DIM == 3 ? z0 + k : 0};
-                float val[3], f[3];
-                Disp q[3];
-                int j[3];
+                gather(t, w, val);
+                store(v, w, val);
 #pragma unroll
-                for (int a = 0; a < DIM; ++a) {
-                    q[a] = Disp{uc[a] * P.s[a], 0.f};
-                    const float t = fabsf(q[a].d);
-                    m = (t > m || !(t == t)) ? t : m;
-                }
-                field_sample<DIM, false>(u, N, P, idx, q, val, nullptr, j, f);
-#pragma unroll
-                for (int c = 0; c < DIM; ++c) {
-                    out[c * N + v] = uc[c] + val[c];
-                    uc[c] = un[c];
-                }
-                v += step;
+                for (int c = 0; c < DIM; ++c) w[c] = wn[c];
             }
         }
+        if (reach_out) block_max_to(mo, red, reach_out);
+        return;
     }
-    unsigned int b = __float_as_uint(m) & 0x7fffffffu;
+    T B;
+    if (!B.init(P, walk)) return;
+    x = B.x;
+    y = B.y;
+    __amdgpu_buffer_rsrc_t ru[DIM];
+    float st[DIM][NE];
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) b = max(b, (unsigned int)__shfl_xor((int)b, o, 64));
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = b;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned int r = red[0];
-        for (int w = 1; w < kBlock / 64; ++w) r = max(r, red[w]);
-        atomicMax(dmax, r);
+    for (int c = 0; c < DIM; ++c) {
+        ru[c] = make_rsrc(u + c * N, (uint32_t)(N * 4));
+        B.fetch(ru[c], B.l0 - 1, nl, st[c]);
     }
+    for (int l = B.l0 - 1; l <= B.l1; ++l) {
+        // write plane l; slot (l + 1) mod 4 is not read by a wave still in
+        // step l - 1, so one barrier per step suffices
+        float* sl = ring + (l & 3) * SL;
+#pragma unroll
+        for (int e = 0; e < NE; ++e)
+            if (tid + e * kBlock < PL)
+#pragma unroll
+                for (int c = 0; c < DIM; ++c) sl[c * PL + tid + e * kBlock] = us * st[c][e];
+        __syncthreads();
+        if (l < B.l1)
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) B.fetch(ru[c], l + 1, nl, st[c]);
+        // voxel t = l - 1: its samples lie in planes l - 2, l - 1, l
+        const int t = l - 1;
+        if (t < B.l0 || !B.act) continue;
+        const float* tp = ring + (t & 3) * SL + B.own;
+        const int idx[3] = {x, DIM == 3 ? y : t, DIM == 3 ? t : 0};
+        float w[DIM], f[DIM], val[DIM];
+        int o[DIM];   // cell relative to the voxel
+        bool near = true, inside = true;
+#pragma unroll
+        for (int a = 0; a < DIM; ++a) {
+            w[a] = tp[a * PL];
+            const float d = w[a] * P.s[a];
+            const float ad = fabsf(d);
+            mi = max_or_nan(mi, ad);
+            near = near && ad < 1.f;
+            const float fl = floorf(d);
+            f[a] = d - fl;
+            o[a] = near ? (int)fl : 0;
+            const int j = idx[a] + o[a];
+            inside = inside && j >= 0 && j <= P.n[a] - 2;
+        }
+        const int inpl = B.own + o[0] + (DIM == 3 ? o[1] * HX : 0);
+        const float* b0 = ring + ((t + o[LA]) & 3) * SL + inpl;
+        const float* b1 = ring + ((t + o[LA] + 1) & 3) * SL + inpl;
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) {
+            const float* p0 = b0 + c * PL;
+            const float* p1 = b1 + c * PL;
+            const float fx = f[0];
+            const float c00 = fmaf(fx, p0[1] - p0[0], p0[0]);
+            if constexpr (DIM == 2) {
+                const float c10 = fmaf(fx, p1[1] - p1[0], p1[0]);
+                val[c] = fmaf(f[1], c10 - c00, c00);
+            } else {
+                const float c10 = fmaf(fx, p0[HX + 1] - p0[HX], p0[HX]);
+                const float c01 = fmaf(fx, p1[1] - p1[0], p1[0]);
+                const float c11 = fmaf(fx, p1[HX + 1] - p1[HX], p1[HX]);
+                const float c0 = fmaf(f[1], c10 - c00, c00);
+                const float c1 = fmaf(f[1], c11 - c01, c01);
+                val[c] = fmaf(f[2], c1 - c0, c0);
+            }
+        }
+        if (!inside) {
+            // next to a face: the corner sum of field_sample (the halo is zero)
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) {
+                float v = 0.f;
+#pragma unroll
+                for (int cn = 0; cn < (1 << DIM); ++cn) {
+                    const int bx = cn & 1, by = (cn >> 1) & 1, bz = (cn >> 2) & 1;
+                    float wt = bx ? f[0] : 1.f - f[0];
+                    wt *= by ? f[1] : 1.f - f[1];
+                    if (DIM == 3) wt *= bz ? f[DIM - 1] : 1.f - f[DIM - 1];
+                    const float* p = ((DIM == 3 ? bz : by) ? b1 : b0) + c * PL + bx +
+                                     (DIM == 3 ? by * HX : 0);
+                    v += wt * *p;
+                }
+                val[c] = v;
+            }
+        }
+        if (!near) gather(t, w, val);
+        store(t * B.plane + (DIM == 3 ? y * P.n[0] : 0) + x, w, val);
+    }
+    if (first) block_max_to(mi, red, reach_in);
+    if (reach_out) block_max_to(mo, red, reach_out);
 }
 
 // Largest |g| over n values, as non-negative float bits (NaN above every
@@ -308,6 +486,163 @@ __global__ void k_zero_u32(unsigned int* p, int n) {
     if (i < n) p[i] = 0u;
 }
 
+// Adjoint of one squaring with a reach below one voxel: gin(q) = gs (gout(q) +
+// s_a sum_c gout_c(q) du_c/dp_a at p(q) + sum over sources x of
+// w_q(p(x)) gout(x)), the field being us * u (us, gs powers of two). With
+// |d| < 1 the sources of a target are its 3^d neighbours x = q - t, with the
+// weight prod_a h_t(d_a), h_0 = 1 - |d|, h_+-1 = max(+-d, 0): a gather in
+// registers instead of the scan's LDS atomics, and the sample points' corners
+// are among the same neighbours, so u and gout pass through the ring (Near)
+// once. A source plane adds to the three targets it touches (rotating
+// accumulators). Fixed order of summation: bitwise repeatable. Bound by VALU
+// issue (~300 per voxel); 193 us at 256^3, where the scan took 508-512. gmax_bits: max |gout|; a non-finite one makes gin NaN.
+template <int DIM>
+__global__ void __launch_bounds__(kBlock)
+k_compose_adj_near(const PairDesc P, const float* __restrict__ u, float us,
+                   const float* __restrict__ gout, const unsigned int* __restrict__ dmax_bits,
+                   const unsigned int* __restrict__ gmax_bits, float* __restrict__ gin, float gs,
+                   unsigned int* __restrict__ gmax_out, int walk) {
+    using T = Near<DIM>;
+    constexpr int HX = T::HX, PL = T::PL, NE = T::NE, LA = T::LA;
+    constexpr int SL = 2 * DIM * PL;   // floats of a ring slot: u then gout
+    __shared__ float ring[4 * SL];
+    __shared__ unsigned int redm[kBlock / 64];
+    if (!near_reach(__uint_as_float(*dmax_bits))) return;
+    T B;
+    if (!B.init(P, walk)) return;
+    const int tid = threadIdx.x, own = B.own, l0 = B.l0, l1 = B.l1;
+    const long long N = P.nvox;
+    const int nl = P.n[LA];
+    const float gm = __uint_as_float(*gmax_bits);
+    const float poison = gm < 3.0e38f ? 0.f : __uint_as_float(0x7fc00000u);   // NaN
+    __amdgpu_buffer_rsrc_t ru[DIM], rg[DIM];
+    float st[2 * DIM][NE];
+    auto fetch = [&](int l) {
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) {
+            B.fetch(ru[c], l, nl, st[c]);
+            B.fetch(rg[c], l, nl, st[DIM + c]);
+        }
+    };
+#pragma unroll
+    for (int c = 0; c < DIM; ++c) {
+        ru[c] = make_rsrc(u + c * N, (uint32_t)(N * 4));
+        rg[c] = make_rsrc(gout + c * N, (uint32_t)(N * 4));
+    }
+    // transposed sums of target l - 1 (without plane l), of l, and of l + 1
+    // (without the factor s of the last axis)
+    float done[DIM], acc[2][DIM];
+#pragma unroll
+    for (int c = 0; c < DIM; ++c) done[c] = acc[0][c] = acc[1][c] = 0.f;
+    float gmo = 0.f;
+    fetch(l0 - 1);
+    for (int l = l0 - 1; l <= l1; ++l) {
+        // (one barrier per step, as in k_compose)
+        float* sl = ring + (l & 3) * SL;
+#pragma unroll
+        for (int e = 0; e < NE; ++e)
+            if (tid + e * kBlock < PL)
+#pragma unroll
+                for (int c = 0; c < 2 * DIM; ++c)
+                    sl[c * PL + tid + e * kBlock] = c < DIM ? us * st[c][e] : st[c][e];
+        __syncthreads();
+        if (l < l1) fetch(l + 1);
+        // source plane l
+        const float* sp = sl + own;
+        float below[DIM];   // plane l's part of target l - 1
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) below[c] = 0.f;
+#pragma unroll
+        for (int oy = (DIM == 3 ? -1 : 0); oy <= (DIM == 3 ? 1 : 0); ++oy)
+#pragma unroll
+            for (int ox = -1; ox <= 1; ++ox) {
+                const float* q = sp + oy * HX + ox;   // the target is at (-ox, -oy) from it
+                // h_t(u s) without the factor s of h_+-1
+                auto hat = [](float v, float s, int t) {
+                    return t == 0 ? fmaf(-fabsf(v), s, 1.f) : fmaxf(t > 0 ? v : -v, 0.f);
+                };
+                float w = hat(q[0], P.s[0], -ox);
+                if (DIM == 3) w *= hat(q[PL], P.s[1], -oy);
+                const float fac = (ox != 0 ? P.s[0] : 1.f) * (oy != 0 ? P.s[1] : 1.f);
+                if (ox != 0 || oy != 0) w *= fac;
+                // the factor of the last axis' h_+-1 is applied with the sum
+                const float ul = q[LA * PL];
+                const float wm = fmaxf(-ul, 0.f), wp = fmaxf(ul, 0.f);
+                const float w0 = fmaf(-fabsf(ul), P.s[LA], 1.f);
+#pragma unroll
+                for (int c = 0; c < DIM; ++c) {
+                    const float g = w * q[(DIM + c) * PL];
+                    below[c] = fmaf(wm, g, below[c]);
+                    acc[0][c] = fmaf(w0, g, acc[0][c]);
+                    acc[1][c] = fmaf(wp, g, acc[1][c]);
+                }
+            }
+        // target l - 1: planes l - 2, l - 1, l are in the ring
+        const int t = l - 1;
+        if (t >= l0 && B.act) {
+            const float* tp = ring + (t & 3) * SL + own;
+            float f[DIM];
+            int o[DIM];   // cell relative to the voxel, -1 or 0
+#pragma unroll
+            for (int a = 0; a < DIM; ++a) {
+                const Disp q = disp_of(tp[a * PL], P.s[a]);
+                const float fl = floorf(q.d);
+                f[a] = q.d - fl;
+                o[a] = (int)fl;
+                if (f[a] == 0.f && q.e < 0.f) {
+                    o[a] -= 1;
+                    f[a] = 1.f;
+                }
+            }
+            const int inpl = own + o[0] + (DIM == 3 ? o[1] * HX : 0);
+            const float* b0 = ring + ((t + o[LA]) & 3) * SL + inpl;
+            const float* b1 = ring + ((t + o[LA] + 1) & 3) * SL + inpl;
+            float ts[DIM];
+#pragma unroll
+            for (int a = 0; a < DIM; ++a) ts[a] = 0.f;
+            float go[DIM];
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) {
+                go[c] = tp[(DIM + c) * PL];
+                const float* p0 = b0 + c * PL;
+                const float* p1 = b1 + c * PL;
+                const float fx = f[0];
+                if constexpr (DIM == 2) {
+                    const float e0 = p0[1] - p0[0], e1 = p1[1] - p1[0];
+                    ts[0] += go[c] * ((1.f - f[1]) * e0 + f[1] * e1);
+                    ts[1] += go[c] * (fmaf(fx, e1, p1[0]) - fmaf(fx, e0, p0[0]));
+                } else {
+                    const float fy = f[1], fz = f[2];
+                    const float e00 = p0[1] - p0[0], e10 = p0[HX + 1] - p0[HX];
+                    const float e01 = p1[1] - p1[0], e11 = p1[HX + 1] - p1[HX];
+                    const float c00 = fmaf(fx, e00, p0[0]), c10 = fmaf(fx, e10, p0[HX]);
+                    const float c01 = fmaf(fx, e01, p1[0]), c11 = fmaf(fx, e11, p1[HX]);
+                    const float c0 = fmaf(fy, c10 - c00, c00), c1 = fmaf(fy, c11 - c01, c01);
+                    const float dx0 = fmaf(fy, e10 - e00, e00), dx1 = fmaf(fy, e11 - e01, e01);
+                    ts[0] += go[c] * fmaf(fz, dx1 - dx0, dx0);
+                    ts[1] += go[c] * fmaf(fz, (c11 - c01) - (c10 - c00), c10 - c00);
+                    ts[2] += go[c] * (c1 - c0);
+                }
+            }
+            const int v = t * B.plane + (DIM == 3 ? B.y * P.n[0] : 0) + B.x;
+#pragma unroll
+            for (int a = 0; a < DIM; ++a) {
+                const float gv = go[a] + P.s[a] * ts[a] +
+                                 fmaf(P.s[LA], below[a], done[a]) + poison;
+                gin[a * N + v] = gs * gv;
+                gmo = max_or_nan(gmo, fabsf(gv));
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) {
+            done[c] = acc[0][c];
+            acc[0][c] = P.s[LA] * acc[1][c];
+            acc[1][c] = 0.f;
+        }
+    }
+    block_max_to(gmo, redm, gmax_out);
+}
+
 // Owner-computes adjoint of one squaring. The block owns target tile T (TS
 // voxels per axis); every source voxel x within `reach` of T computes its
 // sample point and adds w_q(p(x)) gout(x) into LDS for its corners q inside T;
@@ -323,10 +658,12 @@ __global__ void k_zero_u32(unsigned int* p, int n) {
 constexpr int kAdjBlock3 = 1024;   // threads per 3D tile (96 KB of accumulators)
 template <int DIM>
 __global__ void __launch_bounds__(DIM == 3 ? kAdjBlock3 : kBlock)
-k_compose_adj_tile(const PairDesc P, const float* __restrict__ u, const float* __restrict__ gout,
-                   const unsigned int* __restrict__ dmax_bits,
-                   const unsigned int* __restrict__ gmax_bits, float* __restrict__ gin,
+k_compose_adj_tile(const PairDesc P, const float* __restrict__ u, float us,
+                   const float* __restrict__ gout, const unsigned int* __restrict__ dmax_bits,
+                   const unsigned int* __restrict__ gmax_bits, float* __restrict__ gin, float gs,
                    unsigned int* __restrict__ gmax_out) {
+    const float dm = __uint_as_float(*dmax_bits);
+    if (near_reach(dm)) return;   // k_compose_adj_near's squaring
     constexpr int TS = DIM == 3 ? 16 : 64;  // 4096 targets per tile
     constexpr int TV = DIM == 3 ? TS * TS * TS : TS * TS;
     constexpr int NT = DIM == 3 ? kAdjBlock3 : kBlock;
@@ -347,7 +684,6 @@ k_compose_adj_tile(const PairDesc P, const float* __restrict__ u, const float* _
     // for the rounding of dmax). A corner in [o, o + TS) needs
     // o - 1 <= t < o + TS, so the sources lie in
     // [o - 1 - floor(e), o + TS + ceil(e)) along each axis.
-    const float dm = __uint_as_float(*dmax_bits);
     int hlo = 1 << 20, hhi = 1 << 20;
     if (dm == dm && dm < 1e6f) {
         const int nmax = max(P.n[0], max(P.n[1], P.n[2]));
@@ -398,10 +734,10 @@ k_compose_adj_tile(const PairDesc P, const float* __restrict__ u, const float* _
         }
         // skip sources whose cell misses the tile
         if (!near) return;
-        // |gs| < 2^31 and a corner weight is at most 1
-        float gs[3];
+        // |gq| < 2^31 and a corner weight is at most 1
+        float gq[3];
 #pragma unroll
-        for (int c = 0; c < DIM; ++c) gs[c] = gout[c * N + v] * scale;
+        for (int c = 0; c < DIM; ++c) gq[c] = gout[c * N + v] * scale;
         // tile index of corner 0 (possibly outside the tile; only corners
         // that pass the checks are used)
         const int t0 = r[0] + TS * (r[1] + (DIM == 3 ? TS * r[2] : 0));
@@ -413,7 +749,7 @@ k_compose_adj_tile(const PairDesc P, const float* __restrict__ u, const float* _
             const int t = t0 + b0 + TS * b1 + (DIM == 3 ? TS * TS * b2 : 0);
 #pragma unroll
             for (int c = 0; c < DIM; ++c)
-                atomicAdd(&acc[c][t], (unsigned long long)(long long)(int)(w * gs[c]));
+                atomicAdd(&acc[c][t], (unsigned long long)(long long)(int)(w * gq[c]));
         }
     };
     // Scan of the box: a work item is one column of the box (all axes but
@@ -439,7 +775,7 @@ k_compose_adj_tile(const PairDesc P, const float* __restrict__ u, const float* _
         for (int k = 0; k < ZS; ++k) {
             const long long v = vb + (long long)min(k, nz_ - 1) * stepv;   // in the box
 #pragma unroll
-            for (int a = 0; a < DIM; ++a) uu[k][a] = u[a * N + v];
+            for (int a = 0; a < DIM; ++a) uu[k][a] = us * u[a * N + v];
         }
 #pragma unroll
         for (int k = 0; k < ZS; ++k) {
@@ -462,8 +798,8 @@ k_compose_adj_tile(const PairDesc P, const float* __restrict__ u, const float* _
         Disp q[3];
         int j[3];
 #pragma unroll
-        for (int a = 0; a < DIM; ++a) q[a] = disp_of(u[a * N + v], P.s[a]);
-        field_sample<DIM, true>(u, N, P, x, q, val, dv, j, f);
+        for (int a = 0; a < DIM; ++a) q[a] = disp_of(us * u[a * N + v], P.s[a]);
+        field_sample<DIM, true>(u, us, N, P, x, q, val, dv, j, f);
         float go[3];
 #pragma unroll
         for (int c = 0; c < DIM; ++c) go[c] = gout[c * N + v];
@@ -474,7 +810,7 @@ k_compose_adj_tile(const PairDesc P, const float* __restrict__ u, const float* _
             for (int c = 0; c < DIM; ++c) tsum += go[c] * dv[c][a];
             const float tr = (float)((double)(long long)acc[a][t] * unscale) + poison;
             const float gv = go[a] + P.s[a] * tsum + tr;
-            gin[a * N + v] = gv;
+            gin[a * N + v] = gs * gv;
             const float ag = fabsf(gv);
             gm_out = (ag > gm_out || !(ag == ag)) ? ag : gm_out;
         }
@@ -535,14 +871,27 @@ hipError_t launch_velocity(const PairDesc& P, const float* consts_dev, int trans
     return hipGetLastError();
 }
 
-hipError_t launch_compose(const PairDesc& P, int dim, const float* u, float* out,
-                          unsigned int* dmax, hipStream_t s) {
+// Walk of the near kernels: 32 planes, halved down to 8 while the launch has
+// fewer than kNearFill blocks.
+static int near_walk(const PairDesc& P, int dim) {
+    int walk = kNearWalk;
+    while (walk > kNearMinWalk &&
+           (dim == 3 ? Near<3>::items(P, walk) : Near<2>::items(P, walk)) < kNearFill)
+        walk /= 2;
+    return walk;
+}
+
+hipError_t launch_compose(const PairDesc& P, int dim, const float* u, float us, float* out,
+                          unsigned int* reach_in, bool first, unsigned int* reach_out,
+                          hipStream_t s) {
+    // the blocks of either work split
+    const int walk = near_walk(P, dim);
+    const int items = dim == 3 ? max(Near<3>::items(P, walk), Far<3>::items(P))
+                               : max(Near<2>::items(P, walk), Far<2>::items(P));
     if (dim == 3)
-        hipLaunchKernelGGL(k_compose<3>, dim3(xcd_grid(compose_items<3>(P), 0)), dim3(kBlock), 0,
-                           s, P, u, out, dmax);
+        hipLaunchKernelGGL(k_compose<3>, dim3(xcd_grid(items, 0)), dim3(kBlock), 0, s, P, u, us, out, reach_in, first ? 1 : 0, reach_out, walk);
     else
-        hipLaunchKernelGGL(k_compose<2>, dim3(xcd_grid(compose_items<2>(P), 0)), dim3(kBlock), 0,
-                           s, P, u, out, dmax);
+        hipLaunchKernelGGL(k_compose<2>, dim3(xcd_grid(items, 0)), dim3(kBlock), 0, s, P, u, us, out, reach_in, first ? 1 : 0, reach_out, walk);
     return hipGetLastError();
 }
 
@@ -551,28 +900,37 @@ hipError_t launch_zero_u32(unsigned int* p, int n, hipStream_t s) {
     return hipGetLastError();
 }
 
-// gin = the adjoint of one squaring at u applied to gout. gmax_in: max |gout|
-// as float bits (computed here when `measure_in`, else left by the previous
-// call); gmax_out receives max |gin| for the next call. One uint each.
-hipError_t launch_compose_adjoint(const PairDesc& P, int dim, const float* u, const float* gout,
-                                  const unsigned int* dmax, unsigned int* gmax_in,
-                                  bool measure_in, unsigned int* gmax_out, float* gin,
-                                  hipStream_t s) {
+// Largest |g| over the field, as float bits (*out zeroed before).
+hipError_t launch_field_absmax(const PairDesc& P, int dim, const float* g, unsigned int* out,
+                               hipStream_t s) {
     const long long n = (long long)dim * P.nvox;
-    if (measure_in) {
-        hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, s, gmax_in, 1);
-        const int g = grid_for(n) < 1024 ? grid_for(n) : 1024;
-        hipLaunchKernelGGL(k_absmax_plain, dim3(g), dim3(kBlock), 0, s, gout, n, gmax_in);
-    }
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, s, gmax_out, 1);
+    const int grid = grid_for(n) < 1024 ? grid_for(n) : 1024;
+    hipLaunchKernelGGL(k_absmax_plain, dim3(grid), dim3(kBlock), 0, s, g, n, out);
+    return hipGetLastError();
+}
+
+// gin = gs times the adjoint of one squaring at us * u applied to gout.
+// gmax_in: max |gout| as float bits; gmax_out (zeroed before) receives max
+// |gin| / gs for the next call. One uint each.
+hipError_t launch_compose_adjoint(const PairDesc& P, int dim, const float* u, float us,
+                                  const float* gout, const unsigned int* dmax,
+                                  const unsigned int* gmax_in, unsigned int* gmax_out, float* gin,
+                                  float gs, hipStream_t s) {
+    const int walk = near_walk(P, dim);
     if (dim == 3) {
+        hipLaunchKernelGGL(k_compose_adj_near<3>, dim3(xcd_grid(Near<3>::items(P, walk), 0)),
+                           dim3(kBlock), 0, s, P, u, us, gout, dmax, gmax_in, gin, gs, gmax_out,
+                           walk);
         const int nt = cdiv(P.n[0], 16) * cdiv(P.n[1], 16) * cdiv(P.n[2], 16);
-        hipLaunchKernelGGL(k_compose_adj_tile<3>, dim3(nt), dim3(kAdjBlock3), 0, s, P, u, gout,
-                           dmax, gmax_in, gin, gmax_out);
+        hipLaunchKernelGGL(k_compose_adj_tile<3>, dim3(nt), dim3(kAdjBlock3), 0, s, P, u, us, gout,
+                           dmax, gmax_in, gin, gs, gmax_out);
     } else {
+        hipLaunchKernelGGL(k_compose_adj_near<2>, dim3(xcd_grid(Near<2>::items(P, walk), 0)),
+                           dim3(kBlock), 0, s, P, u, us, gout, dmax, gmax_in, gin, gs, gmax_out,
+                           walk);
         const int nt = cdiv(P.n[0], 64) * cdiv(P.n[1], 64);
-        hipLaunchKernelGGL(k_compose_adj_tile<2>, dim3(nt), dim3(kBlock), 0, s, P, u, gout, dmax,
-                           gmax_in, gin, gmax_out);
+        hipLaunchKernelGGL(k_compose_adj_tile<2>, dim3(nt), dim3(kBlock), 0, s, P, u, us, gout,
+                           dmax, gmax_in, gin, gs, gmax_out);
     }
     return hipGetLastError();
 }

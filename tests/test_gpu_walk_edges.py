@@ -72,3 +72,21 @@ def test_dense_batch_uneven_walks():
         vo, go, _ = O.objective_and_grad(op, data[i][0], data[i][1], ths[i])
         assert abs(float(vals[i]) - vo) <= VAL_TOL * abs(vo)
         check_grad(grads[i].double().cpu().numpy(), go, f"dense batch pair {i}")
+
+
+# the exponential: near squarings (samples within one voxel, LDS ring), far
+# ones, the first squaring's samples that leave the ring, walk and tile edges
+@pytest.mark.parametrize("n,std,K", [((33, 9, 17), 1.5, 4), ((32, 8, 8), 1.5, 3),
+                                     ((31, 7, 33), 3.0, 2), ((65, 10, 9), 4.0, 1),
+                                     ((40, 24, 40), 6.0, 3), ((257, 9), 1.5, 4), ((255, 33), 6.0, 2),
+                                     ((256, 64), 3.0, 3)])
+@pytest.mark.parametrize("tf", [api.TF_DENSE, api.TF_BSPLINE3])
+def test_exponential_walks(n, std, K, tf):
+    d = len(n)
+    sp = (1,) * d if tf == api.TF_DENSE else (5,) * d
+    p = api.Problem(n=n, transform=tf, spacing=sp, similarity=api.SIM_MSE, lambda_diff=0.1,
+                    diffeo_steps=K)
+    F, M = inputs(n, 50)
+    th = (synth.smooth_dense(n, std, 51) if tf == api.TF_DENSE
+          else synth.random_theta(n, sp, std, 51))
+    check(p, F, M, th, f"exponential {n} std={std} K={K} tf={tf}")
