@@ -429,7 +429,7 @@ def run_batch(args, dev, sizes, workload, desc, seed_base=1):
                    "step_hbm_gbs": bytes_eval / (ms_step / 1e3) / 1e9},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                      "frac": achieved / PEAK_HBM_GBS, "traffic": traffic,
-                     "kernel": "k_fused3_s8 (NCC)", "kernel_ms": kern_ms,
+                     "kernel": "k_fused3_tile (NCC)", "kernel_ms": kern_ms,
                      "algorithmic_bytes_per_launch": bytes_fused,
                      "pipes": pipes_for(workload)},
     }

@@ -139,6 +139,13 @@ struct LaunchCtx {
                                // (float bits; zero before the launch)
 };
 
+// What the fused B-spline launch needs beside its context.
+struct FusedShape {
+    size_t lds = 0;       // bytes of dynamic LDS of a block
+    int max_ctrl = 0;     // most controls of a pair
+    int ctrl_tiles = 0;   // most tiles whose window holds one control
+};
+
 __host__ __device__ inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 // round a float count up to a multiple of 4 (16-byte aligned LDS carve-up)
 __host__ __device__ inline int a4(int n) { return (n + 3) & ~3; }

@@ -16,7 +16,7 @@
 #include "air_internal.h"
 
 namespace air {
-hipError_t launch_bspline(const LaunchCtx& C, int cfg, size_t lds, int max_ctrl, hipStream_t s,
+hipError_t launch_bspline(const LaunchCtx& C, int cfg, const FusedShape& F, hipStream_t s,
                           hipEvent_t ev0, hipEvent_t ev1);
 hipError_t launch_reg_bspline(const PairDesc* dpairs, const PairDesc& hp, int pair,
                               const float* consts, const float* theta, float* grad_out,
@@ -87,7 +87,7 @@ static const TileCfg kCfg3[] = {
     {16, 16, 4}, {16, 16, 16}, {32, 8, 2}, {16, 16, 8}, {16, 16, 2},
 };
 static const TileCfg kCfg2[] = {{64, 1, 2}, {64, 1, 4}, {64, 1, 8}, {64, 1, 16}, {64, 1, 1}};
-// candidates of the default 3D spacing-8 configuration, longest column first
+// candidates of the default 3D configuration, longest column first
 // (16 x 16 with 16, 8, 4, 2 cells), and the tile count that fills the chip
 static const int kCfg3Fill[] = {6, 8, 5, 9};
 constexpr int kFillTiles = 4096;
@@ -97,15 +97,34 @@ constexpr int kFillTiles = 4096;
 // 4-cell (500 tiles) against 46.1 with 8-cell (300) and 39.3 with 2-cell
 // (1000)
 constexpr int kTwoTilesPerCu = 448;
+// another spacing: a walk longer than this many planes is cut further, until
+// the launch has kLongTiles:
+// 181 x 217 x 181 with spacing 10 61.6 us with 4-cell columns (40 planes, 840
+// tiles) against 67.3 with 8-cell (80 planes, 504); 150 x 190 x 128 with
+// spacing 4 62.8 with 8-cell (32 planes, 480) against 67.4 with 4-cell (840)
+constexpr int kLongWalk = 48, kLongTiles = 800;
 // the same for 2D B-spline plans (64-lane columns of 16, 8, 4, 2, 1 cells)
 static const int kCfg2Fill[] = {3, 2, 1, 0, 4};
 constexpr int kFillTiles2 = 2048;
 
-// kernel variant ids understood by launch_bspline (3D)
-static int variant_of(const TileCfg& c, bool all_s8) {
-    if (c.tx == 32 && c.ty == 8) return all_s8 ? 3 : 0;
-    if (c.tx == 16 && c.ty == 16) return all_s8 ? 4 : 2;
-    return 1;  // 64 x 4
+// kernel variant ids understood by launch_bspline (3D): 3, 4 the spacing-8
+// kernels, 5 - 7 the pipelined kernel of any spacing whose tiles see at most
+// 16 controls along x and y, 0 - 2 the general one (spacing 1 or 2 along a
+// long tile side, say)
+static int variant_of(const TileCfg& c, bool all_s8, bool win16) {
+    if (c.tx == 32 && c.ty == 8) return all_s8 ? 3 : (win16 ? 5 : 0);
+    if (c.tx == 16 && c.ty == 16) return all_s8 ? 4 : (win16 ? 7 : 2);
+    return win16 ? 6 : 1;  // 64 x 4
+}
+// largest control window of the tiles of `t` voxels along an axis
+static int max_window(int n, int t, int sp) {
+    int m = 0;
+    for (int v = 0; v < n; v += t) {
+        int c0, w;
+        ctrl_window(v, std::min(v + t, n), sp, &c0, &w);
+        m = std::max(m, w);
+    }
+    return m;
 }
 constexpr int kNumCfg3 = sizeof(kCfg3) / sizeof(kCfg3[0]);
 constexpr int kNumCfg2 = sizeof(kCfg2) / sizeof(kCfg2[0]);
@@ -133,8 +152,8 @@ struct air_plan {
     std::vector<float> consts;
     WsLayout L{};
     int ntiles_total = 0, nreg_total = 0;
-    size_t lds_fused = 0, lds_reg = 0;
-    int max_ctrl = 0;
+    FusedShape fused;
+    size_t lds_reg = 0;
     int max_dense_blk = 0;
     int dense_zc = 0;  // walk length of the dense passes' blocks (dense_walk)
     int variant = 0;
@@ -153,9 +172,10 @@ struct air_plan {
 
 // ------------------------------------------------------------------ tables
 // Cubic B-spline weights of a voxel at offset r in its cell (t = r / sp):
-// beta3(t + 1), beta3(t), beta3(1 - t), beta3(2 - t).
+// beta3(t + 1), beta3(t), beta3(1 - t), beta3(2 - t). The row after the last
+// offset (t = 1) is the next cell's first voxel seen from this cell.
 static void spline_weights(int sp, std::vector<float>& out) {
-    for (int r = 0; r < sp; ++r) {
+    for (int r = 0; r <= sp; ++r) {
         const double t = (double)r / sp;
         const double w0 = (1 - t) * (1 - t) * (1 - t) / 6.0;
         const double w1 = (3 * t * t * t - 6 * t * t + 4) / 6.0;
@@ -360,7 +380,7 @@ static int dense_walk(const air_plan* P) {
     return zc;
 }
 
-static air_status build_tables(air_plan* P, int dense_zc) {
+static air_status build_tables(air_plan* P, int dense_zc, bool pipelined) {
     const int d = P->dim;
     P->dense_zc = dense_zc;
     const bool bs = P->transform == AIR_TF_BSPLINE3;
@@ -373,14 +393,20 @@ static air_status build_tables(air_plan* P, int dense_zc) {
             if (P->probs[i].spacing[a] != 8) all_s8 = false;
     // 3D: the tile configuration and its kernel; 2D: 8 when every pair has
     // spacing 8 (its finalize then takes the spacing at compile time)
-    P->variant = (d == 3) ? variant_of(cfg, all_s8) : (all_s8 ? 8 : 0);
+    bool win16 = bs && d == 3 && pipelined;
+    for (int i = 0; i < P->npairs && win16 && !all_s8; ++i) {
+        const air_problem& p = P->probs[i];
+        win16 = max_window(p.n[0], cfg.tx, p.spacing[0]) <= 16 &&
+                max_window(p.n[1], cfg.ty, p.spacing[1]) <= 16;
+    }
+    P->variant = (d == 3) ? variant_of(cfg, all_s8, win16) : (all_s8 ? 8 : 0);
     const bool s8 = d == 3 && (P->variant == 3 || P->variant == 4);
     P->pd.assign(P->npairs, PairDesc{});
     P->consts.clear();
     size_t stats_n = 0, part_n = 0, param_n = 0, regpart_n = 0, dense_n = 0;
     int tiles = 0, regs = 0;
     size_t lds_f = 0, lds_r = 0;
-    int max_ctrl = 0, max_dense = 0;
+    int max_ctrl = 0, ctrl_tiles = 0, max_dense = 0;
     for (int i = 0; i < P->npairs; ++i) {
         const air_problem& p = P->probs[i];
         PairDesc& D = P->pd[i];
@@ -425,21 +451,11 @@ static air_status build_tables(air_plan* P, int dense_zc) {
             const int ncell = (D.n[col] - 1) / D.sp[col] + 1;
             const int cells = std::min(cfg.cells, ncell);
             D.col_cells = cells;
-            int wxm = 0, wym = 1;
             const int ntx = cdiv(D.n[0], cfg.tx);
-            for (int t = 0; t < ntx; ++t) {
-                int c0, w;
-                ctrl_window(t * cfg.tx, std::min(t * cfg.tx + cfg.tx, D.n[0]), D.sp[0], &c0, &w);
-                wxm = std::max(wxm, w);
-            }
+            const int wxm = max_window(D.n[0], cfg.tx, D.sp[0]);
+            const int wym = d == 3 ? max_window(D.n[1], cfg.ty, D.sp[1]) : 1;
             if (d == 3) {
                 const int nty = cdiv(D.n[1], cfg.ty);
-                for (int t = 0; t < nty; ++t) {
-                    int c0, w;
-                    ctrl_window(t * cfg.ty, std::min(t * cfg.ty + cfg.ty, D.n[1]), D.sp[1], &c0,
-                                &w);
-                    wym = std::max(wym, w);
-                }
                 D.ntile[0] = ntx;
                 D.ntile[1] = nty;
                 D.ntile[2] = cdiv(ncell, cells);
@@ -454,6 +470,14 @@ static air_status build_tables(air_plan* P, int dense_zc) {
             D.ntiles = D.ntile[0] * D.ntile[1] * D.ntile[2];
             D.tile_begin = tiles;
             tiles += D.ntiles;
+            // a control's support is 4 sp voxels (4 cells along the column)
+            auto reach_tiles = [](int support, int tile, int have) {
+                return std::min((support + tile - 2) / tile + 1, have);
+            };
+            ctrl_tiles = std::max(
+                ctrl_tiles, reach_tiles(4 * D.sp[0], cfg.tx, D.ntile[0]) *
+                                (d == 3 ? reach_tiles(4 * D.sp[1], cfg.ty, D.ntile[1]) : 1) *
+                                reach_tiles(4, cells, cdiv(ncell, cells)));
             D.part_stride = NF * d * D.win[2] * D.win[1] * D.win[0];
             D.part_off = (long long)part_n;
             part_n += (size_t)D.ntiles * D.part_stride;
@@ -465,6 +489,10 @@ static air_status build_tables(air_plan* P, int dense_zc) {
                 const int wyc = cfg.ty / 8 + 3, gp = cfg.tx + 4;
                 f = a4(3 * D.win[2] * wyc * cfg.tx) + a4(NF * 3 * cfg.ty * cfg.tx) +
                     a4(NF * 3 * wyc * gp);
+            } else if (d == 3 && P->variant >= 5) {
+                const int ep = cfg.tx + (80 - cfg.tx % 64) % 64, gp = cfg.tx + 4;
+                f = a4(3 * D.win[2] * wym * cfg.tx) + a4(NF * 3 * cfg.ty * ep) +
+                    ((NF * 3 * wym + 15) & ~15) * gp + (cfg.tx + cfg.ty) * 16;
             } else if (d == 3) {
                 f = a4(3 * D.win[2] * wym * cfg.tx) + a4(NF * 3 * cfg.ty * cfg.tx) +
                     a4(NF * 3 * wym * cfg.tx) + a4(cfg.tx * wxm) + a4(cfg.ty * wym) +
@@ -514,9 +542,10 @@ static air_status build_tables(air_plan* P, int dense_zc) {
     if (P->sim == AIR_SIM_LCC && lcc_lds_bytes(P->lcc_radius) > kMaxLds) return AIR_ERR_UNSUPPORTED;
     P->ntiles_total = tiles;
     P->nreg_total = regs;
-    P->lds_fused = lds_f;
+    P->fused.lds = lds_f;
     P->lds_reg = lds_r;
-    P->max_ctrl = max_ctrl;
+    P->fused.max_ctrl = max_ctrl;
+    P->fused.ctrl_tiles = ctrl_tiles;
     P->max_dense_blk = max_dense;
     WsLayout& L = P->L;
     size_t off = 0;
@@ -567,12 +596,17 @@ static air_status build_tables(air_plan* P, int dense_zc) {
 
 static air_status build_tables(air_plan* P) {
     const int zc = dense_walk(P);
-    air_status st = build_tables(P, zc);
+    const int longest = P->dim == 3 ? kDenseZc : kDenseRows2;
+    auto fits = [&](size_t total) { return total <= AIR_NOALLOC_SCRATCH_BYTES; };
+    air_status st = build_tables(P, zc, true);
+    // the pipelined kernel of any spacing pads its LDS: where that is too
+    // much, the general kernel
+    const bool pipelined = !(st == AIR_ERR_UNSUPPORTED && P->variant >= 5 && P->dim == 3);
+    if (!pipelined) st = build_tables(P, zc, false);
     // more blocks need more partial sums: a plan that fits the scratch array
     // of air_objective_and_grad_noalloc with the longest walk keeps that walk
     // when the shorter one takes it past the array
-    const int longest = P->dim == 3 ? kDenseZc : kDenseRows2;
-    if (st == AIR_OK && zc < longest && P->L.total > AIR_NOALLOC_SCRATCH_BYTES) {
+    if (st == AIR_OK && zc < longest && !fits(P->L.total)) {
         size_t now = 0, then = 0;
         for (const PairDesc& D : P->pd) {
             now += D.dense_nblk;
@@ -581,10 +615,46 @@ static air_status build_tables(air_plan* P) {
         auto stats = [](size_t n) {
             return align256(std::max<size_t>(n, 1) * kStatWords * sizeof(double));
         };
-        if (P->L.total - stats(now) + stats(then) <= AIR_NOALLOC_SCRATCH_BYTES)
-            st = build_tables(P, longest);
+        if (fits(P->L.total - stats(now) + stats(then))) st = build_tables(P, longest, pipelined);
     }
     return st;
+}
+
+// Default tile configuration of a B-spline plan; the tables are built with
+// configuration 0. 3D: 16 x 16 columns, the longest (16, 8, 4, 2 cells) whose
+// launch has kFillTiles tiles, else the longest with about two per CU
+// (kTwoTilesPerCu; of another spacing than 8, a walk of more than kLongWalk
+// planes asks for kLongTiles), else the one with the most tiles; 2D: the longest column (16 .. 1 cells)
+// with kFillTiles2 tiles, else the most tiles. A configuration that cannot be
+// built, or that takes a plan past the scratch array of
+// air_objective_and_grad_noalloc which configuration 0 keeps it within, is
+// passed over.
+static air_status default_tiling(air_plan* P) {
+    const bool two = P->dim == 2;
+    const int* cand = two ? kCfg2Fill : kCfg3Fill;
+    const int ncand = two ? 5 : 4;
+    const int fill = two ? kFillTiles2 : kFillTiles;
+    const bool scratch = P->L.total <= AIR_NOALLOC_SCRATCH_BYTES;
+    int chosen = -1, per_cu = -1;
+    for (int k = 0; k < ncand; ++k) {
+        P->tiling = cand[k];
+        if (build_tables(P) != AIR_OK) continue;
+        if (scratch && P->L.total > AIR_NOALLOC_SCRATCH_BYTES) continue;
+        chosen = cand[k];
+        if (P->ntiles_total >= fill) break;
+        if (!two && per_cu < 0) {
+            int walk = 0;   // planes of the longest column (not of spacing 8)
+            for (const PairDesc& D : P->pd)
+                if (P->variant >= 5) walk = std::max(walk, D.col_cells * D.sp[2]);
+            if (P->ntiles_total >= (walk > kLongWalk ? kLongTiles : kTwoTilesPerCu))
+                per_cu = cand[k];
+        }
+    }
+    if (P->ntiles_total < fill && per_cu >= 0) chosen = per_cu;
+    if (chosen < 0) chosen = 0;
+    if (chosen == P->tiling) return AIR_OK;   // built last
+    P->tiling = chosen;
+    return build_tables(P);
 }
 
 static void release_device(air_plan* P) {
@@ -880,7 +950,7 @@ static air_status run_objective(const air_plan* cP, LaunchCtx& C, hipStream_t s)
     }
     if (P->transform == AIR_TF_BSPLINE3) {
         TraceRange r("air.stage.fused_bspline_and_finalize");
-        e = launch_bspline(C, P->variant, P->lds_fused, P->max_ctrl, s, e0, e1);
+        e = launch_bspline(C, P->variant, P->fused, s, e0, e1);
     } else {
         TraceRange r("air.stage.dense_passes");
         e = launch_dense(C, P->dense_zc, P->max_dense_blk, s, e0, e1);
@@ -1033,33 +1103,13 @@ air_status air_plan_create(const air_problem* probs, int32_t npairs, air_plan** 
         delete P;
         return st;
     }
-    // Default tile configuration of 3D spacing-8 B-spline plans: 16 x 16
-    // columns, the longest column (16, 8, 4, 2 cells) whose launch still has
-    // kFillTiles tiles, else the longest with about two per CU (kTwoTilesPerCu),
-    // else the one with the most tiles; of 2D B-spline plans: the longest
-    // column (16 .. 1 cells) with kFillTiles2 tiles, else the most tiles.
+    // Default tile configuration of B-spline plans (default_tiling below).
     // air_plan_set_tiling (and the autotuner) override it.
-    const bool bs2 = P->dim == 2 && P->transform == AIR_TF_BSPLINE3;
-    if (P->variant == 3 || bs2) {
-        int chosen = -1, per_cu = -1;
-        const int* cand = bs2 ? kCfg2Fill : kCfg3Fill;
-        const int ncand = bs2 ? 5 : 4;
-        const int fill = bs2 ? kFillTiles2 : kFillTiles;
-        for (int k = 0; k < ncand; ++k) {
-            P->tiling = cand[k];
-            if (build_tables(P) != AIR_OK) continue;
-            chosen = cand[k];
-            if (P->ntiles_total >= fill) break;
-            if (!bs2 && per_cu < 0 && P->ntiles_total >= kTwoTilesPerCu) per_cu = cand[k];
-        }
-        if (P->ntiles_total < fill && per_cu >= 0) chosen = per_cu;
-        if (chosen != P->tiling) {
-            P->tiling = chosen >= 0 ? chosen : 0;
-            st = build_tables(P);
-            if (st != AIR_OK) {
-                delete P;
-                return st;
-            }
+    if (P->transform == AIR_TF_BSPLINE3) {
+        st = default_tiling(P);
+        if (st != AIR_OK) {
+            delete P;
+            return st;
         }
     }
     *out = P;

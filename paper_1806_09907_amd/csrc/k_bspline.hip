@@ -269,7 +269,7 @@ k_fused3(const LaunchCtx C) {
     __syncthreads();
 
     // z-controls kept multiplied by the axis scale s_a (voxels per unit of
-    // u), as in k_fused3_s8, so both kernels form the same displacements
+    // u), as in k_fused3_tile, so both kernels form the same displacements
     const float snx = P.s[0], sny = P.s[1], snz = P.s[2];
     const float sc[3] = {snx, sny, snz};
     auto vcol = [&](int c, int kz) -> float {
@@ -347,7 +347,7 @@ k_fused3(const LaunchCtx C) {
                 const long long v = ((long long)z * ny + y) * nx + x;
                 const float Fv = F[v];
                 // displacement in voxels, d = u (n - 1)/2, summed in the same
-                // order as k_fused3_s8; cell and mask of x + d
+                // order as k_fused3_tile; cell and mask of x + d
                 float dd[3];
 #pragma unroll
                 for (int c = 0; c < 3; ++c)
@@ -470,14 +470,20 @@ k_fused3(const LaunchCtx C) {
     }
 }
 
-// --------------------------------------------------------------- fused 3D, spacing 8
-// The same computation as k_fused3 for control spacing 8 on every axis with
-// cell-aligned tiles (TX, TY multiples of 8): the cell structure and the
-// cubic weights w_k(r/8) are compile-time, the voxel body is branch-free, the
-// gathers of the next layer are in flight while the current one finishes,
-// the per-plane register slots rotate instead of shifting, and the LDS
-// transposes read each staged value once. The kernel is bound by VALU issue
-// (about 125 vector instructions per voxel for NCC), not by HBM.
+// --------------------------------------------------------------- fused 3D, pipelined
+// The same computation as k_fused3 with a branch-free voxel body, the gathers
+// of the next layer in flight while the current one finishes, and per-plane
+// register slots that rotate instead of shifting.
+// SP = 8: control spacing 8 on every axis with cell-aligned tiles (TX, TY
+// multiples of 8): the cell structure and the cubic weights w_k(r/8) are
+// compile-time and the LDS transposes read each staged value once. Bound by
+// VALU issue (139 vector instructions per voxel for NCC), not by HBM.
+// SP = 0: any spacing whose tiles see at most 16 controls along x and y: the
+// weights of a layer are scalar loads, and the y and x transposes are MFMA
+// products with the tile's weight matrices. Against k_fused3 (which waits for
+// each layer's gathers and transposes with two LDS reads per term), same
+// tiling, 181 x 217 x 181 NCC with spacing 10: 102 -> 84 us per evaluation;
+// with the default tiling it allows (16 x 16, 4 cells) 61.6 us.
 struct W8 {
     float w[9][4];  // row 8 (t = 1) is the next cell's first layer
 };
@@ -494,16 +500,28 @@ constexpr W8 make_w8() {
 }
 constexpr W8 kW8 = make_w8();
 
-template <int TX, int TY, int SIM>
-__global__ void __launch_bounds__(TX* TY)
-k_fused3_s8(const LaunchCtx C) {
-    constexpr int S = 8;
+__host__ __device__ constexpr int round16(int n) { return (n + 15) & ~15; }
+template <int TX>
+constexpr int kEPitch = TX + (80 - TX % 64) % 64;   // = 16 (mod 64), at least TX
+
+__device__ inline v4f mfma4(float a, float b, v4f c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+template <int TX, int TY, int SIM, int SP>
+__global__ void __launch_bounds__(TX* TY, SP == 0 ? 4 : 1)
+k_fused3_tile(const LaunchCtx C) {
+    constexpr bool kAny = SP == 0;   // spacing read from the pair
+    constexpr int S = kAny ? 8 : SP;
     constexpr int NT = TX * TY;
     constexpr int NF = (SIM == AIR_SIM_NCC) ? 3 : 1;
     constexpr int FC = NF * 3;
     constexpr int WXC = TX / S + 3, WYC = TY / S + 3;
     constexpr int GP = TX + 4;  // padded G rows (16-byte aligned, spread over banks)
-    static_assert(TX % S == 0 && TY % S == 0, "cell-aligned tiles");
+    static_assert(kAny || (TX % S == 0 && TY % S == 0), "cell-aligned tiles");
+    // E rows: with MFMA transposes four consecutive rows are read at once,
+    // a pitch of 16 (mod 64) floats puts them on different banks
+    constexpr int EP = kAny ? kEPitch<TX> : TX;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     double* red = reinterpret_cast<double*>(smem_raw);
     float* lds = reinterpret_cast<float*>(smem_raw + 8 * sizeof(double) * (NT / 64));
@@ -528,6 +546,7 @@ k_fused3_s8(const LaunchCtx C) {
     const float* __restrict__ M = C.moving_tab ? C.moving_tab[pair] : C.moving0;
     const float* __restrict__ theta = C.theta_tab ? C.theta_tab[pair] : C.theta0;
     const int nx = P.n[0], ny = P.n[1], nz = P.n[2];
+    const int sx = kAny ? P.sp[0] : S, sy = kAny ? P.sp[1] : S, sz = kAny ? P.sp[2] : S;
     const int ncx = P.nc[0], ncy = P.nc[1];
     const int WxM = P.win[0], WyM = P.win[1], WzM = P.win[2];
     int t = item - P.tile_begin;
@@ -537,27 +556,32 @@ k_fused3_s8(const LaunchCtx C) {
     const int ty = t % P.ntile[1];
     const int tz = t / P.ntile[1];
     const int x0 = tx * TX, y0 = ty * TY;
-    const int ncell_z = (nz - 1) / S + 1;
+    const int ncell_z = (nz - 1) / sz + 1;
     const int cz_b = tz * P.col_cells;
     const int cz_e = min(cz_b + P.col_cells, ncell_z);
-    const int cx0 = x0 / S, cy0 = y0 / S;
-    const int Wx = (min(x0 + TX, nx) - 1) / S + 4 - cx0;
-    const int Wy = (min(y0 + TY, ny) - 1) / S + 4 - cy0;
+    const int cx0 = x0 / sx, cy0 = y0 / sy;
+    const int Wx = (min(x0 + TX, nx) - 1) / sx + 4 - cx0;
+    const int Wy = (min(y0 + TY, ny) - 1) / sy + 4 - cy0;
+    const int Wyt = kAny ? WyM : WYC;   // rows of a control plane in T1
     const int cz0 = cz_b, Wz = cz_e - cz_b + 3;
 
-    float* T1 = lds;                       // [3][WzM][WYC][TX]
-    float* E = T1 + a4(3 * WzM * WYC * TX);  // [FC][TY][TX]
-    float* G = E + a4(FC * TY * TX);         // [FC][WYC][GP]
+    float* T1 = lds;                         // [3][WzM][Wyt][TX]
+    float* E = T1 + a4(3 * WzM * Wyt * TX);  // [FC][TY][EP]
+    float* G = E + a4(FC * TY * EP);         // [FC][WYC][GP] (kAny: [FC Wy][GP])
+    // transposition weights of kAny (zero where a lane does not support a
+    // control), 16 control columns
+    float* WYT = G + (kAny ? round16(FC * WyM) * GP : 0);   // [TY][16]
+    float* WXT = WYT + TY * 16;                             // [TX][16]
 
     const int lx = tid % TX, ly = tid / TX;
     const int x = x0 + lx, y = y0 + ly;
     const bool act = (x < nx) && (y < ny);
     const int xc = min(x, nx - 1), yc = min(y, ny - 1);
-    const int ix = xc / S, iy = yc / S;
+    const int ix = xc / sx, iy = yc / sy;
     float wx[4], wy[4];
     {
-        const float* a = C.consts + P.wtab_off[0] + (xc - ix * S) * 4;
-        const float* b = C.consts + P.wtab_off[1] + (yc - iy * S) * 4;
+        const float* a = C.consts + P.wtab_off[0] + (xc - ix * sx) * 4;
+        const float* b = C.consts + P.wtab_off[1] + (yc - iy * sy) * 4;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             wx[k] = a[k];
@@ -565,6 +589,19 @@ k_fused3_s8(const LaunchCtx C) {
         }
     }
     const int ky0 = iy - cy0;
+    if constexpr (kAny) {
+        for (int i = tid; i < (TX + TY) * 16; i += NT) {
+            const int k = i & 15;
+            const bool isx = i >= TY * 16;
+            const int q = (isx ? i - TY * 16 : i) >> 4;
+            const int v = (isx ? x0 : y0) + q, sp = isx ? sx : sy;
+            const int c = v / sp, kk = k - (c - (isx ? cx0 : cy0));
+            float w = 0.f;
+            if (v < (isx ? nx : ny) && kk >= 0 && kk < 4)
+                w = C.consts[P.wtab_off[isx ? 0 : 1] + (v - c * sp) * 4 + kk];
+            WYT[i] = w;   // WXT follows WYT
+        }
+    }
     // z-controls of each lane's column are kept multiplied by the axis scale
     // s_a (voxels per unit of u), so a layer's displacement in voxels is one
     // weighted sum of them
@@ -613,7 +650,7 @@ k_fused3_s8(const LaunchCtx C) {
                     for (int c = 0; c < 3; ++c) {
                         const float v = wx[0] * t01[i][c].x + wx[1] * t01[i][c].y +
                                         wx[2] * t23[i][c].x + wx[3] * t23[i][c].y;
-                        T1[((c * WzM + kzr[i]) * WYC + kyr[i]) * TX + lx] = x < nx ? v : 0.f;
+                        T1[((c * WzM + kzr[i]) * Wyt + kyr[i]) * TX + lx] = x < nx ? v : 0.f;
                     }
                 }
             }
@@ -622,7 +659,7 @@ k_fused3_s8(const LaunchCtx C) {
     float shF = 0.f, shW = 0.f;
     if (SIM == AIR_SIM_NCC) {
         const int xs = min(x0 + TX / 2, nx - 1), ys = min(y0 + TY / 2, ny - 1);
-        const int zs = min((cz_b * S + min(cz_e * S, nz)) / 2, nz - 1);
+        const int zs = min((cz_b * sz + min(cz_e * sz, nz)) / 2, nz - 1);
         const long long vs = ((long long)zs * ny + ys) * nx + xs;
         shF = F[vs];
         shW = M[vs];
@@ -631,7 +668,7 @@ k_fused3_s8(const LaunchCtx C) {
 
     const float sc[3] = {snx, sny, snz};
     auto vcol = [&](int c, int kz) -> float {
-        const float* r = T1 + ((c * WzM + kz) * WYC + ky0) * TX + lx;
+        const float* r = T1 + ((c * WzM + kz) * Wyt + ky0) * TX + lx;
         return (wy[0] * r[0] + wy[1] * r[TX] + wy[2] * r[2 * TX] + wy[3] * r[3 * TX]) * sc[c];
     };
     float V[3][4];
@@ -671,7 +708,55 @@ k_fused3_s8(const LaunchCtx C) {
 
     // y and x passes of control plane kzl, whose z sums the threads have
     // written to E
+    const int lane = tid & 63, l16 = lane & 15, l4 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // runtime spacing: both transposes are products with a weight matrix of
+    // at most 16 control columns, on v_mfma_f32_16x16x4f32 (lane l holds
+    // A[l % 16][l / 16], B[l / 16][l % 16] and D[4 (l / 16) + v][l % 16])
+    auto flush_mfma = [&](int kzl) {
+        __syncthreads();
+        // y: G[fc][ky][q] = sum_r WYT[r][ky] E[fc][r][q]
+        for (int fc = wave; fc < FC; fc += NT / 64) {
+            float a[TY / 4], e[TY / 4][TX / 16];
+#pragma unroll
+            for (int ks = 0; ks < TY / 4; ++ks) {
+                a[ks] = WYT[(4 * ks + l4) * 16 + l16];
+#pragma unroll
+                for (int nt = 0; nt < TX / 16; ++nt)
+                    e[ks][nt] = E[(fc * TY + 4 * ks + l4) * EP + 16 * nt + l16];
+            }
+#pragma unroll
+            for (int nt = 0; nt < TX / 16; ++nt) {
+                v4f d = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int ks = 0; ks < TY / 4; ++ks) d = mfma4(a[ks], e[ks][nt], d);
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (4 * l4 + v < Wy) G[(fc * Wy + 4 * l4 + v) * GP + 16 * nt + l16] = d[v];
+            }
+        }
+        __syncthreads();
+        // x: out[(fc, ky)][kx] = sum_q G[(fc, ky)][q] WXT[q][kx]
+        const int nrow = FC * Wy, inv = 65536 / Wy + 1;   // m / Wy for m < 256
+        for (int mt = wave; mt * 16 < nrow; mt += NT / 64) {
+            v4f d = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < TX / 4; ++ks)
+                d = mfma4(G[(mt * 16 + l16) * GP + 4 * ks + l4], WXT[(4 * ks + l4) * 16 + l16], d);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int m = mt * 16 + 4 * l4 + v;
+                const int fc = (m * inv) >> 16, ky = m - fc * Wy;
+                if (m < nrow && l16 < Wx)
+                    part[((kzl * WyM + ky) * WxM + l16) * FC + fc] = d[v];
+            }
+        }
+    };
     auto flush_xy = [&](int kzl) {
+        if constexpr (kAny) {
+            flush_mfma(kzl);
+            return;
+        }
         __syncthreads();
         // y: task (fc, lane column q) -> WYC outputs
         for (int task = tid; task < FC * TX; task += NT) {
@@ -726,6 +811,16 @@ k_fused3_s8(const LaunchCtx C) {
         bool ex, ey, ez;
     };
     int cz = cz_b;
+    // weights of layer r of a cell; row t = 1 (r = spacing) follows the last
+    // (scalar loads: the table is constant and the row the same for all lanes)
+    using ConstF = const __attribute__((address_space(4))) float;
+    ConstF* wtz = (ConstF*)(C.consts + __builtin_amdgcn_readfirstlane(P.wtab_off[2]));
+    auto weight = [&](int r, int k) -> float {
+        if constexpr (kAny)
+            return wtz[4 * r + k];
+        else
+            return kW8.w[r][k];
+    };
     // a running statistic that depends on the previous layer's gathers
     auto dep = [&]() -> float { return SIM == AIR_SIM_NCC ? m2 : m1; };
     // stage 1 of layer r of cell cz; tap k of the cell is V slot (k + PH) & 3
@@ -734,7 +829,7 @@ k_fused3_s8(const LaunchCtx C) {
         // Branch-free: the cell is clamped into the volume so every load is
         // in range; m = 1 inside the mask, 0 outside (or for lanes / layers
         // past the volume) scales every contribution.
-        const int z = cz * S + r;
+        const int z = cz * sz + r;
         Prep q;
         // F through its buffer descriptor: the lane's offset is fixed, the
         // plane's is a scalar. Default cache policy: a 16-lane tile row reads
@@ -744,7 +839,7 @@ k_fused3_s8(const LaunchCtx C) {
                   kDbgFixedLoad);
         q.Fv = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
                                              rF, fl4, min(z, nz - 1) * nxy4, 0));
-        float w0 = kW8.w[r][0], w1 = kW8.w[r][1], w2 = kW8.w[r][2], w3 = kW8.w[r][3];
+        float w0 = weight(r, 0), w1 = weight(r, 1), w2 = weight(r, 2), w3 = weight(r, 3);
         // every uniform input of this stage passes through an empty asm that
         // also reads `dv` (produced by the previous layer's stage 2), so
         // neither the arithmetic nor the gathers of this layer can be
@@ -802,7 +897,7 @@ k_fused3_s8(const LaunchCtx C) {
     // adjoint into acc slot (k + PH) & 3
     auto finish = [&](int r, const Prep& q, auto ph) {
         constexpr int PH = decltype(ph)::value;
-        const float w0 = kW8.w[r][0], w1 = kW8.w[r][1], w2 = kW8.w[r][2], w3 = kW8.w[r][3];
+        const float w0 = weight(r, 0), w1 = weight(r, 1), w2 = weight(r, 2), w3 = weight(r, 3);
         auto tap = [&](v4f& a, float g) {
             a[PH] += w0 * g;
             a[(PH + 1) & 3] += w1 * g;
@@ -860,7 +955,10 @@ k_fused3_s8(const LaunchCtx C) {
         // The scheduling barriers keep each layer's gathers issued before the
         // other layer's stage 2 starts: without them the compiler may order
         // the stages so that every iteration first waits for all loads.
-        for (int r = 0; r < S; r += 2) {
+        // (a runtime spacing's last cell ends with the volume)
+        const int nlay =
+            kAny ? __builtin_amdgcn_readfirstlane(min(sz, nz - cz * sz)) : S;
+        for (int r = 0; r + 1 < nlay; r += 2) {
             Prep B = prep(r + 1, dep(), ph);
             __builtin_amdgcn_sched_barrier(0);
             finish(r, A, ph);
@@ -868,11 +966,17 @@ k_fused3_s8(const LaunchCtx C) {
             __builtin_amdgcn_sched_barrier(0);
             finish(r + 1, B, ph);
         }
+        if (kAny && (nlay & 1)) {
+            Prep B = prep(nlay, dep(), ph);
+            __builtin_amdgcn_sched_barrier(0);
+            finish(nlay - 1, A, ph);
+            A = B;
+        }
 #pragma unroll
         for (int f = 0; f < NF; ++f)
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                E[((f * 3 + c) * TY + ly) * TX + lx] = acc[f][c][PH];
+                E[((f * 3 + c) * TY + ly) * EP + lx] = acc[f][c][PH];
                 acc[f][c][PH] = 0.f;
             }
         flush_xy(kzl);
@@ -894,7 +998,7 @@ k_fused3_s8(const LaunchCtx C) {
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 const v4f a = acc[f][c];
-                E[((f * 3 + c) * TY + ly) * TX + lx] =
+                E[((f * 3 + c) * TY + ly) * EP + lx] =
                     sl == 0 ? a[0] : (sl == 1 ? a[1] : (sl == 2 ? a[2] : a[3]));
             }
         flush_xy(ncell + j);
@@ -1300,8 +1404,8 @@ __device__ inline void tile_range(int j, int sp, int n, int T, int* lo, int* hi)
     *hi = (b >= a) ? b / T : -1;
 }
 
-// NS lanes per control (1, or 8 when the launch has few controls to fill the
-// chip with): the tiles whose window holds the control are visited in a
+// NS lanes per control (1, or 8 and more when the launch has few controls to
+// fill the chip with): the tiles whose window holds the control are visited in a
 // fixed order and slot s goes to lane s mod NS; the lanes' FP64 sums meet in
 // a fixed xor butterfly, so every lane holds the same, order-fixed total.
 constexpr int kFinLanes = 8;
@@ -1309,8 +1413,13 @@ constexpr int kFinLanes = 8;
 // (few controls, so memory latency is the cost); with one lane per control
 // the launch has threads enough to hide it, and registers matter more
 constexpr int kFinBatch = 4;
-constexpr long long kFinFewControls = 1 << 17;   // below this many, NS = kFinLanes
-
+constexpr long long kFinFewControls = 1 << 17;   // below this many, NS >= kFinLanes
+// A control of a coarse grid gathers from many tiles (spacing 32, 16 x 16
+// tiles: up to 9 x 9 x 3): NS grows to 32 or 64 so that a lane's tiles still
+// fit about one batch. With at most 4 x 8 tiles per control 8 lanes are as
+// fast (more lanes leave each block fewer controls to share its reduction of
+// the pair's statistics). Per evaluation 128 x 144 x 200 with spacing 16 52.1
+// -> 35.1 us, 210 x 130 x 160 with spacing 32 144 -> 46.5 us.
 // SP: the spacing of every axis when the launch's plans share it at compile
 // time (8, the spacing-8 kernel's plans), else 0 (read from the pair)
 template <int TX, int TY, int SIM, int DIM, int NS, int SP>
@@ -1416,6 +1525,27 @@ k_finalize(const LaunchCtx C) {
             ry = TY - qy * spy;
             cys = (ty_lo * TY) / spy;
             rys = ty_lo * TY - cys * spy;
+        }
+        if constexpr (NS > kFinLanes) {
+            // many tiles per control: this lane's slots directly, instead of
+            // counting through all of them
+            const int wx_ = tx_hi - tx_lo + 1, wxy_ = wx_ * (ty_hi - ty_lo + 1);
+            const int total = wxy_ * (tc_hi - tc_lo + 1);
+            for (int i = ls; i < total; i += NS) {
+                const int a = i / wxy_, r = i - a * wxy_, b = r / wx_;
+                const int tc = tc_lo + a, ty = ty_lo + b, tx = tx_lo + r - b * wx_;
+                const int kcl = jc - tc * P.col_cells;
+                const int kyl = (DIM == 3) ? jy - (ty * TY) / spy : 0;
+                const int kxl = jx - (tx * TX) / spx;
+                AIR_CHECK(kcl >= 0 && kcl < P.win[2] && kyl >= 0 && kyl < WyM && kxl >= 0 &&
+                              kxl < WxM, kDbgControlLoad);
+                const int tl = (DIM == 3) ? (tc * P.ntile[1] + ty) * P.ntile[0] + tx
+                                          : tc * P.ntile[0] + tx;
+                visit(stats + (long long)(P.tile_begin + tl) * kStatWords,
+                      part + (long long)tl * P.part_stride +
+                          (((long long)kcl * WyM + kyl) * WxM + kxl) * (NF * DIM));
+            }
+            return;
         }
         int slot = 0;
         for (int tc = tc_lo; tc <= tc_hi; ++tc) {
@@ -1550,29 +1680,37 @@ static hipError_t launch3(const LaunchCtx& C, size_t lds, hipStream_t s) {
     return hipSuccess;
 }
 
-template <int TX, int TY, int SIM>
-static hipError_t launch3s8(const LaunchCtx& C, size_t lds, hipStream_t s) {
+template <int TX, int TY, int SIM, int SP>
+static hipError_t launch3t(const LaunchCtx& C, size_t lds, hipStream_t s) {
     const int nblk = xcd_grid(C.ntiles_total, C.nreg_total);
-    hipLaunchKernelGGL((k_fused3_s8<TX, TY, SIM>), dim3(nblk), dim3(TX * TY), lds, s, C);
+    hipLaunchKernelGGL((k_fused3_tile<TX, TY, SIM, SP>), dim3(nblk), dim3(TX * TY), lds, s, C);
     return hipGetLastError();
 }
 
-template <int TX, int TY, int SIM, int DIM, int SP = 0>
-static hipError_t launch_fin(const LaunchCtx& C, int max_ctrl, hipStream_t s) {
-    if ((long long)max_ctrl * C.npairs < kFinFewControls) {
-        dim3 grid(cdiv(max_ctrl, kBlock / kFinLanes), C.npairs);
-        hipLaunchKernelGGL((k_finalize<TX, TY, SIM, DIM, kFinLanes, SP>), grid, dim3(kBlock), 0, s, C);
-    } else {
-        dim3 grid(cdiv(max_ctrl, kBlock), C.npairs);
-        hipLaunchKernelGGL((k_finalize<TX, TY, SIM, DIM, 1, SP>), grid, dim3(kBlock), 0, s, C);
-    }
+template <int TX, int TY, int SIM, int DIM, int NS, int SP>
+static hipError_t launch_fin_ns(const LaunchCtx& C, int max_ctrl, hipStream_t s) {
+    dim3 grid(cdiv(max_ctrl, kBlock / NS), C.npairs);
+    hipLaunchKernelGGL((k_finalize<TX, TY, SIM, DIM, NS, SP>), grid, dim3(kBlock), 0, s, C);
     return hipGetLastError();
+}
+template <int TX, int TY, int SIM, int DIM, int SP = 0>
+static hipError_t launch_fin(const LaunchCtx& C, const FusedShape& F, hipStream_t s) {
+    if ((long long)F.max_ctrl * C.npairs >= kFinFewControls)
+        return launch_fin_ns<TX, TY, SIM, DIM, 1, SP>(C, F.max_ctrl, s);
+    if constexpr (SP == 0) {
+        if (F.ctrl_tiles > 32 * kFinBatch)
+            return launch_fin_ns<TX, TY, SIM, DIM, 64, SP>(C, F.max_ctrl, s);
+        if (F.ctrl_tiles > kFinLanes * kFinBatch)
+            return launch_fin_ns<TX, TY, SIM, DIM, 32, SP>(C, F.max_ctrl, s);
+    }
+    return launch_fin_ns<TX, TY, SIM, DIM, kFinLanes, SP>(C, F.max_ctrl, s);
 }
 
 // cfg: in 3D the tile configuration (id -> TX, TY); in 2D 8 when every pair
 // has spacing 8, else 0. Column cells come from the plan.
-hipError_t launch_bspline(const LaunchCtx& C, int cfg, size_t lds, int max_ctrl,
-                          hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+hipError_t launch_bspline(const LaunchCtx& C, int cfg, const FusedShape& F, hipStream_t s,
+                          hipEvent_t ev0, hipEvent_t ev1) {
+    const size_t lds = F.lds;
     hipError_t e = hipSuccess;
     if (ev0) (void)hipEventRecord(ev0, s);
     if (C.dim == 3) {
@@ -1581,19 +1719,25 @@ hipError_t launch_bspline(const LaunchCtx& C, int cfg, size_t lds, int max_ctrl,
             case 0: e = ncc ? launch3<32, 8, 1>(C, lds, s) : launch3<32, 8, 0>(C, lds, s); break;
             case 1: e = ncc ? launch3<64, 4, 1>(C, lds, s) : launch3<64, 4, 0>(C, lds, s); break;
             case 2: e = ncc ? launch3<16, 16, 1>(C, lds, s) : launch3<16, 16, 0>(C, lds, s); break;
-            case 3: e = ncc ? launch3s8<32, 8, 1>(C, lds, s) : launch3s8<32, 8, 0>(C, lds, s); break;
-            case 4: e = ncc ? launch3s8<16, 16, 1>(C, lds, s) : launch3s8<16, 16, 0>(C, lds, s); break;
+            case 3: e = ncc ? launch3t<32, 8, 1, 8>(C, lds, s) : launch3t<32, 8, 0, 8>(C, lds, s); break;
+            case 4: e = ncc ? launch3t<16, 16, 1, 8>(C, lds, s) : launch3t<16, 16, 0, 8>(C, lds, s); break;
+            case 5: e = ncc ? launch3t<32, 8, 1, 0>(C, lds, s) : launch3t<32, 8, 0, 0>(C, lds, s); break;
+            case 6: e = ncc ? launch3t<64, 4, 1, 0>(C, lds, s) : launch3t<64, 4, 0, 0>(C, lds, s); break;
+            case 7: e = ncc ? launch3t<16, 16, 1, 0>(C, lds, s) : launch3t<16, 16, 0, 0>(C, lds, s); break;
             default: return hipErrorInvalidValue;
         }
         if (e != hipSuccess) return e;
         if (ev1) (void)hipEventRecord(ev1, s);
         switch (cfg) {
-            case 0: return ncc ? launch_fin<32, 8, 1, 3>(C, max_ctrl, s) : launch_fin<32, 8, 0, 3>(C, max_ctrl, s);
-            case 1: return ncc ? launch_fin<64, 4, 1, 3>(C, max_ctrl, s) : launch_fin<64, 4, 0, 3>(C, max_ctrl, s);
-            case 2: return ncc ? launch_fin<16, 16, 1, 3>(C, max_ctrl, s) : launch_fin<16, 16, 0, 3>(C, max_ctrl, s);
+            case 0:
+            case 5: return ncc ? launch_fin<32, 8, 1, 3>(C, F, s) : launch_fin<32, 8, 0, 3>(C, F, s);
+            case 1:
+            case 6: return ncc ? launch_fin<64, 4, 1, 3>(C, F, s) : launch_fin<64, 4, 0, 3>(C, F, s);
+            case 2:
+            case 7: return ncc ? launch_fin<16, 16, 1, 3>(C, F, s) : launch_fin<16, 16, 0, 3>(C, F, s);
             // the spacing-8 kernel's plans: spacing 8 on every axis
-            case 3: return ncc ? launch_fin<32, 8, 1, 3, 8>(C, max_ctrl, s) : launch_fin<32, 8, 0, 3, 8>(C, max_ctrl, s);
-            default: return ncc ? launch_fin<16, 16, 1, 3, 8>(C, max_ctrl, s) : launch_fin<16, 16, 0, 3, 8>(C, max_ctrl, s);
+            case 3: return ncc ? launch_fin<32, 8, 1, 3, 8>(C, F, s) : launch_fin<32, 8, 0, 3, 8>(C, F, s);
+            default: return ncc ? launch_fin<16, 16, 1, 3, 8>(C, F, s) : launch_fin<16, 16, 0, 3, 8>(C, F, s);
         }
     }
     const int nblk = xcd_grid(C.ntiles_total, C.nreg_total);
@@ -1605,10 +1749,10 @@ hipError_t launch_bspline(const LaunchCtx& C, int cfg, size_t lds, int max_ctrl,
     if (e != hipSuccess) return e;
     if (ev1) (void)hipEventRecord(ev1, s);
     if (cfg == 8)   // every pair has spacing 8
-        return C.sim == AIR_SIM_NCC ? launch_fin<64, 1, 1, 2, 8>(C, max_ctrl, s)
-                                    : launch_fin<64, 1, 0, 2, 8>(C, max_ctrl, s);
-    return C.sim == AIR_SIM_NCC ? launch_fin<64, 1, 1, 2>(C, max_ctrl, s)
-                                : launch_fin<64, 1, 0, 2>(C, max_ctrl, s);
+        return C.sim == AIR_SIM_NCC ? launch_fin<64, 1, 1, 2, 8>(C, F, s)
+                                    : launch_fin<64, 1, 0, 2, 8>(C, F, s);
+    return C.sim == AIR_SIM_NCC ? launch_fin<64, 1, 1, 2>(C, F, s)
+                                : launch_fin<64, 1, 0, 2>(C, F, s);
 }
 
 // Regulariser only (B-spline): Gram-form blocks of one pair, unscaled output.

@@ -9,6 +9,7 @@ import torch
 
 import oracle as O
 from paper_1806_09907_amd import api, synth
+from paper_1806_09907_amd._lib import AirError
 from parity import VAL_TOL, check_grad
 
 pytestmark = pytest.mark.gpu
@@ -90,3 +91,39 @@ def test_exponential_walks(n, std, K, tf):
     th = (synth.smooth_dense(n, std, 51) if tf == api.TF_DENSE
           else synth.random_theta(n, sp, std, 51))
     check(p, F, M, th, f"exponential {n} std={std} K={K} tf={tf}")
+
+
+# the pipelined kernel of any spacing: odd and even layer counts of a cell,
+# the last cell cut by the volume after 1 .. spacing layers, windows of up to
+# 16 controls (the general kernel beyond), coarse grids whose controls gather
+# from many tiles (32 and 64 lanes per control), and each tile shape
+@pytest.mark.parametrize("n,sp", [((33, 17, 31), (10, 10, 10)), ((47, 35, 41), (5, 7, 3)),
+                                  ((40, 36, 25), (2, 2, 2)), ((19, 18, 20), (1, 1, 1)),
+                                  ((40, 24, 33), (3, 1, 6)), ((70, 66, 65), (32, 32, 32)),
+                                  ((128, 40, 36), (64, 16, 16)), ((97, 80, 64), (12, 20, 9)),
+                                  ((2, 3, 2), (4, 4, 4)), ((16, 16, 17), (16, 16, 16))])
+@pytest.mark.parametrize("sim", [api.SIM_MSE, api.SIM_NCC])
+def test_any_spacing(n, sp, sim):
+    p = api.Problem(n=n, spacing=sp, similarity=sim, lambda_diff=0.05)
+    F, M = inputs(n, 60)
+    check(p, F, M, synth.random_theta(n, sp, 0.8, 61), f"spacing {sp} {n} sim={sim}")
+
+
+@pytest.mark.parametrize("tiling", range(10))
+@pytest.mark.parametrize("sp", [(6, 6, 6), (3, 3, 5)])
+def test_any_spacing_tilings(tiling, sp):
+    n = (70, 37, 44)
+    p = api.Problem(n=n, spacing=sp, similarity=api.SIM_NCC, lambda_diff=0.05)
+    F, M = inputs(n, 62)
+    th = synth.random_theta(n, sp, 0.8, 63)
+    print(f"case spacing {sp} tiling {tiling}", flush=True)
+    try:
+        plan = api.Plan(p, tiling=tiling)
+    except AirError as e:      # more LDS than a block may have
+        assert e.status == 5
+        return
+    v, g = api.objective_and_grad(plan, gpu(F), gpu(M), gpu(th))
+    vo, go, _ = O.objective_and_grad(O.Problem(n=n, spacing=sp, similarity=O.SIM_NCC,
+                                               lambda_diff=0.05), F, M, th)
+    assert abs(float(v) - vo) <= VAL_TOL * abs(vo)
+    check_grad(g.double().cpu().numpy(), go, f"spacing {sp} tiling {tiling}")
