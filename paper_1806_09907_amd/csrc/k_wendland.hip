@@ -318,6 +318,273 @@ k_wend_gather(const PairDesc P, const float* __restrict__ H, float scale, int ac
     }
 }
 
+// ---- 3D grids whose cells see 4 controls per axis (cubic B-splines; Wendland
+// with sigma up to 2 spacings): the same contractions with every operand of a
+// wave's product in flight at once.
+
+// The controls of one 16-cell group are read from theta itself (a control
+// past the grid reads past the buffer, which gives zero), 16-byte stores
+// write four phases along x at once where the spacing allows it (VEC: a
+// multiple of 4). A K step is one (qz, qy) row of controls, its four k the
+// qx, in the order of k_wend_expand, so u is the same bit for bit. All 112
+// loads of a wave are issued before their products; k_wend_expand waits for
+// each step's. 128^3, spacing 8: 24.1 us
+// and 4.7 for the padded copy -> 15-16 us (5.1 us of MFMA issue).
+template <bool VEC>
+__global__ void __launch_bounds__(kBlock)
+k_cell_expand4(const PairDesc P, const float* __restrict__ W, const float* __restrict__ theta,
+               float scale, float* __restrict__ u) {
+    const int lane = threadIdx.x & 63;
+    const int i16 = lane & 15, k4 = lane >> 4;
+    const int gw = __builtin_amdgcn_readfirstlane(blockIdx.x * kWaves + (threadIdx.x >> 6));
+    const int npc = P.wpad[0] / 64;             // phase chunks
+    const int ngx = cdiv(P.wncell[0], kWCells);
+    if (gw >= ngx * P.wncell[1] * P.wncell[2] * npc) return;
+    const int pc = gw % npc;
+    const int g = gw / npc;
+    const int cx0 = (g % ngx) * kWCells;
+    const int cy = (g / ngx) % P.wncell[1];
+    const int cz = g / (ngx * P.wncell[1]);
+    const int Ppad = P.wpad[0];
+    const long long NC = (long long)P.nc[0] * P.nc[1] * P.nc[2];
+    __amdgpu_buffer_rsrc_t rT[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) rT[c] = make_rsrc(theta + c * NC, (uint32_t)(NC * 4));
+    const int jx = cx0 + i16 + k4;
+    const int vo = jx < P.nc[0] ? jx * 4 : 0x7ffffff0;
+    const float* Wr = W + k4 * Ppad + pc * 64 + i16;
+    float a[16][4], b[16][3];
+#pragma unroll
+    for (int st = 0; st < 16; ++st) {
+        const int jz = cz + (st >> 2), jy = cy + (st & 3);
+        const bool in = jz < P.nc[2] && jy < P.nc[1];   // uniform
+        const int so = in ? (jz * P.nc[1] + jy) * P.nc[0] * 4 : 0;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) b[st][c] = load1(rT[c], in ? vo : 0x7ffffff0, so);
+#pragma unroll
+        for (int m = 0; m < 4; ++m) a[st][m] = Wr[st * 4 * Ppad + m * 16];
+    }
+    v4f acc[4][3];
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) acc[m][c] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int st = 0; st < 16; ++st)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const float bc = scale * b[st][c];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) acc[m][c] = mfma4(a[st][m], bc, acc[m][c]);
+        }
+    const int P3 = P.sp[0] * P.sp[1] * P.sp[2];
+    const int nx = P.n[0], ny = P.n[1], nz = P.n[2], iN = (int)P.nvox;
+    const int x0 = (cx0 + i16) * P.sp[0], y0 = cy * P.sp[1], z0 = cz * P.sp[2];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const int r0 = pc * 64 + m * 16 + 4 * k4;   // this lane's phases r0 .. r0 + 3
+        if constexpr (VEC) {
+            if (r0 >= P3) continue;
+            const Idx3 rc = idx3(r0, P.sp[0], P.sp[1]);
+            const int x = x0 + rc.x, y = y0 + rc.y, z = z0 + rc.z;
+            if (x >= nx || y >= ny || z >= nz) continue;
+            const int vox = (z * ny + y) * nx + x;
+            if (x + 3 < nx) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    __builtin_memcpy(u + (long long)c * iN + vox, &acc[m][c], 16);
+            } else {
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+#pragma unroll
+                    for (int v = 0; v < 3; ++v)
+                        if (x + v < nx) u[(long long)c * iN + vox + v] = acc[m][c][v];
+            }
+        } else {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                if (r0 + v >= P3) continue;
+                const Idx3 rc = idx3(r0 + v, P.sp[0], P.sp[1]);
+                const int x = x0 + rc.x, y = y0 + rc.y, z = z0 + rc.z;
+                if (x >= nx || y >= ny || z >= nz) continue;
+                const int vox = (z * ny + y) * nx + x;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) u[(long long)c * iN + vox] = acc[m][c][v];
+            }
+        }
+    }
+}
+
+// The transpose. A block of eight waves takes one 16-cell group; wave w the
+// phase chunks w, w + 8, .., 64 phases each. A lane loads four phases of its
+// cell at once (VEC: one 16-byte load), K step j of 16 phases being phase j
+// of every lane's four. The waves' products are added in LDS in a fixed
+// order, and H is summed over qx there:
+//   Hx(c, qz, qy, cz, cy, group, i) = sum_qx H(cell 16 group + i - qx, q),
+// i < 19, stored with pitch kHx, a third of H, so the gather reads 16 to 32
+// values per control instead of 128. 128^3, spacing 8: 18.9
+// and 10.4 us for the gather -> 14.3 and 4.0.
+constexpr int kHx = 20;
+constexpr int kCellTBlock = 512;
+template <bool VEC>
+__global__ void __launch_bounds__(kCellTBlock)
+k_cell_t4(const PairDesc P, const float* __restrict__ WT, const float* __restrict__ g,
+          float* __restrict__ Hx) {
+    constexpr int NW = kCellTBlock / 64, NA = 48;
+    __shared__ float red[NW / 2][NA][64];
+    const int lane = threadIdx.x & 63;
+    const int i16 = lane & 15, k4 = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int ngx = cdiv(P.wncell[0], kWCells);
+    const int grp = blockIdx.x % ngx, cy = (blockIdx.x / ngx) % P.wncell[1];
+    const int cz = blockIdx.x / (ngx * P.wncell[1]);
+    const int npc = P.wpad[0] / 64, Qpad = P.wpad[1];
+    const int P3 = P.sp[0] * P.sp[1] * P.sp[2];
+    const int nx = P.n[0], ny = P.n[1], nz = P.n[2];
+    const long long N = P.nvox;
+    const int cxl = grp * kWCells + i16;
+    const int x0 = cxl * P.sp[0], y0 = cy * P.sp[1], z0 = cz * P.sp[2];
+    __amdgpu_buffer_rsrc_t rg[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) rg[c] = make_rsrc(g + c * N, (uint32_t)(N * 4));
+    v4f acc[4][3];
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) acc[m][c] = v4f{0.f, 0.f, 0.f, 0.f};
+    for (int pc = w; pc < npc; pc += NW) {
+        v4f b[4][3];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int r0 = pc * 64 + 16 * q + 4 * k4;
+            if constexpr (VEC) {
+                const Idx3 rc = idx3(r0, P.sp[0], P.sp[1]);
+                const int x = x0 + rc.x, y = y0 + rc.y, z = z0 + rc.z;
+                const bool ok = r0 < P3 && x < nx && y < ny && z < nz;
+                const int vo = ok ? ((z * ny + y) * nx + x) * 4 : 0x7ffffff0;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    v4f v = __builtin_bit_cast(
+                        v4f, __builtin_amdgcn_raw_buffer_load_b128(rg[c], vo, 0, 0));
+                    // past the row's end: the next row's voxels
+#pragma unroll
+                    for (int e = 1; e < 4; ++e) v[e] = x + e < nx ? v[e] : 0.f;
+                    b[q][c] = v;
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const Idx3 rc = idx3(r0 + e, P.sp[0], P.sp[1]);
+                    const int x = x0 + rc.x, y = y0 + rc.y, z = z0 + rc.z;
+                    const bool ok = r0 + e < P3 && x < nx && y < ny && z < nz;
+                    const int vo = ok ? ((z * ny + y) * nx + x) * 4 : 0x7ffffff0;
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) b[q][c][e] = load1(rg[c], vo, 0);
+                }
+            }
+        }
+        float a[16][4];
+        const float* Wq = WT + (pc * 64 + 4 * k4) * Qpad + i16;   // rows >= P3 are zero
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int m = 0; m < 4; ++m) a[4 * q + e][m] = Wq[(16 * q + e) * Qpad + 16 * m];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c)
+                        acc[m][c] = mfma4(a[4 * q + e][m], b[q][c][e], acc[m][c]);
+    }
+    if (w >= NW / 2) {
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) red[w - NW / 2][(m * 3 + c) * 4 + v][lane] = acc[m][c][v];
+    }
+    __syncthreads();
+    if (w < NW / 2) {
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) red[w][(m * 3 + c) * 4 + v][lane] += acc[m][c][v];
+    }
+    __syncthreads();
+    // control q = 4 (4 m + k4) + v of the products is (qz, qy) = (m, k4), qx = v
+    for (int o = threadIdx.x; o < 16 * 3 * kHx; o += kCellTBlock) {
+        const int i = o % kHx, rest = o / kHx;
+        const int c = rest % 3, qyz = rest / 3;
+        float s = 0.f;
+#pragma unroll
+        for (int qx = 0; qx < 4; ++qx) {
+            const int t = i - qx;
+            if (t < 0 || t >= kWCells) continue;
+#pragma unroll
+            for (int ww = 0; ww < NW / 2; ++ww)
+                s += red[ww][((qyz >> 2) * 3 + c) * 4 + qx][(qyz & 3) * 16 + t];
+        }
+        Hx[((((long long)c * 16 + qyz) * P.wncell[2] + cz) * P.wncell[1] + cy) * ngx * kHx +
+           grp * kHx + i] = s;
+    }
+}
+
+// out(j) (+)= scale * the sum of Hx over the (qz, qy) and groups that hold
+// control j. As in k_wend_gather, 64 controls per block, (qz, qy) split over
+// the waves.
+__global__ void __launch_bounds__(kBlock)
+k_cell_gather4(const PairDesc P, const float* __restrict__ Hx, float scale, int accumulate,
+               float* __restrict__ out) {
+    __shared__ float red[kWaves][64];
+    const int lane = threadIdx.x & 63;
+    const int w = threadIdx.x >> 6;
+    const int NC = P.nc[0] * P.nc[1] * P.nc[2];
+    const int ngx = cdiv(P.wncell[0], kWCells);
+    const long long i = (long long)blockIdx.x * 64 + lane;   // (component, control)
+    float s = 0.f;
+    if (i < 3LL * NC) {
+        const int c = (int)(i / NC), j = (int)(i - (long long)c * NC);
+        const int jx = j % P.nc[0], jyz = j / P.nc[0];
+        const int jy = jyz % P.nc[1], jz = jyz / P.nc[1];
+        const int ghi = min(jx / kWCells, ngx - 1), glo = jx > 18 ? (jx - 3) / kWCells : 0;
+#pragma unroll
+        for (int k = 0; k < 16 / kWaves; ++k) {
+            const int qyz = w * (16 / kWaves) + k;
+            const int cz = jz - (qyz >> 2), cy = jy - (qyz & 3);
+            if (cz < 0 || cz >= P.wncell[2] || cy < 0 || cy >= P.wncell[1]) continue;
+            const float* h = Hx + ((((long long)c * 16 + qyz) * P.wncell[2] + cz) * P.wncell[1] +
+                                   cy) * ngx * kHx;
+            for (int gi = glo; gi <= ghi; ++gi)
+                if (jx - gi * kWCells < kWCells + 3) s += h[gi * kHx + jx - gi * kWCells];
+        }
+    }
+    red[w][lane] = s;
+    __syncthreads();
+    if (w == 0 && i < 3LL * NC) {
+        float t = 0.f;
+#pragma unroll
+        for (int ww = 0; ww < kWaves; ++ww) t += red[ww][lane];
+        const float v = scale * t;
+        out[i] = accumulate ? out[i] + v : v;
+    }
+}
+
+// Whether the kernels above take the plan: 3D, four controls per axis, byte
+// offsets in 32 bits, and at least three cells along x (with fewer, Hx would
+// not fit in the workspace of H).
+__host__ inline bool cells4(const PairDesc& P, int dim) {
+    return dim == 3 && P.wK[0] == 4 && P.wK[1] == 4 && P.wK[2] == 4 && P.wncell[0] >= 3 &&
+           (long long)P.nc[0] * P.nc[1] * P.nc[2] < (1LL << 29);
+}
+
 __host__ inline int wend_grid(long long n) {
     const long long b = (n + kBlock - 1) / kBlock;
     return (int)(b < 4096 ? (b < 1 ? 1 : b) : 4096);
@@ -335,7 +602,14 @@ hipError_t launch_wendland_expand(const PairDesc& P, const float* consts_dev, in
     const int ngx = cdiv(P.wncell[0], kWCells);
     const long long waves = (long long)ngx * P.wncell[1] * P.wncell[2] * (P.wpad[0] / 64);
     const int blocks = (int)((waves + kWaves - 1) / kWaves);
-    if (dim == 3) {
+    if (cells4(P, dim)) {
+        if (P.sp[0] % 4 == 0)
+            hipLaunchKernelGGL(k_cell_expand4<true>, dim3(blocks), dim3(kBlock), 0, s, P, W,
+                               theta, scale, u);
+        else
+            hipLaunchKernelGGL(k_cell_expand4<false>, dim3(blocks), dim3(kBlock), 0, s, P, W,
+                               theta, scale, u);
+    } else if (dim == 3) {
         hipLaunchKernelGGL(k_wend_pad<3>, dim3(wend_grid(np)), dim3(kBlock), 0, s, P, theta,
                            scale, thp);
         hipLaunchKernelGGL(k_wend_expand<3>, dim3(blocks), dim3(kBlock), 0, s, P, W, thp, u);
@@ -357,7 +631,15 @@ hipError_t launch_wendland_adjoint(const PairDesc& P, const float* consts_dev, i
     const int blocks = ngx * P.wncell[1] * P.wncell[2] * (P.wpad[1] / 64) * kTSplit;
     const long long NC = (long long)dim * P.nc[0] * P.nc[1] * P.nc[2];
     const int gblocks = (int)((NC + 63) / 64);
-    if (dim == 3) {
+    if (cells4(P, dim)) {
+        const int groups = ngx * P.wncell[1] * P.wncell[2];
+        if (P.sp[0] % 4 == 0)
+            hipLaunchKernelGGL(k_cell_t4<true>, dim3(groups), dim3(kCellTBlock), 0, s, P, WT, g, H);
+        else
+            hipLaunchKernelGGL(k_cell_t4<false>, dim3(groups), dim3(kCellTBlock), 0, s, P, WT, g, H);
+        hipLaunchKernelGGL(k_cell_gather4, dim3(gblocks), dim3(kBlock), 0, s, P, H, scale,
+                           accumulate ? 1 : 0, grad);
+    } else if (dim == 3) {
         hipLaunchKernelGGL(k_wend_cells_t<3>, dim3(blocks), dim3(kBlock), 0, s, P, WT, g, H);
         hipLaunchKernelGGL(k_wend_gather<3>, dim3(gblocks), dim3(kBlock), 0, s, P, H, scale,
                            accumulate ? 1 : 0, grad);

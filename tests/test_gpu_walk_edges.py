@@ -127,3 +127,25 @@ def test_any_spacing_tilings(tiling, sp):
                                                lambda_diff=0.05), F, M, th)
     assert abs(float(v) - vo) <= VAL_TOL * abs(vo)
     check_grad(g.double().cpu().numpy(), go, f"spacing {sp} tiling {tiling}")
+
+
+# per-cell contractions of fields on the voxel grid: four controls per axis
+# with whole and partial 16-cell groups, rows that end inside four phases,
+# spacings that are no multiple of 4, grids of too few cells (the general
+# kernels), and more controls per axis (likewise)
+@pytest.mark.parametrize("n,sp", [((128, 9, 17), (8, 8, 8)), ((133, 20, 12), (8, 5, 4)),
+                                  ((35, 33, 34), (6, 6, 6)), ((17, 16, 24), (8, 8, 8)),
+                                  ((16, 24, 40), (8, 8, 8)), ((70, 13, 11), (4, 4, 4)),
+                                  ((50, 21, 30), (10, 3, 7)), ((30, 12, 9), (1, 2, 3))])
+@pytest.mark.parametrize("kind", ["tv", "lcc", "wendland", "wendland3"])
+def test_field_contractions(n, sp, kind):
+    kw = {}
+    if kind.startswith("wendland"):
+        kw = dict(transform=api.TF_WENDLAND,
+                  sigma=tuple((2.0 if kind == "wendland" else 2.7) * s for s in sp))
+    p = api.Problem(n=n, spacing=sp, similarity=api.SIM_LCC if kind == "lcc" else api.SIM_NCC,
+                    lambda_diff=0.02, lcc_radius=2,
+                    regulariser=api.REG_ISO_TV if kind == "tv" else api.REG_DIFFUSION, **kw)
+    F, M = inputs(n, 70)
+    th = synth.random_controls(n, p.ncontrol(), 0.7, 71)
+    check(p, F, M, th, f"contraction {kind} {n} spacing {sp}")
