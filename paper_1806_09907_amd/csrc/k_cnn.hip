@@ -397,6 +397,229 @@ k_conv_fwd_brick_in2(const u16* __restrict__ X, ConvDims D, const u16* __restric
                          ((long long)(zv0 + zb + wave) * D.ny + y0) * D.nx + x0, lane);
 }
 
+// Linear form, for any sizes: a block takes M = 16 MT MG consecutive voxels of
+// the stack. Their 27 neighbours lie in three runs of M + 2 nx + 2 consecutive
+// voxels (one per dz), which the block stages in LDS with all channels; a tap
+// outside its volume reads a zero slot. MG groups of MT 16-voxel tiles times
+// KS ranges of the reduction make the block's eight waves, so a weight operand
+// feeds MT products and is fetched once per MG waves, and small volumes still
+// give many blocks. A wave's operands are MT 16-byte LDS reads and NT16
+// 16-byte loads of weights (two steps in flight) per 32 reduction columns,
+// with no barrier in between. The KS partial tiles are added in a fixed tree
+// through LDS. The split-K form it replaces gathered every tap of every input
+// from L2 and waited for each step's loads (MFMA pipes 8 % busy): 112 -> 48
+// channels at 8 x 16^3 41.5 -> 27.3 us, the data gradient 48.2 -> 27.5 us (9.5
+// GFLOP each, 7.5 us at the rate of a large BF16 product).
+constexpr int kLinWaves = 8;
+constexpr int kLinMaxLds = 150 * 1024;
+struct LinShape {
+    int pitch;        // u16 per staged voxel (odd multiple of 8 where that spreads the banks)
+    int run;          // voxels of a run
+    int stage;        // bytes of the runs and the zero slot, then the tap table
+    int bytes;        // LDS of a block
+};
+__host__ __device__ inline LinShape lin_shape(const ConvDims& D, int nt16, int m, int ks) {
+    LinShape L;
+    L.pitch = (D.cin / 8) % 4 == 0 ? D.cin + 8 : D.cin;
+    L.run = m + 2 * D.nx + 2;
+    L.stage = (3 * L.run * L.pitch + 8) * 2;
+    L.stage = (L.stage + 15) & ~15;
+    const int red = (ks > 2 ? ks / 2 : ks) * m * (nt16 * 16 + 4) * 4;   // see the tree below
+    const int tile = L.stage + D.Kpad / 8 * 8;
+    L.bytes = tile > red ? tile : red;
+    return L;
+}
+template <int NT16, int MT, int MG>
+__global__ void __launch_bounds__(kLinWaves * 64)
+k_conv_fwd_lin(const u16* __restrict__ X, ConvDims D, const u16* __restrict__ Wt, ConvEpi E,
+               int vec) {
+    constexpr int NT = kLinWaves * 64, KS = kLinWaves / MG, M = 16 * MT * MG;
+    constexpr int CP = kEpiPitch(NT16);
+    extern __shared__ __align__(16) unsigned char lds[];
+    const LinShape L = lin_shape(D, NT16, M, KS);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int mg = wave % MG, ks = wave / MG;
+    const int g = lane >> 4, r = lane & 15;
+    const long long N = (long long)D.nx * D.ny * D.nz;
+    const long long m0 = (long long)blockIdx.x * M;
+    const int plane = D.nx * D.ny;
+    // stage the three runs (voxels outside the stack are never used: their
+    // taps read the zero slot)
+    const int c8n = D.cin / 8, per = L.run * c8n;
+    const long long vend = N * D.cin;
+    for (int i0 = tid; i0 < 3 * per; i0 += 8 * NT) {
+        // eight loads in flight per thread
+        uint4 q[8];
+        int dst[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int i = i0 + e * NT;
+            const int dz = i >= 2 * per ? 2 : (i >= per ? 1 : 0), j = i - dz * per;
+            const int lv = j / c8n;
+            // the run's channels are consecutive in memory
+            const long long src = (m0 + (long long)(dz - 1) * plane - D.nx - 1) * D.cin + 8LL * j;
+            q[e] = make_uint4(0, 0, 0, 0);
+            dst[e] = i < 3 * per ? (dz * L.run + lv) * L.pitch + 8 * (j - lv * c8n) : -1;
+            if (dst[e] >= 0 && src >= 0 && src < vend)
+                q[e] = *reinterpret_cast<const uint4*>(X + src);
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (dst[e] >= 0) *reinterpret_cast<uint4*>(reinterpret_cast<u16*>(lds) + dst[e]) = q[e];
+    }
+    const int zero = 3 * L.run * L.pitch * 2;   // byte offset of the zero slot
+    if (tid < 4) reinterpret_cast<uint32_t*>(lds + zero)[tid] = 0u;
+    // per 8 reduction columns: byte offset of the tap's operand from its
+    // voxel's own staged position, and the tap (27 past the last column)
+    int2* tab = reinterpret_cast<int2*>(lds + L.stage);
+    for (int i = tid; i < D.Kpad / 8; i += NT) {
+        const int k = 8 * i;
+        const int tap = k < D.K ? k / D.cin : 27, ci = k - tap * D.cin;
+        const int dz = tap / 9, dy = (tap / 3) % 3, dx = tap % 3;
+        tab[i] = make_int2(
+            tap < 27 ? ((dz * L.run + dy * D.nx + dx) * L.pitch + ci) * 2 : 0, tap);
+    }
+    // this lane's voxels: staged position and the taps inside their volume
+    int base[MT];
+    uint32_t taps[MT];
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+        const int lv = (mg * MT + t) * 16 + r;
+        base[t] = lv * L.pitch * 2;
+        taps[t] = 0u;
+        const long long m = m0 + lv;
+        if (m < N) {
+            const int x = (int)(m % D.nx), y = (int)((m / D.nx) % D.ny), z = (int)(m / plane);
+            const int zl = z % D.nzv;
+            uint32_t mx = 0, my = 0;   // bits dx, and dy in groups of three
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                if ((unsigned)(x + d - 1) < (unsigned)D.nx) mx |= 1u << d;
+            }
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+                if ((unsigned)(y + d - 1) < (unsigned)D.ny) my |= mx << (3 * d);
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+                if ((unsigned)(zl + d - 1) < (unsigned)D.nzv) taps[t] |= my << (9 * d);
+        }
+    }
+    __syncthreads();
+    f32x4 acc[MT][NT16];
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int j = 0; j < NT16; ++j) acc[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int nst = D.Kpad / 32;
+    const int s0 = nst * ks / KS, s1 = nst * (ks + 1) / KS;
+    // weights: rows past cout and columns past K read past the buffer (zero)
+    const __amdgpu_buffer_rsrc_t rW = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<u16*>(Wt), (short)0, D.cout * D.K * 2, 0x00020000);
+    auto weights = [&](int st, bf16x8* b) {
+        const int k = 32 * st + 8 * g;
+        const int vo = k < D.K ? (r * D.K + k) * 2 : 0x7ffffff0;
+#pragma unroll
+        for (int j = 0; j < NT16; ++j)
+            b[j] = __builtin_bit_cast(
+                bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rW, vo, j * 16 * D.K * 2, 0));
+    };
+    auto step = [&](int st, const bf16x8* b) {
+        const int2 e = tab[4 * st + g];
+        bf16x8 a[MT];
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+            const int o = ((taps[t] >> e.y) & 1u) ? base[t] + e.x : zero;
+            AIR_CHECK(o >= 0 && o + 16 <= zero + 16, kDbgConvInput);
+            a[t] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(lds + o));
+        }
+#pragma unroll
+        for (int j = 0; j < NT16; ++j)
+#pragma unroll
+            for (int t = 0; t < MT; ++t)
+                acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t], b[j], acc[t][j], 0, 0, 0);
+    };
+    // two weight sets rotate (a step past the range loads its last one again)
+    bf16x8 b0[NT16], b1[NT16];
+    if (s0 < s1) weights(s0, b0);
+    for (int st = s0; st < s1; st += 2) {
+        weights(min(st + 1, s1 - 1), b1);
+        step(st, b0);
+        weights(min(st + 2, s1 - 1), b0);
+        if (st + 1 < s1) step(st + 1, b1);
+    }
+    __syncthreads();   // every wave is done with the runs and the table
+    // the KS partials of a tile: the upper half of the ranges is added to the
+    // lower half until two are left, then all threads add those two
+    float* part = reinterpret_cast<float*>(lds);
+    auto slot = [&](int q, int t, int j, int i) -> float& {   // voxel row 4 g + i, channel r
+        return part[((q * M) + (mg * MT + t) * 16 + 4 * g + i) * CP + j * 16 + r];
+    };
+#pragma unroll
+    for (int h = KS / 2; h >= 2; h /= 2) {
+        if (ks >= h && ks < 2 * h)
+#pragma unroll
+            for (int t = 0; t < MT; ++t)
+#pragma unroll
+                for (int j = 0; j < NT16; ++j)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) slot(ks - h, t, j, i) = acc[t][j][i];
+        __syncthreads();
+        if (ks < h)
+#pragma unroll
+            for (int t = 0; t < MT; ++t)
+#pragma unroll
+                for (int j = 0; j < NT16; ++j)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[t][j][i] += slot(ks, t, j, i);
+        __syncthreads();
+    }
+    if (ks < 2)
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+            for (int j = 0; j < NT16; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) slot(ks, t, j, i) = acc[t][j][i];
+    __syncthreads();
+    if (vec) {
+        // whole 8-channel vectors
+        const int C8 = D.cout / 8;
+        for (int o = tid; o < M * C8; o += NT) {
+            const int lv = o / C8, co = 8 * (o - lv * C8);
+            if (m0 + lv >= N) break;
+            float v[8], w[8];
+            load8f(part + lv * CP + co, v);
+            load8f(part + (M + lv) * CP + co, w);
+            const long long row = m0 + lv;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                v[k] += w[k] + (E.bias ? E.bias[co + k] : 0.f);
+                if (E.act == 1) v[k] = v[k] > 0.f ? v[k] : 0.1f * v[k];
+            }
+            if (E.act == 2) {
+                float a[8];
+                unpack8(*reinterpret_cast<const uint4*>(E.gate + row * E.ldg + E.goff + co), a);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[k] = a[k] > 0.f ? v[k] : 0.1f * v[k];
+            }
+            if (E.ybf) *reinterpret_cast<uint4*>(E.ybf + row * E.ldy + E.yoff + co) = pack8(v);
+            if (E.yf) {
+                float* y = E.yf + row * E.ldyf + co;
+                *reinterpret_cast<float4*>(y) = make_float4(v[0], v[1], v[2], v[3]);
+                *reinterpret_cast<float4*>(y + 4) = make_float4(v[4], v[5], v[6], v[7]);
+            }
+        }
+        return;
+    }
+    for (int o = tid; o < M * D.cout; o += NT) {
+        const int lv = o / D.cout, co = o - lv * D.cout;
+        if (m0 + lv >= N) break;
+        const float v = part[lv * CP + co] + part[(M + lv) * CP + co];
+        conv_store(E, m0 + lv, co, v, E.bias ? E.bias[co] : 0.f);
+    }
+}
+
 // Split-K form for small volumes (too few blocks of the forms above to
 // fill the chip): a block takes MT tiles of 16 voxels, its four waves take
 // every fourth 32-wide reduction step (each weight operand a wave loads
@@ -603,12 +826,14 @@ k_conv_bwdw(const u16* __restrict__ X, ConvDims D, const u16* __restrict__ dY, i
 // block shifted by (dy, dz); a tap with dx = +-1 takes one more dword from
 // the neighbouring block and a funnel shift by one element (v_alignbyte).
 
-// XB[b][c][j] = X[voxel 8b + j][c] for c < C (8x8 transposes in registers),
-// for two tensors with the same voxels in one launch: items [0, nblk C0/8)
-// transpose X0 (C0 channels), the rest X1 (C1 channels)
+// XB[b][c][j] = X[voxel 8 (b mod nxb) + j of row b / nxb][c] for c < C (8x8
+// transposes in registers; nxb = ceil(nx / 8) blocks per row, zero past the
+// row's end), for two tensors with the same voxels in one launch: items
+// [0, nblk C0/8) transpose X0 (C0 channels), the rest X1 (C1 channels)
 __global__ void __launch_bounds__(kBlock)
 k_to_xb(const u16* __restrict__ X0, int C0, u16* __restrict__ XB0, const u16* __restrict__ X1,
-        int C1, u16* __restrict__ XB1, long long nblk) {
+        int C1, u16* __restrict__ XB1, long long nblk, int nx) {
+    const int nxb = (nx + 7) / 8;
     const long long n0 = nblk * (C0 / 8);
     const long long total = n0 + nblk * (C1 / 8);
     for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < total;
@@ -616,15 +841,19 @@ k_to_xb(const u16* __restrict__ X0, int C0, u16* __restrict__ XB0, const u16* __
         const bool second = i >= n0;
         const u16* X = second ? X1 : X0;
         u16* XB = second ? XB1 : XB0;
-        const int C = second ? C1 : C0, ld = C, off = 0;
+        const int C = second ? C1 : C0;
         const long long k = second ? i - n0 : i;
         const int C8 = C / 8;
         const int cg = (int)(k % C8);
         const long long b = k / C8;
+        const long long row = b / nxb;
+        const int x0 = (int)(b - row * nxb) * 8;
         uint32_t w[8][4];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const uint4 q = *reinterpret_cast<const uint4*>(X + (b * 8 + j) * ld + off + 8 * cg);
+            uint4 q = make_uint4(0, 0, 0, 0);
+            if (x0 + j < nx)
+                q = *reinterpret_cast<const uint4*>(X + (row * nx + x0 + j) * C + 8 * cg);
             w[j][0] = q.x; w[j][1] = q.y; w[j][2] = q.z; w[j][3] = q.w;
         }
 #pragma unroll
@@ -1371,6 +1600,33 @@ air_status air_conv3d_fwd(const uint16_t* x, const int32_t dims[3], int32_t batc
         }
         return hipGetLastError() == hipSuccess ? AIR_OK : AIR_ERR_LAUNCH;
     }
+    // the linear form on 128-voxel blocks where they give about one per CU,
+    // on 64- and 32-voxel blocks where the weights are large (their re-reads
+    // and latency are what the other forms spend). One layer's three
+    // directions, 112 -> 48 channels: 8 x 16^3 142.8 -> 104.2 us (64: 114.5,
+    // 32: 127.8), 3 x 16^3 95.2 -> 69.1 with 64 (128: 80.7, 32: 74.7), 16^3
+    // 84.1 -> 56.1 with 32 (64: 62.7); 32 -> 48 channels at 16^3 34.5 us on
+    // the split-K form, 35.3 on 32-voxel blocks
+    const long long wk = (long long)cout * D.K;
+    const int lin = N >= 25600 ? 128 : (N >= 11520 && wk >= 40000) ? 64 : wk >= 65536 ? 32 : 0;
+    if (lin) {
+        const LinShape L = lin_shape(D, nt, lin, lin == 128 ? 4 : 8);
+        const long long nb = (N + lin - 1) / lin;
+        if (L.bytes <= kLinMaxLds && nb <= 0x7fffffffLL && (long long)D.nx * D.ny < (1LL << 30)) {
+            const dim3 grid((unsigned)nb), blk(kLinWaves * 64);
+            const int vec = vector_epilogue_ok(E, cout) ? 1 : 0;
+            switch (nt * 256 + lin) {
+#define LIN(T, M_, MT_, MG_) case T * 256 + M_: hipLaunchKernelGGL((k_conv_fwd_lin<T, MT_, MG_>), \
+                                     grid, blk, L.bytes, s, X, D, W, E, vec); break;
+#define CASE(T) LIN(T, 128, 4, 2) LIN(T, 64, 4, 1) LIN(T, 32, 2, 1)
+                CASE(1) CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8)
+#undef CASE
+#undef LIN
+                default: return AIR_ERR_SHAPE;
+            }
+            return hipGetLastError() == hipSuccess ? AIR_OK : AIR_ERR_LAUNCH;
+        }
+    }
     // the most voxels per wave that still give 1024 blocks of four waves;
     // below that, the split-K form with four or one 16-voxel tiles per block
     // keeps the chip busy (code 0: one tile, 3: four tiles)
@@ -1395,9 +1651,26 @@ air_status air_conv3d_fwd(const uint16_t* x, const int32_t dims[3], int32_t batc
     return hipGetLastError() == hipSuccess ? AIR_OK : AIR_ERR_LAUNCH;
 }
 
-// the x-blocked form: whole 8-voxel x blocks and at most four 16-channel
-// output tiles per wave
-static bool bwdw_xb(const int32_t dims[3], int cout) { return dims[0] % 8 == 0 && cout <= 64; }
+// the x-blocked form: at most four 16-channel output tiles per wave, and
+// whole 8-voxel x blocks, or, where the library chooses the chunk, rows padded
+// to them with zeros (both operands, so the pad adds nothing). The padded
+// form pays its copies back on products of at least 2^24 (voxels times
+// channels) and pads of at most 2/5: one layer's three directions, 112 -> 48
+// channels, 8 x 20^3, 376 us with the weight gradient on the tensors as they
+// are, 194 padded; 3 x 12^3 68.5 and 57.4; but 32 -> 48 channels, 3 x 12^3,
+// 31 and 42; 48 -> 64, 8 x 10^3 (padded to 16), 55 and 63. Returns the rows'
+// length in voxels, 0 for the form on the tensors as they are.
+static int bwdw_xb(const int32_t dims[3], long long nz, int cin, int cout, int chunk) {
+    if (cout > 64 || (dims[0] % 8 && chunk)) return 0;
+    const long long nxp = (dims[0] + 7LL) / 8 * 8;
+    if (dims[0] % 8 == 0) return (int)nxp;
+    if (5 * nxp > 7LL * dims[0] || nz * dims[1] * dims[0] * cin * cout < (1LL << 24)) return 0;
+    // offsets of a tap's block in 32 bits, voxel counts of the stack too
+    if (2LL * dims[1] * nxp * cin + 27LL * cin * 8 >= (1LL << 31) ||
+        nxp * dims[1] * nz >= (1LL << 40) || nxp > 0x7fffffffLL)
+        return 0;
+    return (int)nxp;
+}
 
 // voxels per partial of the backward-weight GEMM: about one resident round
 // of blocks (`target` blocks) over the whole reduction
@@ -1415,8 +1688,9 @@ air_status air_conv3d_bwd_weight_workspace(const int32_t dims[3], int32_t batch,
                                            int32_t cout, int32_t chunk, size_t* bytes) {
     if (!dims || !bytes || chunk < 0 || chunk % kBwStep || batch < 1) return AIR_ERR_INVALID_ARG;
     if (dims[0] < 1 || dims[1] < 1 || dims[2] < 1 || cin < 1 || cout < 1) return AIR_ERR_SHAPE;
-    const long long N = (long long)dims[0] * dims[1] * dims[2] * batch;
-    const bool xb = bwdw_xb(dims, cout);
+    const int nxp = bwdw_xb(dims, (long long)dims[2] * batch, cin, cout, chunk);
+    const bool xb = nxp > 0;
+    const long long N = (long long)(xb ? nxp : dims[0]) * dims[1] * dims[2] * batch;
     const long long c = chunk ? chunk : bwdw_chunk(N, cin, cout, xb);
     const long long nch = (N + c - 1) / c;
     if (nch > 65535) return AIR_ERR_SHAPE;
@@ -1442,8 +1716,9 @@ air_status air_conv3d_bwd_weight(const uint16_t* x, const int32_t dims[3], int32
     const long long nz = (long long)dims[2] * batch;
     if (nz > (1LL << 30)) return AIR_ERR_SHAPE;
     ConvDims D{dims[0], dims[1], (int)nz, dims[2], cin, cout, 27 * cin, (27 * cin + 31) / 32 * 32};
-    const long long N = (long long)D.nx * D.ny * D.nz;
-    const bool xb = bwdw_xb(dims, cout);
+    const int nxp = bwdw_xb(dims, nz, cin, cout, chunk);
+    const bool xb = nxp > 0;
+    const long long N = (long long)(xb ? nxp : D.nx) * D.ny * D.nz;
     const long long c = chunk ? chunk : bwdw_chunk(N, cin, cout, xb);
     const int nch = (int)((N + c - 1) / c);
     hipStream_t s = (hipStream_t)stream;
@@ -1463,8 +1738,9 @@ air_status air_conv3d_bwd_weight(const uint16_t* x, const int32_t dims[3], int32
     u16* dYB = XB + ((2 * N * cin + 255) & ~255LL) / 2;
     const long long nblk = N / 8;
     hipLaunchKernelGGL(k_to_xb, dim3(grid1(nblk * ((cin + cout) / 8))), dim3(kBlock), 0, s,
-                       (const u16*)x, (int)cin, XB, (const u16*)dy, (int)cout, dYB, nblk);
-    return air_conv3d_bwd_weight_xb(XB, dims, batch, cin, 0, dYB, cout, chunk, dwt, db, ws, pb,
+                       (const u16*)x, (int)cin, XB, (const u16*)dy, (int)cout, dYB, nblk, (int)dims[0]);
+    const int32_t pdims[3] = {nxp, dims[1], dims[2]};
+    return air_conv3d_bwd_weight_xb(XB, pdims, batch, cin, 0, dYB, cout, chunk, dwt, db, ws, pb,
                                     stream);
 }
 

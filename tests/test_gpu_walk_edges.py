@@ -149,3 +149,61 @@ def test_field_contractions(n, sp, kind):
     F, M = inputs(n, 70)
     th = synth.random_controls(n, p.ncontrol(), 0.7, 71)
     check(p, F, M, th, f"contraction {kind} {n} spacing {sp}")
+
+
+# convolutions on linear blocks of 32, 64 and 128 voxels: partial last blocks,
+# volume seams inside a block, channel counts that are no multiple of 8 or 16,
+# and the weight gradient on rows padded to whole x blocks
+@pytest.mark.parametrize("cin,cout,dims,batch", [
+    (112, 48, (5, 3, 7), 3),       # 32-voxel blocks, several volumes per block
+    (48, 64, (10, 9, 4), 2),       # 32
+    (48, 32, (23, 24, 7), 3),      # 64
+    (32, 48, (12, 15, 31), 3),     # 64; padded weight gradient with seams
+    (8, 24, (33, 29, 27), 1),      # 128, 1.5 channel tiles
+    (16, 20, (40, 40, 17), 1),     # 128, no vector epilogue
+    (64, 128, (21, 16, 77), 1),    # 128, eight channel tiles, padded bank pitch
+    (112, 16, (49, 30, 18), 1),    # rows too wide for the staged runs
+])
+def test_conv_linear_blocks(cin, cout, dims, batch):
+    from paper_1806_09907_amd import cnn
+    nx, ny, nz = dims
+    rng = np.random.default_rng(cin + cout)
+
+    def bf(a):
+        return torch.from_numpy(np.asarray(a, np.float32)).to(DEV).bfloat16().contiguous()
+
+    def host(t):
+        return t.double().cpu().numpy()
+
+    x = bf(rng.normal(size=(batch * nz, ny, nx, cin)))
+    w = bf(rng.normal(size=(cout, 27 * cin)) / np.sqrt(27 * cin))
+    gate = bf(rng.normal(size=(batch * nz, ny, nx, cout)))
+    b = rng.normal(size=cout).astype(np.float32)
+    shape = (batch * nz, ny, nx, cout)
+    y = torch.empty(shape, dtype=torch.float32, device=DEV)
+    yb = torch.empty(shape, dtype=torch.bfloat16, device=DEV)
+    print(f"case conv {cin}->{cout} {dims} x {batch}", flush=True)
+    cnn.conv_fwd(x, dims, cin, w, gpu(b), cout, 1, y_bf=yb, y_f32=y, batch=batch)
+    yg = torch.empty(shape, dtype=torch.bfloat16, device=DEV)
+    cnn.conv_fwd(x, dims, cin, w, None, cout, 2, y_bf=yg, batch=batch, gate=gate, ldg=cout)
+    xh, wh, gh = host(x), host(w), host(gate)
+    pre = np.concatenate([O.conv3d_fwd(xh[v * nz:(v + 1) * nz], wh) for v in range(batch)])
+    ref = pre + b.astype(np.float64)
+    ref = np.where(ref > 0, ref, 0.1 * ref)
+    assert np.linalg.norm(host(y) - ref) <= 1e-5 * np.linalg.norm(ref)
+    assert torch.equal(yb, y.bfloat16())
+    refg = np.where(gh > 0, pre, 0.1 * pre)
+    # one rounding to bf16 on top: half an ulp, 2^-9 of each value
+    assert np.all(np.abs(host(yg) - refg) <= 2.0 ** -8 * np.abs(refg) + 1e-4)
+    if cout % 8 == 0:
+        dy = bf(rng.normal(size=shape))
+        dw = torch.empty((cout, 27 * cin), dtype=torch.float32, device=DEV)
+        db = torch.empty(cout, dtype=torch.float32, device=DEV)
+        cnn.conv_bwd_weight(x, dims, cin, dy, cout, dw, db, cnn.Workspace(DEV), batch=batch)
+        dyh = host(dy)
+        rw, rb = np.zeros((cout, 27 * cin)), np.zeros(cout)
+        for v in range(batch):
+            _, dwv, dbv = O.conv3d_bwd(xh[v * nz:(v + 1) * nz], wh, dyh[v * nz:(v + 1) * nz])
+            rw, rb = rw + dwv, rb + dbv
+        assert np.linalg.norm(host(dw) - rw) <= 1e-5 * np.linalg.norm(rw)
+        assert np.linalg.norm(host(db) - rb) <= 1e-5 * np.linalg.norm(rb)
