@@ -148,7 +148,9 @@ air_status air_plan_param_count(const air_plan* plan, int32_t pair, int64_t* cou
 int32_t air_tiling_count(int32_t dim);
 air_status air_tiling_describe(int32_t dim, int32_t id, int32_t* tile_x, int32_t* tile_y,
                                int32_t* column_cells);
-/* Select a tile configuration; changes the workspace size and re-uploads. */
+/* Select a tile configuration; changes the workspace size and re-uploads. (2D
+ * plans of small pairs that keep the default evaluate each pair in one block
+ * instead of tiles; selecting a configuration selects the tiles.) */
 air_status air_plan_set_tiling(air_plan* plan, int32_t id);
 air_status air_plan_get_tiling(const air_plan* plan, int32_t* id);
 

@@ -144,6 +144,8 @@ struct FusedShape {
     size_t lds = 0;       // bytes of dynamic LDS of a block
     int max_ctrl = 0;     // most controls of a pair
     int ctrl_tiles = 0;   // most tiles whose window holds one control
+    int whole = 0;        // pixels per thread of the one-block 2D kernel (0: tiles)
+    size_t whole_lds = 0; // and its LDS bytes
 };
 
 __host__ __device__ inline int cdiv(int a, int b) { return (a + b - 1) / b; }

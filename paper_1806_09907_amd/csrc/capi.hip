@@ -18,6 +18,7 @@
 namespace air {
 hipError_t launch_bspline(const LaunchCtx& C, int cfg, const FusedShape& F, hipStream_t s,
                           hipEvent_t ev0, hipEvent_t ev1);
+int whole2_pixels(const int* n, const int* nc, const int* sp, size_t* lds);
 hipError_t launch_reg_bspline(const PairDesc* dpairs, const PairDesc& hp, int pair,
                               const float* consts, const float* theta, float* grad_out,
                               double* regpart, float* value, int dim, size_t lds, hipStream_t s);
@@ -106,6 +107,11 @@ constexpr int kLongWalk = 48, kLongTiles = 800;
 // the same for 2D B-spline plans (64-lane columns of 16, 8, 4, 2, 1 cells)
 static const int kCfg2Fill[] = {3, 2, 1, 0, 4};
 constexpr int kFillTiles2 = 2048;
+// 2D pairs of up to this many pixels are evaluated by one block each: 64^2 MSE
+// 16.3 -> 11.2 us per evaluation, 48 x 51 NCC 17.9 -> 13.3; at 90^2 both ways
+// take 16.6 (spacing 8) and 21.8 us (spacing 6, NCC), at 60 x 270 the tiles
+// 18.6 and one block 23.8
+constexpr long long kWholeMaxPixels = 7168;
 
 // kernel variant ids understood by launch_bspline (3D): 3, 4 the spacing-8
 // kernels, 5 - 7 the pipelined kernel of any spacing whose tiles see at most
@@ -147,6 +153,7 @@ struct air_plan {
     int reg = AIR_REG_DIFFUSION;  // regulariser kind
     float reg_weight = 0.f;       // its weight (TV plans; diffusion weights live per pair)
     int tiling = 0;
+    bool tiling_set = false;  // chosen by the caller (no one-block kernel then)
     std::vector<air_problem> probs;
     std::vector<PairDesc> pd;
     std::vector<float> consts;
@@ -546,6 +553,21 @@ static air_status build_tables(air_plan* P, int dense_zc, bool pipelined) {
     P->lds_reg = lds_r;
     P->fused.max_ctrl = max_ctrl;
     P->fused.ctrl_tiles = ctrl_tiles;
+    // a 2D plan of small pairs with no tiling of the caller's: one block per
+    // pair
+    P->fused.whole = 0;
+    P->fused.whole_lds = 0;
+    if (bs && d == 2 && !P->tiling_set) {
+        int px = 1;
+        for (const PairDesc& D : P->pd) {
+            size_t lds = 0;
+            const int q = D.nvox <= kWholeMaxPixels ? whole2_pixels(D.n, D.nc, D.sp, &lds) : 0;
+            px = q == 0 ? 0 : std::max(px, q);
+            if (px == 0) break;
+            P->fused.whole_lds = std::max(P->fused.whole_lds, lds);
+        }
+        P->fused.whole = px;
+    }
     P->max_dense_blk = max_dense;
     WsLayout& L = P->L;
     size_t off = 0;
@@ -1161,10 +1183,13 @@ air_status air_plan_set_tiling(air_plan* plan, int32_t id) {
     if (id < 0 || id >= air_tiling_count(plan->dim)) return AIR_ERR_INVALID_ARG;
     std::lock_guard<std::mutex> g(plan->mu);
     const int old = plan->tiling;
+    const bool old_set = plan->tiling_set;
     plan->tiling = id;
+    plan->tiling_set = true;
     air_status st = build_tables(plan);
     if (st != AIR_OK) {
         plan->tiling = old;
+        plan->tiling_set = old_set;
         build_tables(plan);
         return st;
     }

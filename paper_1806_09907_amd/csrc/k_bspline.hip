@@ -1670,6 +1670,272 @@ k_finalize(const LaunchCtx C) {
     if (bad) atomicOr(flags, AIR_FLAG_NONFINITE);
 }
 
+// --------------------------------------------------------------- small 2D pairs
+// The whole evaluation of a small 2D pair in one block of 1024 threads, PX
+// pixels each: images, controls and tables are loaded together once, and
+// every later stage runs from LDS and registers, so the evaluation waits for
+// memory once and is one launch. The tile kernels spread such a pair over a
+// few dozen single waves, each a chain of dependent loads, and need the
+// finalize as a second launch. Same displacements, cells and mask as
+// k_fused2; NCC's coefficients are known before the transposes, so one field
+// per component is transposed instead of three. Bound by the one CU's VALU
+// issue (about 1000 instructions per thread): 64^2 MSE 16.7 us of kernels ->
+// 9.5.
+constexpr int kWholeThreads = 1024;
+constexpr size_t kWholeMaxLds = 150 * 1024;
+struct WholeLds {   // float offsets; G (2 npix) shares the space of M and T
+    int th, ap, ad, gram, wx, wy, m, t, total;
+};
+__host__ __device__ inline WholeLds whole_lds(const int* n, const int* nc, const int* sp) {
+    const int np = n[0] * n[1], ctl = nc[0] * nc[1], row = nc[1] * n[0];
+    WholeLds L{};
+    int o = 2 * 8 * (kWholeThreads / 64);            // block_sum's doubles
+    L.th = o;   o += a4(2 * ctl);
+    L.ap = o;   o += a4(2 * ctl);
+    L.ad = o;   o += a4(2 * ctl);
+    L.gram = o; o += a4(14 * (nc[0] + nc[1]));
+    L.wx = o;   o += 4 * sp[0];
+    L.wy = o;   o += 4 * sp[1];
+    L.t = o;    o += a4(2 * row);                    // T1, then the y-transposed field
+    L.m = o;
+    o += a4(2 * np);                                 // M, then the two field components
+    L.total = o;
+    return L;
+}
+// block_sum for K <= 8 doubles and sixteen waves, the waves' sums added by
+// groups of sixteen lanes (every thread gets the totals).
+template <int K>
+__device__ inline void whole_sum(double (&v)[K], double* scratch) {
+    constexpr int NW = kWholeThreads / 64;
+    static_assert(NW == 16 && K <= 8, "one lane per wave in a group of sixteen");
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = wave_sum(v[k]);
+    if (lane == 0)
+#pragma unroll
+        for (int k = 0; k < K; ++k) scratch[k * NW + (threadIdx.x >> 6)] = v[k];
+    __syncthreads();
+    double t[2];
+#pragma unroll
+    for (int h = 0; h < (K + 3) / 4; ++h) {
+        const int k = min((lane >> 4) + 4 * h, K - 1);
+        t[h] = scratch[k * NW + (lane & 15)];
+#pragma unroll
+        for (int o = 8; o >= 1; o >>= 1) t[h] += __shfl_xor(t[h], o, 16);
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = __shfl(t[k >> 2], 16 * (k & 3), 64);
+}
+// n / d for 0 <= n < 2^20 with inv = 1 / d in FP32: (n + 1/2) / d is at least
+// 1 / (2 d) from an integer, more than the product's rounding.
+__device__ inline int div_small(int n, float inv) { return (int)(((float)n + 0.5f) * inv); }
+template <int SIM, int PX>
+__global__ void __launch_bounds__(kWholeThreads)
+k_whole2(const LaunchCtx C) {
+    constexpr int NT = kWholeThreads;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    double* red = reinterpret_cast<double*>(smem_raw);
+    float* lds = reinterpret_cast<float*>(smem_raw);
+    const int pair = blockIdx.x, tid = threadIdx.x;
+    const PairDesc P = C.pairs[pair];
+    const float* __restrict__ F = C.fixed_tab ? C.fixed_tab[pair] : C.fixed0;
+    const float* __restrict__ M = C.moving_tab ? C.moving_tab[pair] : C.moving0;
+    const float* __restrict__ theta = C.theta_tab ? C.theta_tab[pair] : C.theta0;
+    float* grad = C.grad_tab ? C.grad_tab[pair] : C.grad0;
+    const int nx = P.n[0], ny = P.n[1], np = nx * ny;
+    const int ncx = P.nc[0], ncy = P.nc[1], ctl = ncx * ncy;
+    const int sx = P.sp[0], sy = P.sp[1];
+    const float inx = 1.f / nx, incx = 1.f / ncx, isx = 1.f / sx, isy = 1.f / sy;
+    const WholeLds L = whole_lds(P.n, P.nc, P.sp);
+    float *TH = lds + L.th, *AP = lds + L.ap, *AD = lds + L.ad, *GR = lds + L.gram;
+    float *WX = lds + L.wx, *WY = lds + L.wy, *T1 = lds + L.t, *MI = lds + L.m;
+    // everything the evaluation reads from memory
+    float Fv[PX], mv[PX];
+#pragma unroll
+    for (int i = 0; i < PX; ++i) {
+        const int q = min(tid + i * NT, np - 1);
+        Fv[i] = F[q];
+        mv[i] = M[q];
+    }
+    const int qc = (ny / 2) * nx + nx / 2;
+    const float shF = SIM == AIR_SIM_NCC ? F[qc] : 0.f, shW = SIM == AIR_SIM_NCC ? M[qc] : 0.f;
+    for (int i = tid; i < 2 * ctl; i += NT) TH[i] = theta[i];
+    const int gx = 14 * ncx, gy = 14 * ncy;
+    for (int i = tid; i < gx + gy; i += NT)
+        GR[i] = i < gx ? C.consts[P.gram_off[0] + i] : C.consts[P.gram_off[1] + i - gx];
+    for (int i = tid; i < 4 * (sx + sy); i += NT) {
+        if (i < 4 * sx) WX[i] = C.consts[P.wtab_off[0] + i];
+        else WY[i - 4 * sx] = C.consts[P.wtab_off[1] + i - 4 * sx];
+    }
+#pragma unroll
+    for (int i = 0; i < PX; ++i)
+        if (tid + i * NT < np) MI[tid + i * NT] = mv[i];
+    __syncthreads();
+    // control rows interpolated along x, and the regulariser's y products
+    const float *Px = GR, *Dx = GR + 7 * ncx, *Py = GR + gx, *Dy = Py + 7 * ncy;
+    for (int o = tid; o < 2 * ncy * nx; o += NT) {
+        const int row = div_small(o, inx), x = o - row * nx;   // row = c ncy + jy
+        const int ix = div_small(x, isx);
+        const float* w = WX + (x - ix * sx) * 4;
+        const float* t = TH + row * ncx + ix;
+        T1[o] = w[0] * t[0] + w[1] * t[1] + w[2] * t[2] + w[3] * t[3];
+    }
+    for (int o = tid; o < 2 * ctl; o += NT) {
+        const int c = o >= ctl ? 1 : 0, j = o - c * ctl, ky = div_small(j, incx);
+        float ap = 0.f, ad = 0.f;
+#pragma unroll
+        for (int d = -3; d <= 3; ++d) {
+            if (ky + d < 0 || ky + d >= ncy) continue;
+            const float a = TH[o + d * ncx];
+            ap += Py[ky * 7 + d + 3] * a;
+            ad += Dy[ky * 7 + d + 3] * a;
+        }
+        AP[o] = ap;
+        AD[o] = ad;
+    }
+    __syncthreads();
+    // pixels: sample, derivatives, moments
+    int cnt = 0;
+    float m1 = 0.f, m2 = 0.f, m3 = 0.f, m4 = 0.f, m5 = 0.f;
+    float Wv[PX], d0[PX], d1[PX];
+    unsigned int inm = 0;
+#pragma unroll
+    for (int i = 0; i < PX; ++i) {
+        const int q = min(tid + i * NT, np - 1);
+        const int y = div_small(q, inx), x = q - y * nx, iy = div_small(y, isy);
+        const float* wy = WY + (y - iy * sy) * 4;
+        float u[2];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const float* t = T1 + (c * ncy + iy) * nx + x;
+            u[c] = wy[0] * t[0] + wy[1] * t[nx] + wy[2] * t[2 * nx] + wy[3] * t[3 * nx];
+        }
+        const AxisCell ax = axis_cell(x, Disp{u[0] * P.s[0], 0.f}, nx);
+        const AxisCell ay = axis_cell(y, Disp{u[1] * P.s[1], 0.f}, ny);
+        const bool in = tid + i * NT < np && ax.in && ay.in;
+        // a point on the last pixel takes the cell below with f = 1
+        const bool ex = ax.t == nx - 1, ey = ay.t == ny - 1;
+        const int jx = min(max(ex ? nx - 2 : ax.t, 0), nx - 2);
+        const int jy = min(max(ey ? ny - 2 : ay.t, 0), ny - 2);
+        const float fx = ex ? 1.f : ax.f, fy = ey ? 1.f : ay.f;
+        const float* a = MI + jy * nx + jx;
+        const float dy0 = a[nx] - a[0], dy1 = a[nx + 1] - a[1];
+        const float g0 = a[0] + fy * dy0, g1 = a[1] + fy * dy1;
+        const float W = g0 + fx * (g1 - g0);
+        Wv[i] = in ? W : 0.f;
+        d0[i] = in ? (ex ? -W : g1 - g0) : 0.f;
+        d1[i] = in ? (ey ? -W : dy0 + fx * (dy1 - dy0)) : 0.f;
+        if (in) {
+            inm |= 1u << i;
+            cnt += 1;
+            if (SIM == AIR_SIM_NCC) {
+                const float dF = Fv[i] - shF, dW = W - shW;
+                m1 += dF;
+                m2 += dW;
+                m3 += dF * dF;
+                m4 += dW * dW;
+                m5 += dF * dW;
+            } else {
+                const float e = W - Fv[i];
+                m1 += e * e;
+            }
+        }
+    }
+    // regulariser: its value (with this reduction) from the x products
+    double vr = 0.0;
+    for (int o = tid; o < 2 * ctl; o += NT) {
+        const int row = div_small(o, incx) * ncx, kx = o - row;
+        float r = 0.f;
+#pragma unroll
+        for (int d = -3; d <= 3; ++d) {
+            if (kx + d < 0 || kx + d >= ncx) continue;
+            const int j = row + kx + d;
+            r += Dx[kx * 7 + d + 3] * AP[j] + Px[kx * 7 + d + 3] * AD[j];
+        }
+        vr += (double)TH[o] * (double)r;
+        TH[o] = P.lambda * 2.0f * P.inv_xr * r;   // its gradient (no one else reads TH[o] now)
+    }
+    double v[7] = {(double)cnt, (double)m1, (double)m2, (double)m3, (double)m4, (double)m5, vr};
+    if constexpr (SIM == AIR_SIM_NCC) {
+        whole_sum(v, red);
+    } else {
+        double w[3] = {v[0], v[1], vr};
+        whole_sum(w, red);
+        v[0] = w[0];
+        v[1] = w[1];
+        v[6] = w[2];
+    }
+    if (SIM == AIR_SIM_NCC) {   // moments about zero, as the tiles' are summed
+        const double N = v[0], f1 = v[1], w1 = v[2], sF = shF, sW = shW;
+        v[5] += sF * w1 + sW * f1 + N * sF * sW;
+        v[3] += 2.0 * sF * f1 + N * sF * sF;
+        v[4] += 2.0 * sW * w1 + N * sW * sW;
+        v[1] += N * sF;
+        v[2] += N * sW;
+    }
+    const Coef k = coef_from_sums<SIM>(v);
+    // the adjoint field (MI is read no more), one value per component
+    float* G = MI;
+#pragma unroll
+    for (int i = 0; i < PX; ++i) {
+        const int q = tid + i * NT;
+        if (q >= np) break;
+        float e = 0.f;
+        if ((inm >> i) & 1u)
+            e = SIM == AIR_SIM_NCC
+                    ? (float)(k.alpha * ((double)Fv[i] - k.muF) + k.beta * ((double)Wv[i] - k.muW))
+                    : Wv[i] - Fv[i];
+        G[q] = e * d0[i];
+        G[np + q] = e * d1[i];
+    }
+    __syncthreads();
+    // y: T1[c][jy][x] = sum over the rows of the four cells of control jy
+    for (int o = tid; o < 2 * ncy * nx; o += NT) {
+        const int row = div_small(o, inx), x = o - row * nx;
+        const int c = row >= ncy ? 1 : 0, jy = row - c * ncy;
+        const float* g = G + c * np + x;
+        float s = 0.f;
+#pragma unroll
+        for (int kk = 3; kk >= 0; --kk) {                  // rows in increasing order
+            const int y0 = (jy - kk) * sy, y1 = min(y0 + sy, ny);
+            if (y0 < 0) continue;
+#pragma unroll 4
+            for (int y = y0; y < y1; ++y) s += WY[(y - y0) * 4 + kk] * g[y * nx];
+        }
+        T1[o] = s;
+    }
+    __syncthreads();
+    // x: four lanes per control, a cell each
+    constexpr int KT = 4;
+    bool bad = false;
+    for (int o = tid; o < 2 * ctl * KT; o += NT) {
+        const int kk = o % KT, j = o / KT, row = div_small(j, incx), jx = j - row * ncx;
+        const float* g = T1 + row * nx;
+        const int x0 = (jx - kk) * sx, x1 = min(x0 + sx, nx);
+        float s = 0.f;
+        if (x0 >= 0)
+#pragma unroll 4
+            for (int x = x0; x < x1; ++x) s += WX[(x - x0) * 4 + kk] * g[x];
+        s += __shfl_xor(s, 1, KT);
+        s += __shfl_xor(s, 2, KT);
+        if (kk == 0) {
+            const double a = SIM == AIR_SIM_NCC ? 1.0 : k.alpha;
+            const int c = row >= ncy ? 1 : 0;
+            const float out =
+                (k.degenerate ? 0.f : (float)(a * (double)s * (double)P.s[c])) + TH[j];
+            grad[j] = out;
+            bad = bad || !isfinite(out);
+        }
+    }
+    const int anybad = __syncthreads_or(bad ? 1 : 0);
+    if (tid == 0) {
+        uint32_t* flags = reinterpret_cast<uint32_t*>(C.ws + C.L.flags) + pair;
+        *flags = 0u;
+        store_pair_coef(C, P, pair, k, v[6] * (double)P.inv_xr);
+        if (anybad) atomicOr(flags, AIR_FLAG_NONFINITE);
+    }
+}
+
 // --------------------------------------------------------------- launchers
 template <int TX, int TY, int SIM>
 static hipError_t launch3(const LaunchCtx& C, size_t lds, hipStream_t s) {
@@ -1706,6 +1972,21 @@ static hipError_t launch_fin(const LaunchCtx& C, const FusedShape& F, hipStream_
     return launch_fin_ns<TX, TY, SIM, DIM, kFinLanes, SP>(C, F.max_ctrl, s);
 }
 
+// Pixels per thread (1, 2, 4, 8) of the one-block kernel for a 2D pair, and its
+// LDS; 0 if the pair is too large for it.
+int whole2_pixels(const int* n, const int* nc, const int* sp, size_t* lds) {
+    const long long np = (long long)n[0] * n[1];
+    if (np > 8 * kWholeThreads) return 0;
+    const WholeLds L = whole_lds(n, nc, sp);
+    *lds = sizeof(float) * (size_t)L.total;
+    if ((long long)nc[0] * nc[1] > 16 * kWholeThreads ||
+        L.total <= 0 || *lds > kWholeMaxLds)
+        return 0;
+    int px = 1;
+    while (np > (long long)px * kWholeThreads) px *= 2;
+    return px;
+}
+
 // cfg: in 3D the tile configuration (id -> TX, TY); in 2D 8 when every pair
 // has spacing 8, else 0. Column cells come from the plan.
 hipError_t launch_bspline(const LaunchCtx& C, int cfg, const FusedShape& F, hipStream_t s,
@@ -1739,6 +2020,22 @@ hipError_t launch_bspline(const LaunchCtx& C, int cfg, const FusedShape& F, hipS
             case 3: return ncc ? launch_fin<32, 8, 1, 3, 8>(C, F, s) : launch_fin<32, 8, 0, 3, 8>(C, F, s);
             default: return ncc ? launch_fin<16, 16, 1, 3, 8>(C, F, s) : launch_fin<16, 16, 0, 3, 8>(C, F, s);
         }
+    }
+    if (F.whole > 0) {
+        const bool ncc = C.sim == AIR_SIM_NCC;
+        const dim3 grid(C.npairs), blk(kWholeThreads);
+        switch (F.whole) {
+#define CASE(PX) case PX:                                                                      \
+        if (ncc) hipLaunchKernelGGL((k_whole2<1, PX>), grid, blk, F.whole_lds, s, C);           \
+        else hipLaunchKernelGGL((k_whole2<0, PX>), grid, blk, F.whole_lds, s, C);               \
+        break;
+            CASE(1) CASE(2) CASE(4) CASE(8)
+#undef CASE
+            default: return hipErrorInvalidValue;
+        }
+        e = hipGetLastError();
+        if (e == hipSuccess && ev1) (void)hipEventRecord(ev1, s);
+        return e;
     }
     const int nblk = xcd_grid(C.ntiles_total, C.nreg_total);
     if (C.sim == AIR_SIM_NCC)

@@ -207,3 +207,50 @@ def test_conv_linear_blocks(cin, cout, dims, batch):
             rw, rb = rw + dwv, rb + dbv
         assert np.linalg.norm(host(dw) - rw) <= 1e-5 * np.linalg.norm(rw)
         assert np.linalg.norm(host(db) - rb) <= 1e-5 * np.linalg.norm(rb)
+
+
+# small 2D pairs, one block each: the edges of 1, 2, 4 and 7 pixels per thread,
+# controls as dense as the pixels, one cell for the whole image, the last
+# size before the tiles, and images no wider than a cell
+SMALL2 = [((32, 32), (8, 8)), ((33, 31), (8, 8)), ((64, 32), (5, 3)), ((41, 50), (4, 4)),
+          ((64, 64), (8, 8)), ((65, 63), (8, 16)), ((112, 64), (8, 8)), ((7168 // 2, 2), (16, 1)),
+          ((2, 2), (4, 4)), ((9, 300), (2, 64)), ((40, 41), (1, 1)), ((3, 1000), (8, 8))]
+
+
+@pytest.mark.parametrize("n,sp", SMALL2)
+@pytest.mark.parametrize("sim", [api.SIM_MSE, api.SIM_NCC])
+def test_small_2d_one_block(n, sp, sim):
+    p = api.Problem(n=n, spacing=sp, similarity=sim, lambda_diff=0.1)
+    F, M = inputs(n, 80)
+    check(p, F, M, synth.random_theta(n, sp, 0.8, 81), f"small 2D {n} spacing {sp} sim={sim}")
+
+
+def test_small_2d_batch_flags_and_tiles():
+    """A batch of small pairs; one of them entirely outside (degenerate), one
+    with a NaN control (non-finite); and the tiles a caller selects agree."""
+    sizes = [(40, 31), (64, 64), (33, 70), (20, 20)]
+    probs = [api.Problem(n=n, spacing=(8, 8), similarity=api.SIM_NCC, lambda_diff=0.05)
+             for n in sizes]
+    data = [inputs(n, 90 + i) for i, n in enumerate(sizes)]
+    ths = [synth.random_theta(n, (8, 8), 1.0, 95 + i) for i, n in enumerate(sizes)]
+    ths[2] = ths[2] + np.float32(5.0)
+    ths[3] = ths[3].copy()
+    ths[3][0, 2, 2] = np.nan
+    F, M, T = ([gpu(d[0]) for d in data], [gpu(d[1]) for d in data], [gpu(t) for t in ths])
+    plan = api.Plan(probs)
+    vals, grads, _ = api.objective_and_grad_batched(plan, F, M, T)
+    flags = api.get_flags(plan)
+    assert flags[0] == flags[1] == 0
+    assert flags[2] == api.FLAG_DEGENERATE and flags[3] & api.FLAG_NONFINITE
+    tiled = api.Plan(probs, tiling=plan.tiling)
+    vt, gt, _ = api.objective_and_grad_batched(tiled, F, M, T)
+    assert api.get_flags(tiled) == flags
+    for i in range(3):
+        if i == 2:
+            assert torch.equal(grads[i], gt[i])
+            continue
+        op = O.Problem(n=sizes[i], spacing=(8, 8), similarity=O.SIM_NCC, lambda_diff=0.05)
+        vo, go, _ = O.objective_and_grad(op, data[i][0], data[i][1], ths[i])
+        for v, g in ((vals, grads), (vt, gt)):
+            assert abs(float(v[i]) - vo) <= VAL_TOL * abs(vo)
+            check_grad(g[i].double().cpu().numpy(), go, f"small 2D batch pair {i}")
