@@ -61,7 +61,7 @@ hipError_t launch_wendland_adjoint(const PairDesc& P, const float* consts_dev, i
                                    bool accumulate, hipStream_t s);
 int wendland_cells_per_wave();
 int wendland_h_parts();
-int lcc_partials(const PairDesc& P);
+int lcc_partials(const PairDesc& P, int dim, int r);
 size_t lcc_lds_bytes(int r);
 bool lcc_fused(int dim, int r);
 hipError_t launch_lcc(const PairDesc& P, int dim, int r, const float* F, const float* M,
@@ -609,7 +609,7 @@ static air_status build_tables(air_plan* P, int dense_zc, bool pipelined) {
         L.lcc_s = off;     // the FP64 box sums only where the passes are not fused
         if (!lcc_fused(P->dim, P->lcc_radius)) off = align256(off + 6 * N * 8);
         L.lcc_a = off;     off = align256(off + 3 * N * 4);
-        L.lcc_part = off;  off = align256(off + 2 * (size_t)lcc_partials(D) * 8);
+        L.lcc_part = off;  off = align256(off + 2 * (size_t)lcc_partials(D, P->dim, P->lcc_radius) * 8);
         L.lcc_scal = off;  off = align256(off + 8);
     }
     L.total = off;
@@ -1072,6 +1072,7 @@ uint32_t debug_take_bspline();
 uint32_t debug_take_dense();
 uint32_t debug_take_diffeo();
 uint32_t debug_take_cnn();
+uint32_t debug_take_lcc();
 }  // namespace air
 #endif
 
@@ -1082,7 +1083,8 @@ air_status air_debug_bounds_take(uint32_t* flags) {
     *flags = 0;
 #ifdef AIR_DEBUG_BOUNDS
     if (hipDeviceSynchronize() != hipSuccess) return AIR_ERR_DEVICE;
-    *flags = debug_take_bspline() | debug_take_dense() | debug_take_diffeo() | debug_take_cnn();
+    *flags = debug_take_bspline() | debug_take_dense() | debug_take_diffeo() | debug_take_cnn() |
+             debug_take_lcc();
     return AIR_OK;
 #else
     return AIR_ERR_UNSUPPORTED;

@@ -254,3 +254,33 @@ def test_small_2d_batch_flags_and_tiles():
         for v, g in ((vals, grads), (vt, gt)):
             assert abs(float(v[i]) - vo) <= VAL_TOL * abs(vo)
             check_grad(g[i].double().cpu().numpy(), go, f"small 2D batch pair {i}")
+
+
+# LCC: tiles of 32 x 8 columns and their remainders, one to several z chunks
+# (shorter than the window too), every radius of the fused passes and one past
+# them, samples outside the volume
+@pytest.mark.parametrize("n,r", [((33, 9, 5), 1), ((31, 8, 3), 4), ((64, 17, 70), 3),
+                                 ((100, 40, 9), 2), ((32, 16, 37), 4), ((34, 7, 12), 5)])
+@pytest.mark.parametrize("tf", [api.TF_DENSE, api.TF_BSPLINE3])
+def test_lcc_walks(n, r, tf):
+    p = api.Problem(n=n, transform=tf, spacing=(1, 1, 1) if tf == api.TF_DENSE else (8, 8, 8),
+                    similarity=api.SIM_LCC, lcc_radius=r, lambda_diff=0.1)
+    F, M = inputs(n, 17)
+    shape = (3,) + tuple(reversed(n)) if tf == api.TF_DENSE else p.param_shape()
+    th = np.random.default_rng(18).normal(0.0, 0.5, shape)
+    for a in range(3):
+        th[a] *= 2.0 / (n[a] - 1)
+    check(p, F, M, th.astype(np.float32), f"lcc walk {n} r={r} tf={tf}")
+
+
+@pytest.mark.parametrize("n", [(2, 9, 7), (5, 300, 4), (257, 3, 11), (70, 41), (3, 65)])
+def test_lcc_sampling_far_outside(n):
+    """Paired gathers at every kind of edge: displacements of up to more than
+    half the volume. The window of radius 8 keeps every variance far from 0,
+    where the coefficients are well conditioned."""
+    d = len(n)
+    p = api.Problem(n=n, transform=api.TF_DENSE, spacing=(1,) * d, similarity=api.SIM_LCC,
+                    lcc_radius=8, lambda_diff=0.0)
+    F, M = inputs(n, 19, 6)
+    th = np.random.default_rng(20).uniform(-1.2, 1.2, (d,) + tuple(reversed(n))).astype(np.float32)
+    check(p, F, M, th, f"lcc outside {n}")
