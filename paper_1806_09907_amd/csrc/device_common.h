@@ -31,6 +31,15 @@ __device__ inline v2f load2(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
     return __builtin_bit_cast(v2f, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
 }
 
+// Byte offset past every volume (4 nvox < 2^31): loads give 0, stores are dropped.
+constexpr int kNoElem = 0x7ffffff0;
+__device__ inline uint8_t load1u8(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
+    return __builtin_amdgcn_raw_buffer_load_b8(r, voff, soff, 0);
+}
+__device__ inline void store1(__amdgpu_buffer_rsrc_t r, float v, int voff, int soff) {
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), r, voff, soff, 0);
+}
+
 // Bounds checks of computed indices, compiled in the debug build
 // (-DAIR_DEBUG_BOUNDS, libairhip_debug.so) and empty otherwise. A failed
 // check sets its bit in the flag word of its translation unit (a buffer

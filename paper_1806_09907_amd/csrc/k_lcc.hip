@@ -45,14 +45,6 @@ __device__ inline void lcc_coef(const double* s, float* aB, float* aD, float* aE
     *rho = r;
 }
 
-constexpr int kNoElem = 0x7ffffff0;   // byte offset past every volume (4 nvox < 2^31)
-__device__ inline uint8_t load1u8(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
-    return __builtin_amdgcn_raw_buffer_load_b8(r, voff, soff, 0);
-}
-__device__ inline void store1(__amdgpu_buffer_rsrc_t r, float v, int voff, int soff) {
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), r, voff, soff, 0);
-}
-
 // Gathers of one zero-padded sample: the x pairs of its 2^(DIM-1) rows, each
 // in one load at the clamped pair start. A row outside the volume reads zeros
 // (kNoElem); lo and hi tell which of a pair is the cell's left and right

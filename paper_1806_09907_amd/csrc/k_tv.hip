@@ -3,7 +3,7 @@
 //   isotropic:   R = (1/|X_R|) sum_{x in X_R} sqrt(sum_c sum_a D_a u_c(x)^2)
 // with the forward differences D_a u_c(x) = u_c(x + e_a) - u_c(x) over
 // X_R = prod_a [0, n_a - 2] (the diffusion term's discretisation) and the
-// subgradient 0 where a term is 0. One thread per voxel x writes
+// subgradient 0 where a term is 0. Every voxel x gets
 //   dR/du_c(x) = (1/|X_R|) (sum_a [x - e_a in X_R] k_ca(x - e_a)
 //                           - [x in X_R] sum_a k_ca(x)),
 // k = sign(D) (anisotropic) or D / ||J|| (isotropic), where J(y) is the
@@ -16,28 +16,31 @@ namespace air {
 namespace {
 
 constexpr int kTvBlocks = 4096;
-
-__host__ inline int tv_grid(long long n) {
-    const long long b = (n + kBlock - 1) / kBlock;
-    return (int)(b < kTvBlocks ? (b < 1 ? 1 : b) : kTvBlocks);
+// items: kBlock columns by zc planes
+__host__ __device__ inline int tv_items(const PairDesc& P, int zc) {
+    return cdiv(P.n[0] * P.n[1], kBlock) * cdiv(P.n[2], zc);
+}
+// Planes a thread walks: 8, or fewer where that leaves less than two blocks
+// a CU (a walk's planes are a serial chain of loads): 48 x 40 x 33
+// takes 32.7 us an evaluation so and 37.5 with 8, 64^3 57.6 and 61.4.
+__host__ inline int tv_zc(const PairDesc& P) {
+    int zc = 8;
+    while (zc > 1 && tv_items(P, zc) < 512) zc /= 2;
+    return zc;
 }
 
-// k_ca(y) for every c, a at a point y of X_R; returns the term's value at y.
+// k_ca for every c, a from the differences at a point of X_R; returns the
+// term's value there.
 template <int DIM, int KIND>
-__device__ inline float tv_coef(const float* __restrict__ u, long long N, const long long* st,
-                                long long y, float (*k)[3]) {
-    float D[3][3];
+__device__ inline float tv_coef(const float (*D)[3], float (*k)[3]) {
     float ss = 0.f, l1 = 0.f;
 #pragma unroll
-    for (int c = 0; c < DIM; ++c) {
-        const float u0 = u[c * N + y];
+    for (int c = 0; c < DIM; ++c)
 #pragma unroll
         for (int a = 0; a < DIM; ++a) {
-            D[c][a] = u[c * N + y + st[a]] - u0;
             ss += D[c][a] * D[c][a];
             l1 += fabsf(D[c][a]);
         }
-    }
     if (KIND == AIR_REG_ANISO_TV) {
 #pragma unroll
         for (int c = 0; c < DIM; ++c)
@@ -55,54 +58,154 @@ __device__ inline float tv_coef(const float* __restrict__ u, long long N, const 
     return nrm;
 }
 
+// What a plane adds to the values a column carries: the neighbours of the
+// voxel within its plane, the three points of the plane above that the terms
+// at x, x - e_x and x - e_y reach, and the gradient to add to.
+template <int DIM>
+struct TvRow {
+    float xp[DIM], yp[DIM], xmyp[DIM], xpym[DIM], u1[DIM], xm1[DIM], ym1[DIM], g[DIM];
+};
+
 // grad (+)= scale * dR/du; partial[block] = sum over the block's voxels in X_R
-// of the term (FP64).
+// of the term (FP64). Bound by its loads: a voxel's gradient needs the terms
+// at four points, 48 values when each is formed by itself. A thread walks
+// zc planes of one column: the three values of the plane above are the next
+// plane's own, and its term at x - e_z is the last plane's term at x, so a
+// voxel loads 21 values, one plane ahead of their use; neighbouring items run
+// on one XCD. 128^3 (anisotropic, added to a gradient): 20.9 -> 18.4 us;
+// whole evaluations 181 x 217 x 181 isotropic 244 -> 196 us, 256^3 664 -> 583.
 template <int DIM, int KIND>
 __global__ void __launch_bounds__(kBlock)
-k_tv(const PairDesc P, const float* __restrict__ u, float scale, float* __restrict__ grad,
+k_tv(const PairDesc P, int zc, const float* __restrict__ u, float scale, float* __restrict__ grad,
      int accumulate, double* __restrict__ partial) {
     __shared__ double red[8 * (kBlock / 64)];
     const long long N = P.nvox;
-    const int nx = P.n[0], ny = P.n[1], nz = P.n[2];
-    const long long st[3] = {1, nx, (long long)nx * ny};
+    const int nx = P.n[0], ny = P.n[1], nz = P.n[2], sz = nx * ny;
+    const int ncb = cdiv(sz, kBlock), T = tv_items(P, zc), tq = (T + 7) / 8;
     const float inv_xr = P.inv_xr;
+    const uint32_t nb = 4u * (uint32_t)N;
+    __amdgpu_buffer_rsrc_t ru[DIM], rg[DIM], rg0[DIM];
+#pragma unroll
+    for (int c = 0; c < DIM; ++c) {
+        ru[c] = make_rsrc(u + c * N, nb);
+        rg[c] = make_rsrc(grad + c * N, nb);
+        rg0[c] = make_rsrc(grad + c * N, accumulate ? nb : 0u);
+    }
     double acc[1] = {0.0};
-    for (long long v = (long long)blockIdx.x * kBlock + threadIdx.x; v < N;
-         v += (long long)gridDim.x * kBlock) {
-        const int x[3] = {(int)(v % nx), (int)((v / nx) % ny),
-                          DIM == 3 ? (int)(v / ((long long)nx * ny)) : 0};
-        const int n[3] = {nx, ny, nz};
-        bool in_r = true;
+    // the items of XCD b % 8 are one contiguous run
+    for (int i = blockIdx.x / 8; i < tq; i += gridDim.x / 8) {
+        const int item = blockIdx.x % 8 * tq + i;
+        if (item >= T) break;
+        const int z0 = item / ncb * zc, z1 = min(nz, z0 + zc);
+        const int col = (item % ncb) * kBlock + threadIdx.x;
+        const bool on = col < sz;
+        const int y = col / nx, x = col - y * nx;
+        const bool xr = on && x <= nx - 2, yr = on && y <= ny - 2, xl = on && x >= 1,
+                   yl = on && y >= 1;
+        const int o0 = on ? 4 * col : kNoElem, oxp = xr ? 4 * (col + 1) : kNoElem,
+                  oyp = yr ? 4 * (col + nx) : kNoElem, oxm = xl ? 4 * (col - 1) : kNoElem,
+                  oym = yl ? 4 * (col - nx) : kNoElem,
+                  oxmyp = xl && yr ? 4 * (col - 1 + nx) : kNoElem,
+                  oxpym = xr && yl ? 4 * (col + 1 - nx) : kNoElem;
+        const auto fetch = [&](int z, TvRow<DIM>& r) {
+            const bool zi = z < z1;
+            const int so = zi ? 4 * z * sz : 0;
+            // the plane above, where there is one
+            const bool up = DIM == 3 && zi && z + 1 < nz;
+            const int so1 = up ? 4 * (z + 1) * sz : 0;
 #pragma unroll
-        for (int a = 0; a < DIM; ++a)
-            if (x[a] > n[a] - 2) in_r = false;
-        float g[3] = {0.f, 0.f, 0.f};
-        float k[3][3];
-        if (in_r) {
-            acc[0] += (double)tv_coef<DIM, KIND>(u, N, st, v, k);
-#pragma unroll
-            for (int c = 0; c < DIM; ++c)
-#pragma unroll
-                for (int a = 0; a < DIM; ++a) g[c] -= k[c][a];
-        }
-#pragma unroll
-        for (int a = 0; a < DIM; ++a) {
-            // the term at y = x - e_a, if y is in X_R
-            bool prev = x[a] >= 1;
-#pragma unroll
-            for (int b = 0; b < DIM; ++b) {
-                const int yb = x[b] - (b == a ? 1 : 0);
-                if (yb > n[b] - 2) prev = false;
+            for (int c = 0; c < DIM; ++c) {
+                r.xp[c] = load1(ru[c], zi ? oxp : kNoElem, so);
+                r.yp[c] = load1(ru[c], zi ? oyp : kNoElem, so);
+                r.xmyp[c] = load1(ru[c], zi ? oxmyp : kNoElem, so);
+                r.xpym[c] = load1(ru[c], zi ? oxpym : kNoElem, so);
+                if (DIM == 3) {
+                    r.u1[c] = load1(ru[c], up ? o0 : kNoElem, so1);
+                    r.xm1[c] = load1(ru[c], up ? oxm : kNoElem, so1);
+                    r.ym1[c] = load1(ru[c], up ? oym : kNoElem, so1);
+                }
+                r.g[c] = load1(rg0[c], zi ? o0 : kNoElem, so);
             }
-            if (!prev) continue;
-            tv_coef<DIM, KIND>(u, N, st, v - st[a], k);
-#pragma unroll
-            for (int c = 0; c < DIM; ++c) g[c] += k[c][a];
-        }
+        };
+        TvRow<DIM> r;
+        fetch(z0, r);
+        float u0[DIM], xm[DIM], ym[DIM], kz[DIM];
+        float D[3][3], k[3][3];
 #pragma unroll
         for (int c = 0; c < DIM; ++c) {
-            const float val = scale * inv_xr * g[c];
-            grad[c * N + v] = accumulate ? grad[c * N + v] + val : val;
+            u0[c] = load1(ru[c], o0, 4 * z0 * sz);
+            xm[c] = load1(ru[c], oxm, 4 * z0 * sz);
+            ym[c] = load1(ru[c], oym, 4 * z0 * sz);
+            kz[c] = 0.f;
+        }
+        if (DIM == 3 && z0 > 0) {   // the term at z0 - 1
+            const int so = 4 * (z0 - 1) * sz;
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) {
+                const float b = load1(ru[c], o0, so);
+                D[c][0] = load1(ru[c], oxp, so) - b;
+                D[c][1] = load1(ru[c], oyp, so) - b;
+                D[c][2] = u0[c] - b;
+            }
+            tv_coef<DIM, KIND>(D, k);
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) kz[c] = xr && yr ? k[c][2] : 0.f;
+        }
+        for (int z = z0; z < z1; ++z) {
+            TvRow<DIM> t = r;
+            fetch(z + 1, r);
+            const bool zr = DIM == 2 || z <= nz - 2;
+            float g[DIM];
+            // the term at x
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) {
+                D[c][0] = t.xp[c] - u0[c];
+                D[c][1] = t.yp[c] - u0[c];
+                if (DIM == 3) D[c][2] = t.u1[c] - u0[c];
+            }
+            const float val = tv_coef<DIM, KIND>(D, k);
+            const bool in_r = xr && yr && zr;
+            acc[0] += in_r ? (double)val : 0.0;
+            float kn[DIM];
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) {
+                g[c] = 0.f;
+#pragma unroll
+                for (int a = 0; a < DIM; ++a) g[c] -= k[c][a];
+                g[c] = in_r ? g[c] : 0.f;
+                kn[c] = in_r && DIM == 3 ? k[c][2] : 0.f;
+            }
+            // at x - e_x
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) {
+                D[c][0] = u0[c] - xm[c];
+                D[c][1] = t.xmyp[c] - xm[c];
+                if (DIM == 3) D[c][2] = t.xm1[c] - xm[c];
+            }
+            tv_coef<DIM, KIND>(D, k);
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) g[c] += xl && yr && zr ? k[c][0] : 0.f;
+            // at x - e_y
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) {
+                D[c][0] = t.xpym[c] - ym[c];
+                D[c][1] = u0[c] - ym[c];
+                if (DIM == 3) D[c][2] = t.ym1[c] - ym[c];
+            }
+            tv_coef<DIM, KIND>(D, k);
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) {
+                g[c] += xr && yl && zr ? k[c][1] : 0.f;
+                g[c] += kz[c];   // at x - e_z
+                const float v = scale * inv_xr * g[c];
+                store1(rg[c], accumulate ? t.g[c] + v : v, o0, 4 * z * sz);
+                if (DIM == 3) {
+                    u0[c] = t.u1[c];
+                    xm[c] = t.xm1[c];
+                    ym[c] = t.ym1[c];
+                    kz[c] = kn[c];
+                }
+            }
         }
     }
     block_sum<kBlock, 1>(acc, red);
@@ -132,22 +235,22 @@ int tv_partials() { return kTvBlocks; }
 hipError_t launch_tv(const PairDesc& P, int dim, int kind, const float* u, float scale,
                      float* grad, bool accumulate_grad, double* partial, float weight,
                      float* value, bool accumulate_value, hipStream_t s) {
-    const int g = tv_grid(P.nvox);
+    const int zc = tv_zc(P), g = min(xcd_grid(tv_items(P, zc), 0), kTvBlocks);
     const int acc = accumulate_grad ? 1 : 0;
     if (dim == 3) {
         if (kind == AIR_REG_ANISO_TV)
-            hipLaunchKernelGGL((k_tv<3, AIR_REG_ANISO_TV>), dim3(g), dim3(kBlock), 0, s, P, u,
-                               scale, grad, acc, partial);
+            hipLaunchKernelGGL((k_tv<3, AIR_REG_ANISO_TV>), dim3(g), dim3(kBlock), 0, s, P, zc,
+                               u, scale, grad, acc, partial);
         else
-            hipLaunchKernelGGL((k_tv<3, AIR_REG_ISO_TV>), dim3(g), dim3(kBlock), 0, s, P, u,
-                               scale, grad, acc, partial);
+            hipLaunchKernelGGL((k_tv<3, AIR_REG_ISO_TV>), dim3(g), dim3(kBlock), 0, s, P, zc,
+                               u, scale, grad, acc, partial);
     } else {
         if (kind == AIR_REG_ANISO_TV)
-            hipLaunchKernelGGL((k_tv<2, AIR_REG_ANISO_TV>), dim3(g), dim3(kBlock), 0, s, P, u,
-                               scale, grad, acc, partial);
+            hipLaunchKernelGGL((k_tv<2, AIR_REG_ANISO_TV>), dim3(g), dim3(kBlock), 0, s, P, zc,
+                               u, scale, grad, acc, partial);
         else
-            hipLaunchKernelGGL((k_tv<2, AIR_REG_ISO_TV>), dim3(g), dim3(kBlock), 0, s, P, u,
-                               scale, grad, acc, partial);
+            hipLaunchKernelGGL((k_tv<2, AIR_REG_ISO_TV>), dim3(g), dim3(kBlock), 0, s, P, zc,
+                               u, scale, grad, acc, partial);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -284,3 +284,19 @@ def test_lcc_sampling_far_outside(n):
     F, M = inputs(n, 19, 6)
     th = np.random.default_rng(20).uniform(-1.2, 1.2, (d,) + tuple(reversed(n))).astype(np.float32)
     check(p, F, M, th, f"lcc outside {n}")
+
+
+# total variation: walks of 1, 2, 4 and 8 planes with their remainders, columns
+# that end inside a block, the thinnest volumes
+@pytest.mark.parametrize("n", [(2, 2, 2), (33, 9, 5), (128, 70, 33), (130, 127, 31),
+                               (129, 128, 57), (200, 180, 41), (300, 2), (65, 70)])
+@pytest.mark.parametrize("reg", [api.REG_ANISO_TV, api.REG_ISO_TV])
+def test_tv_walks(n, reg):
+    d = len(n)
+    p = api.Problem(n=n, transform=api.TF_DENSE, spacing=(1,) * d, similarity=api.SIM_MSE,
+                    lambda_diff=0.3, regulariser=reg)
+    F, M = inputs(n, 21)
+    th = np.random.default_rng(22).normal(0.0, 1.0, (d,) + tuple(reversed(n)))
+    for a in range(d):
+        th[a] *= 2.0 / (n[a] - 1)
+    check(p, F, M, th.astype(np.float32), f"tv walk {n} reg={reg}")
