@@ -170,11 +170,18 @@ __host__ __device__ inline int xcd_grid(int T, int R) {
 // move the interpolation weights by up to half an ulp of the point (4e-6
 // voxel at x ~ 100), while d carries an error below half an ulp of the
 // displacement itself. The cell and the mask are decided on x + d + e.
+// mul_rounded keeps the product from being contracted into a later addition:
+// d - floor(d) would otherwise become the fraction of the unrounded product in
+// some kernels and not in others.
+__device__ inline float mul_rounded(float u, float s) {
+#pragma clang fp contract(off)
+    return u * s;
+}
 struct Disp {
     float d, e;
 };
 __device__ inline Disp disp_of(float u, float s) {
-    const float d = u * s;
+    const float d = mul_rounded(u, s);
     return {d, fmaf(u, s, -d)};
 }
 // The cell [t, t + 1] holding the exact point x + d + e along one axis of n

@@ -310,7 +310,10 @@ struct Far {
 // path or more) took 247-262 us per squaring at 256^3, the ring 120-135 us;
 // reading and writing the field once is 80 us. The first squaring does not
 // know its reach: it takes the ring and gathers the samples that leave it.
-// Both ways the same operations in the same order.
+// Both ways the fraction of the rounded displacement (mul_rounded) and the
+// same operations in the same order, so a sample has the same bits whichever
+// way it is read, and the adjoint (either form) finds the cell that the
+// squaring interpolated in.
 template <int DIM>
 __global__ void __launch_bounds__(kBlock)
 k_compose(const PairDesc P, const float* __restrict__ u, float us, float* __restrict__ out,
@@ -332,7 +335,7 @@ k_compose(const PairDesc P, const float* __restrict__ u, float us, float* __rest
         Disp q[3];
         int j[3];
 #pragma unroll
-        for (int a = 0; a < DIM; ++a) q[a] = Disp{w[a] * P.s[a], 0.f};
+        for (int a = 0; a < DIM; ++a) q[a] = Disp{mul_rounded(w[a], P.s[a]), 0.f};
         field_sample<DIM, false>(u, us, N, P, idx, q, val, nullptr, j, f);
     };
     auto store = [&](int v, const float* w, const float* val) {
@@ -402,7 +405,7 @@ k_compose(const PairDesc P, const float* __restrict__ u, float us, float* __rest
 #pragma unroll
         for (int a = 0; a < DIM; ++a) {
             w[a] = tp[a * PL];
-            const float d = w[a] * P.s[a];
+            const float d = mul_rounded(w[a], P.s[a]);
             const float ad = fabsf(d);
             mi = max_or_nan(mi, ad);
             near = near && ad < 1.f;
@@ -490,7 +493,8 @@ __global__ void k_zero_u32(unsigned int* p, int n) {
 // s_a sum_c gout_c(q) du_c/dp_a at p(q) + sum over sources x of
 // w_q(p(x)) gout(x)), the field being us * u (us, gs powers of two). With
 // |d| < 1 the sources of a target are its 3^d neighbours x = q - t, with the
-// weight prod_a h_t(d_a), h_0 = 1 - |d|, h_+-1 = max(+-d, 0): a gather in
+// weight prod_a h_t(d_a), h_0 = 1 - |d|, h_+-1 = max(+-d, 0) (the squaring's
+// 1 - f and f; for d < 0, f = 1 - |d| is rounded, and h_-1 = 1 - f): a gather in
 // registers instead of the scan's LDS atomics, and the sample points' corners
 // are among the same neighbours, so u and gout pass through the ring (Near)
 // once. A source plane adds to the three targets it touches (rotating
@@ -530,7 +534,6 @@ k_compose_adj_near(const PairDesc P, const float* __restrict__ u, float us,
         rg[c] = make_rsrc(gout + c * N, (uint32_t)(N * 4));
     }
     // transposed sums of target l - 1 (without plane l), of l, and of l + 1
-    // (without the factor s of the last axis)
     float done[DIM], acc[2][DIM];
 #pragma unroll
     for (int c = 0; c < DIM; ++c) done[c] = acc[0][c] = acc[1][c] = 0.f;
@@ -549,6 +552,10 @@ k_compose_adj_near(const PairDesc P, const float* __restrict__ u, float us,
         if (l < l1) fetch(l + 1);
         // source plane l
         const float* sp = sl + own;
+        auto hat = [](float d, int t) {   // h_t(d)
+            const float h0 = 1.f - fabsf(d);
+            return t == 0 ? h0 : t > 0 ? fmaxf(d, 0.f) : d < 0.f ? 1.f - h0 : 0.f;
+        };
         float below[DIM];   // plane l's part of target l - 1
 #pragma unroll
         for (int c = 0; c < DIM; ++c) below[c] = 0.f;
@@ -557,18 +564,12 @@ k_compose_adj_near(const PairDesc P, const float* __restrict__ u, float us,
 #pragma unroll
             for (int ox = -1; ox <= 1; ++ox) {
                 const float* q = sp + oy * HX + ox;   // the target is at (-ox, -oy) from it
-                // h_t(u s) without the factor s of h_+-1
-                auto hat = [](float v, float s, int t) {
-                    return t == 0 ? fmaf(-fabsf(v), s, 1.f) : fmaxf(t > 0 ? v : -v, 0.f);
-                };
-                float w = hat(q[0], P.s[0], -ox);
-                if (DIM == 3) w *= hat(q[PL], P.s[1], -oy);
-                const float fac = (ox != 0 ? P.s[0] : 1.f) * (oy != 0 ? P.s[1] : 1.f);
-                if (ox != 0 || oy != 0) w *= fac;
-                // the factor of the last axis' h_+-1 is applied with the sum
-                const float ul = q[LA * PL];
-                const float wm = fmaxf(-ul, 0.f), wp = fmaxf(ul, 0.f);
-                const float w0 = fmaf(-fabsf(ul), P.s[LA], 1.f);
+                float d[DIM];
+#pragma unroll
+                for (int a = 0; a < DIM; ++a) d[a] = mul_rounded(q[a * PL], P.s[a]);
+                float w = hat(d[0], -ox);
+                if (DIM == 3) w *= hat(d[1], -oy);
+                const float wm = hat(d[LA], -1), w0 = hat(d[LA], 0), wp = hat(d[LA], 1);
 #pragma unroll
                 for (int c = 0; c < DIM; ++c) {
                     const float g = w * q[(DIM + c) * PL];
@@ -585,14 +586,11 @@ k_compose_adj_near(const PairDesc P, const float* __restrict__ u, float us,
             int o[DIM];   // cell relative to the voxel, -1 or 0
 #pragma unroll
             for (int a = 0; a < DIM; ++a) {
-                const Disp q = disp_of(tp[a * PL], P.s[a]);
-                const float fl = floorf(q.d);
-                f[a] = q.d - fl;
+                // (|d| < 1: an integer d is 0, exactly, so it has no left cell)
+                const float d = mul_rounded(tp[a * PL], P.s[a]);
+                const float fl = floorf(d);
+                f[a] = d - fl;
                 o[a] = (int)fl;
-                if (f[a] == 0.f && q.e < 0.f) {
-                    o[a] -= 1;
-                    f[a] = 1.f;
-                }
             }
             const int inpl = own + o[0] + (DIM == 3 ? o[1] * HX : 0);
             const float* b0 = ring + ((t + o[LA]) & 3) * SL + inpl;
@@ -627,8 +625,7 @@ k_compose_adj_near(const PairDesc P, const float* __restrict__ u, float us,
             const int v = t * B.plane + (DIM == 3 ? B.y * P.n[0] : 0) + B.x;
 #pragma unroll
             for (int a = 0; a < DIM; ++a) {
-                const float gv = go[a] + P.s[a] * ts[a] +
-                                 fmaf(P.s[LA], below[a], done[a]) + poison;
+                const float gv = go[a] + P.s[a] * ts[a] + (done[a] + below[a] + poison);
                 gin[a * N + v] = gs * gv;
                 gmo = max_or_nan(gmo, fabsf(gv));
             }
@@ -636,7 +633,7 @@ k_compose_adj_near(const PairDesc P, const float* __restrict__ u, float us,
 #pragma unroll
         for (int c = 0; c < DIM; ++c) {
             done[c] = acc[0][c];
-            acc[0][c] = P.s[LA] * acc[1][c];
+            acc[0][c] = acc[1][c];
             acc[1][c] = 0.f;
         }
     }
@@ -709,7 +706,7 @@ k_compose_adj_tile(const PairDesc P, const float* __restrict__ u, float us,
         for (int a = 0; a < DIM; ++a) {
             // the transposed weights (1 - f, f) of the cell below an integer
             // point equal those of the cell above it, so e is not needed here
-            const float d0 = uv[a] * P.s[a];
+            const float d0 = mul_rounded(uv[a], P.s[a]);
             if (!(d0 == d0) || d0 == INFINITY || d0 == -INFINITY) finite = false;
             const float d = fminf(fmaxf(d0, -1e9f), 1e9f);
             const float fl = floorf(d);
