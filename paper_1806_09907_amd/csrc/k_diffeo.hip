@@ -498,8 +498,11 @@ __global__ void k_zero_u32(unsigned int* p, int n) {
 // registers instead of the scan's LDS atomics, and the sample points' corners
 // are among the same neighbours, so u and gout pass through the ring (Near)
 // once. A source plane adds to the three targets it touches (rotating
-// accumulators). Fixed order of summation: bitwise repeatable. Bound by VALU
-// issue (~300 per voxel); 193 us at 256^3, where the scan took 508-512. gmax_bits: max |gout|; a non-finite one makes gin NaN.
+// accumulators). The transposed sums are kept in 64 bits, like the scan's, and
+// rounded once; their order is fixed, so the result is bitwise repeatable.
+// Bound by VALU issue (~430 per voxel, a third of it FP64); 244 us at 256^3
+// (193 with 32-bit sums), where the scan took 508-512. gmax_bits: max |gout|;
+// a non-finite one makes gin NaN.
 template <int DIM>
 __global__ void __launch_bounds__(kBlock)
 k_compose_adj_near(const PairDesc P, const float* __restrict__ u, float us,
@@ -534,9 +537,9 @@ k_compose_adj_near(const PairDesc P, const float* __restrict__ u, float us,
         rg[c] = make_rsrc(gout + c * N, (uint32_t)(N * 4));
     }
     // transposed sums of target l - 1 (without plane l), of l, and of l + 1
-    float done[DIM], acc[2][DIM];
+    double done[DIM], acc[2][DIM];
 #pragma unroll
-    for (int c = 0; c < DIM; ++c) done[c] = acc[0][c] = acc[1][c] = 0.f;
+    for (int c = 0; c < DIM; ++c) done[c] = acc[0][c] = acc[1][c] = 0.0;
     float gmo = 0.f;
     fetch(l0 - 1);
     for (int l = l0 - 1; l <= l1; ++l) {
@@ -556,9 +559,9 @@ k_compose_adj_near(const PairDesc P, const float* __restrict__ u, float us,
             const float h0 = 1.f - fabsf(d);
             return t == 0 ? h0 : t > 0 ? fmaxf(d, 0.f) : d < 0.f ? 1.f - h0 : 0.f;
         };
-        float below[DIM];   // plane l's part of target l - 1
+        double below[DIM];   // plane l's part of target l - 1
 #pragma unroll
-        for (int c = 0; c < DIM; ++c) below[c] = 0.f;
+        for (int c = 0; c < DIM; ++c) below[c] = 0.0;
 #pragma unroll
         for (int oy = (DIM == 3 ? -1 : 0); oy <= (DIM == 3 ? 1 : 0); ++oy)
 #pragma unroll
@@ -569,13 +572,14 @@ k_compose_adj_near(const PairDesc P, const float* __restrict__ u, float us,
                 for (int a = 0; a < DIM; ++a) d[a] = mul_rounded(q[a * PL], P.s[a]);
                 float w = hat(d[0], -ox);
                 if (DIM == 3) w *= hat(d[1], -oy);
-                const float wm = hat(d[LA], -1), w0 = hat(d[LA], 0), wp = hat(d[LA], 1);
+                const double wm = w * hat(d[LA], -1), w0 = w * hat(d[LA], 0),
+                             wp = w * hat(d[LA], 1);
 #pragma unroll
                 for (int c = 0; c < DIM; ++c) {
-                    const float g = w * q[(DIM + c) * PL];
-                    below[c] = fmaf(wm, g, below[c]);
-                    acc[0][c] = fmaf(w0, g, acc[0][c]);
-                    acc[1][c] = fmaf(wp, g, acc[1][c]);
+                    const double g = q[(DIM + c) * PL];
+                    below[c] = fma(wm, g, below[c]);
+                    acc[0][c] = fma(w0, g, acc[0][c]);
+                    acc[1][c] = fma(wp, g, acc[1][c]);
                 }
             }
         // target l - 1: planes l - 2, l - 1, l are in the ring
@@ -625,7 +629,8 @@ k_compose_adj_near(const PairDesc P, const float* __restrict__ u, float us,
             const int v = t * B.plane + (DIM == 3 ? B.y * P.n[0] : 0) + B.x;
 #pragma unroll
             for (int a = 0; a < DIM; ++a) {
-                const float gv = go[a] + P.s[a] * ts[a] + (done[a] + below[a] + poison);
+                const float tr = (float)(done[a] + below[a]) + poison;
+                const float gv = go[a] + P.s[a] * ts[a] + tr;
                 gin[a * N + v] = gs * gv;
                 gmo = max_or_nan(gmo, fabsf(gv));
             }
@@ -634,7 +639,7 @@ k_compose_adj_near(const PairDesc P, const float* __restrict__ u, float us,
         for (int c = 0; c < DIM; ++c) {
             done[c] = acc[0][c];
             acc[0][c] = acc[1][c];
-            acc[1][c] = 0.f;
+            acc[1][c] = 0.0;
         }
     }
     block_max_to(gmo, redm, gmax_out);

@@ -41,3 +41,52 @@ def test_squaring_from_lds_and_from_memory_bitwise(n):
     far_u[corner] = 0.0
     bad = (near_u != far_u).sum().item()
     assert bad == 0, f"{bad} of {near_u.numel()} differ"
+
+
+# The adjoint of a squaring that moves less than one voxel sums a voxel's
+# transposed terms in 64 bits. A constant displacement of eighths has exact
+# weights, and the image gradient is zero at every second voxel, where the
+# result is the transposed sum alone: rounded once, it lies within 2^-24 of its
+# own size, also where its terms cancel (2^-23 asserted; 32-bit sums are off by
+# 2^-24 of the largest term).
+@pytest.mark.parametrize("n", [(65, 33, 17), (129, 65)])
+def test_transposed_sums_in_64_bits(n):
+    d = len(n)
+    shape = tuple(reversed(n))
+    disp = (3 / 8, -1 / 4, 1 / 8)[:d]
+    th = np.zeros((d,) + shape)
+    for a in range(d):
+        th[a] = 2 * disp[a] * 2.0 / (n[a] - 1)     # u_0 = theta / 2; exact: n - 1 is a power of 2
+    x = np.broadcast_to(np.arange(n[0], dtype=np.float64), shape)
+    F = x + np.random.default_rng(3).normal(0.0, 8.0, shape)
+    even = (np.arange(n[0]) % 2) == 0
+    F[..., even] = (x + 2 * disp[0])[..., even]    # the warped image there, exactly
+    one = api.Problem(n=n, transform=api.TF_DENSE, spacing=(1,) * d, similarity=api.SIM_MSE,
+                      lambda_diff=0.0, diffeo_steps=1)
+    zero = api.Problem(n=n, transform=api.TF_DENSE, spacing=(1,) * d, similarity=api.SIM_MSE,
+                       lambda_diff=0.0, diffeo_steps=0)
+    print(f"case transposed sums {n}", flush=True)
+    p1 = api.Plan(one)
+    u1 = api.displacement(p1, gpu(th))
+    _, g1 = api.objective_and_grad(p1, gpu(F), gpu(x), gpu(th))
+    _, g0 = api.objective_and_grad(api.Plan(zero), gpu(F), gpu(x), u1)
+    g = g0[0].double().cpu().numpy()               # dL/du_1 along x
+    want = np.zeros(shape)
+    for c in range(2 ** d):
+        w, moved = 1.0, g
+        for a in range(d):
+            fl = np.floor(disp[a])
+            f = disp[a] - fl
+            bit = (c >> a) & 1
+            w *= f if bit else 1.0 - f
+            moved = np.roll(moved, int(fl) + bit, axis=d - 1 - a)
+        want += w * moved
+    inner = (slice(3, -3),) * d
+    got = 2.0 * g1[0].double().cpu().numpy()       # dL/du_0 = 2 dL/dtheta
+    at = np.zeros(shape, bool)
+    at[..., even] = True
+    at, got, want, g = at[inner], got[inner], want[inner], g[inner]
+    assert np.all(g[at] == 0.0) and np.all(want[at] != 0.0)
+    err = np.max(np.abs(got[at] - want[at]) / np.abs(want[at]))
+    print(f"largest relative error {err:.2e}", flush=True)
+    assert err <= 2.0 ** -23
