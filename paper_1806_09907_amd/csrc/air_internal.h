@@ -30,6 +30,12 @@ struct TraceRange {
 
 constexpr int kMaxPairs = 4096;
 constexpr int kMaxSpacing = 64;
+// Voxels of a pair: byte offsets of its FP32 images and field components fit
+// in an int. kNoElem is a (dword aligned) byte offset past every such buffer:
+// a buffer load there gives 0, a buffer store is dropped.
+constexpr long long kMaxVoxels = (1LL << 29) - 1;
+constexpr int kNoElem = 0x7ffffffc;
+static_assert(kNoElem % 4 == 0 && kNoElem >= 4 * kMaxVoxels, "kNoElem lies past every buffer");
 constexpr int kBlock = 256;          // threads per block of every kernel
 constexpr int kStatWords = 8;        // doubles per tile statistics slot
 // dense-field passes: a block owns kDenseTX x kDenseTY voxels of (x, y) and

@@ -31,8 +31,6 @@ __device__ inline v2f load2(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
     return __builtin_bit_cast(v2f, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
 }
 
-// Byte offset past every volume (4 nvox < 2^31): loads give 0, stores are dropped.
-constexpr int kNoElem = 0x7ffffff0;
 __device__ inline uint8_t load1u8(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
     return __builtin_amdgcn_raw_buffer_load_b8(r, voff, soff, 0);
 }

@@ -518,7 +518,7 @@ k_conv_fwd_lin(const u16* __restrict__ X, ConvDims D, const u16* __restrict__ Wt
         const_cast<u16*>(Wt), (short)0, D.cout * D.K * 2, 0x00020000);
     auto weights = [&](int st, bf16x8* b) {
         const int k = 32 * st + 8 * g;
-        const int vo = k < D.K ? (r * D.K + k) * 2 : 0x7ffffff0;
+        const int vo = k < D.K ? (r * D.K + k) * 2 : kNoElem;
 #pragma unroll
         for (int j = 0; j < NT16; ++j)
             b[j] = __builtin_bit_cast(

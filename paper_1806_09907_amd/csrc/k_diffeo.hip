@@ -246,7 +246,7 @@ struct Near {
             const int cx = i % HX, cy = i / HX;
             const int gx = x0 - 1 + cx, gy = DIM == 3 ? y0 - 1 + cy : 0;
             const bool ok = i < PL && gx >= 0 && gx < nx && gy >= 0 && (DIM == 2 || gy < ny);
-            eo[e] = ok ? (gy * nx + gx) * 4 : 0x7ffffff0;
+            eo[e] = ok ? (gy * nx + gx) * 4 : kNoElem;
         }
         return true;
     }

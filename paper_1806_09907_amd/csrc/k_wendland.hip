@@ -351,7 +351,7 @@ k_cell_expand4(const PairDesc P, const float* __restrict__ W, const float* __res
 #pragma unroll
     for (int c = 0; c < 3; ++c) rT[c] = make_rsrc(theta + c * NC, (uint32_t)(NC * 4));
     const int jx = cx0 + i16 + k4;
-    const int vo = jx < P.nc[0] ? jx * 4 : 0x7ffffff0;
+    const int vo = jx < P.nc[0] ? jx * 4 : kNoElem;
     const float* Wr = W + k4 * Ppad + pc * 64 + i16;
     float a[16][4], b[16][3];
 #pragma unroll
@@ -360,7 +360,7 @@ k_cell_expand4(const PairDesc P, const float* __restrict__ W, const float* __res
         const bool in = jz < P.nc[2] && jy < P.nc[1];   // uniform
         const int so = in ? (jz * P.nc[1] + jy) * P.nc[0] * 4 : 0;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) b[st][c] = load1(rT[c], in ? vo : 0x7ffffff0, so);
+        for (int c = 0; c < 3; ++c) b[st][c] = load1(rT[c], in ? vo : kNoElem, so);
 #pragma unroll
         for (int m = 0; m < 4; ++m) a[st][m] = Wr[st * 4 * Ppad + m * 16];
     }
@@ -461,7 +461,7 @@ k_cell_t4(const PairDesc P, const float* __restrict__ WT, const float* __restric
                 const Idx3 rc = idx3(r0, P.sp[0], P.sp[1]);
                 const int x = x0 + rc.x, y = y0 + rc.y, z = z0 + rc.z;
                 const bool ok = r0 < P3 && x < nx && y < ny && z < nz;
-                const int vo = ok ? ((z * ny + y) * nx + x) * 4 : 0x7ffffff0;
+                const int vo = ok ? ((z * ny + y) * nx + x) * 4 : kNoElem;
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
                     v4f v = __builtin_bit_cast(
@@ -477,7 +477,7 @@ k_cell_t4(const PairDesc P, const float* __restrict__ WT, const float* __restric
                     const Idx3 rc = idx3(r0 + e, P.sp[0], P.sp[1]);
                     const int x = x0 + rc.x, y = y0 + rc.y, z = z0 + rc.z;
                     const bool ok = r0 + e < P3 && x < nx && y < ny && z < nz;
-                    const int vo = ok ? ((z * ny + y) * nx + x) * 4 : 0x7ffffff0;
+                    const int vo = ok ? ((z * ny + y) * nx + x) * 4 : kNoElem;
 #pragma unroll
                     for (int c = 0; c < 3; ++c) b[q][c][e] = load1(rg[c], vo, 0);
                 }
@@ -582,7 +582,7 @@ k_cell_gather4(const PairDesc P, const float* __restrict__ Hx, float scale, int 
 // not fit in the workspace of H).
 __host__ inline bool cells4(const PairDesc& P, int dim) {
     return dim == 3 && P.wK[0] == 4 && P.wK[1] == 4 && P.wK[2] == 4 && P.wncell[0] >= 3 &&
-           (long long)P.nc[0] * P.nc[1] * P.nc[2] < (1LL << 29);
+           (long long)P.nc[0] * P.nc[1] * P.nc[2] <= kMaxVoxels;
 }
 
 __host__ inline int wend_grid(long long n) {

@@ -282,3 +282,23 @@ def test_debug_bounds_entry_in_the_release_build():
     assert L.air_debug_bounds_take(C.byref(f)) == 5      # AIR_ERR_UNSUPPORTED
     assert f.value == 0
     assert L.air_debug_bounds_take(None) == 1            # AIR_ERR_INVALID_ARG
+
+
+def test_out_of_range_offset_lies_past_the_largest_volume():
+    """Masked lanes address their buffers at kNoElem: it has to lie past 4 N
+    bytes for every accepted N, and no kernel may use an offset of its own."""
+    csrc = os.path.join(ROOT, "paper_1806_09907_amd", "csrc")
+    text = {f: open(os.path.join(csrc, f)).read() for f in sorted(os.listdir(csrc))
+            if f.endswith((".hip", ".h"))}
+    values = [int(v, 16) for t in text.values()
+              for v in re.findall(r"\bkNoElem\s*=\s*(0x[0-9a-fA-F]+)", t)]
+    assert len(values) == 1
+    for n in [(233, 1103, 2089), (870, 4859, 127)]:          # 2^29 - 1, 2^29 - 2 voxels
+        Plan(Problem(n=n, transform=TF_DENSE, spacing=(1, 1, 1)))
+        assert values[0] >= 4 * n[0] * n[1] * n[2]
+    with pytest.raises(_lib.AirError):
+        Plan(Problem(n=(512, 1024, 1024), transform=TF_DENSE, spacing=(1, 1, 1)))
+    for f, t in text.items():
+        other = [v for v in re.findall(r"0x7f[0-9a-fA-F]{6}\b", t)
+                 if int(v, 16) not in (0x7fffffff, 0x7fc00000, values[0])]
+        assert not other, (f, other)

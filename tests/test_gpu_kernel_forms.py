@@ -90,3 +90,36 @@ def test_transposed_sums_in_64_bits(n):
     err = np.max(np.abs(got[at] - want[at]) / np.abs(want[at]))
     print(f"largest relative error {err:.2e}", flush=True)
     assert err <= 2.0 ** -23
+
+
+# The largest volumes but one: the lanes of a last, partial block of columns
+# address their buffers past 4 N bytes, so nothing but its owner writes the
+# last voxels. Constant images: the gradient is the total variation's, a sum of
+# signs, and exact up to the rounding of its factor.
+def test_largest_volume_last_voxels():
+    n = (870, 4859, 127)                                     # 2^29 - 2 voxels
+    lam = 0.5
+    plan = api.Plan(api.Problem(n=n, transform=api.TF_DENSE, spacing=(1, 1, 1),
+                                similarity=api.SIM_MSE, lambda_diff=lam,
+                                regulariser=api.REG_ANISO_TV))
+    print(f"case largest volume {n}", flush=True)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(5)
+    F = torch.zeros(tuple(reversed(n)), device=DEV)
+    th = torch.empty((3,) + tuple(reversed(n)), device=DEV)
+    th.normal_(0.0, 1e-4, generator=gen)
+    _, g = api.objective_and_grad(plan, F, F, th)
+    u = th[:, -3:].double()                                  # the last three planes
+    want = torch.zeros_like(u)
+    inner = (slice(None),) + (slice(0, -1),) * 3             # the term's points
+    for a in range(3):
+        ahead = [slice(None)] + [slice(0, -1)] * 3
+        ahead[1 + a] = slice(1, None)
+        k = torch.sign(u[tuple(ahead)] - u[inner])
+        want[tuple(ahead)] += k
+        want[inner] -= k
+    want *= lam / ((n[0] - 1) * (n[1] - 1) * (n[2] - 1))
+    got = g[:, -2:].double()
+    err = (got - want[:, -2:]).abs().max().item() / want.abs().max().item()
+    print(f"largest error {err:.2e}", flush=True)
+    assert err <= 1e-6
