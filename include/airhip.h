@@ -184,7 +184,11 @@ air_status air_regulariser(const air_plan* plan, int32_t pair, const float* thet
                            void* stream);
 
 /* Stages 1-5 (Sec. II-A eq. objective): value = S + lambda R and
- * grad = dL/dtheta, for a plan with exactly one pair. */
+ * grad = dL/dtheta, for a plan with exactly one pair. A B-spline plan's
+ * images may be non-finite where they do not count (the fixed image where the
+ * sample point lies outside the volume, the moving one where no point inside
+ * reads it); 3D plans of one similarity pass with spacing 8 on every axis
+ * need finite images. */
 air_status air_objective_and_grad(const air_plan* plan, const float* fixed,
                                   const float* moving, const float* theta,
                                   float* value, float* grad, void* ws, size_t ws_bytes,

@@ -25,6 +25,10 @@
 
 namespace air {
 
+// The shift of the NCC moments: any finite value serves, and the voxel it is
+// taken from may be outside the mask.
+__device__ inline float finite_or_0(float v) { return isfinite(v) ? v : 0.f; }
+
 // --------------------------------------------------------------- regulariser
 // dR/dtheta_c = (2/|X_R|) sum_a K_a theta_c with K_a the Kronecker product of
 // per-axis banded Gram matrices: D (differences) on axis a, P on the others.
@@ -263,8 +267,8 @@ k_fused3(const LaunchCtx C) {
         const int xs = min(x0 + TX / 2, nx - 1), ys = min(y0 + TY / 2, ny - 1);
         const int zs = min((cz_b * sz + min(cz_e * sz, nz)) / 2, nz - 1);
         const long long vs = ((long long)zs * ny + ys) * nx + xs;
-        shF = F[vs];
-        shW = M[vs];
+        shF = finite_or_0(F[vs]);
+        shW = finite_or_0(M[vs]);
     }
     __syncthreads();
 
@@ -661,8 +665,8 @@ k_fused3_tile(const LaunchCtx C) {
         const int xs = min(x0 + TX / 2, nx - 1), ys = min(y0 + TY / 2, ny - 1);
         const int zs = min((cz_b * sz + min(cz_e * sz, nz)) / 2, nz - 1);
         const long long vs = ((long long)zs * ny + ys) * nx + xs;
-        shF = F[vs];
-        shW = M[vs];
+        shF = kAny ? finite_or_0(F[vs]) : F[vs];
+        shW = kAny ? finite_or_0(M[vs]) : M[vs];
     }
     __syncthreads();
 
@@ -827,8 +831,8 @@ k_fused3_tile(const LaunchCtx C) {
     auto prep = [&](int r, float dv, auto ph) -> Prep {
         constexpr int PH = decltype(ph)::value;
         // Branch-free: the cell is clamped into the volume so every load is
-        // in range; m = 1 inside the mask, 0 outside (or for lanes / layers
-        // past the volume) scales every contribution.
+        // in range; m = 1 (SP = 0: all bits set) inside the mask, 0 outside
+        // (or for lanes / layers past the volume) decides what contributes.
         const int z = cz * sz + r;
         Prep q;
         // F through its buffer descriptor: the lane's offset is fixed, the
@@ -880,7 +884,7 @@ k_fused3_tile(const LaunchCtx C) {
         const bool in = (int)(__float_as_uint(q.fx) <= kOne) &
                         (int)(__float_as_uint(q.fy) <= kOne) &
                         (int)(__float_as_uint(q.fz) <= kOne) & (int)act & (int)(z < nz);
-        q.m = in ? 1.f : 0.f;
+        q.m = in ? (kAny ? __uint_as_float(~0u) : 1.f) : 0.f;
         // byte offset of the cell's first corner: the row step clz ny + cly
         // is an exact float (|.| < 2^24), the rest 24-bit integer arithmetic
         const int rows = (int)fmaf(clz, nyf, cly);
@@ -917,12 +921,23 @@ k_fused3_tile(const LaunchCtx C) {
         const float h0 = dz00 + fy * (dz10 - dz00);
         const float h1 = dz01 + fy * (dz11 - dz01);
         float d[3];
-        d[0] = m * (q.ex ? -W : g1 - g0);
-        d[1] = m * (q.ey ? -W : dy0 + fx * (dy1 - dy0));
-        d[2] = m * (q.ez ? -W : h0 + fx * (h1 - h0));
-        cnt += m;
+        // outside the mask everything is 0. SP = 0 selects, so that what lies
+        // there may be non-finite, as in k_fused3: a fixed image's NaN, a
+        // moving one's in a clamped corner, an extrapolation that overflows
+        // (by the bits of m, all ones or zero: a compare and select per value
+        // cost 2 %). SP = 8 multiplies, which has always spread those.
+        auto masked = [&](float v) -> float {
+            if constexpr (kAny)
+                return __uint_as_float(__float_as_uint(v) & __float_as_uint(m));
+            else
+                return m * v;
+        };
+        d[0] = masked(q.ex ? -W : g1 - g0);
+        d[1] = masked(q.ey ? -W : dy0 + fx * (dy1 - dy0));
+        d[2] = masked(q.ez ? -W : h0 + fx * (h1 - h0));
+        cnt += masked(1.f);
         if (SIM == AIR_SIM_NCC) {
-            const float dF = m * (Fv - shF), dW = m * (W - shW);
+            const float dF = masked(Fv - shF), dW = masked(W - shW);
             m1 += dF;
             m2 += dW;
             m3 += dF * dF;
@@ -935,10 +950,10 @@ k_fused3_tile(const LaunchCtx C) {
                 tap(acc[NF - 1][c], d[c]);
             }
         } else {
-            const float e = m * (W - Fv);
+            const float e = masked(W - Fv);
             m1 += e * e;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) tap(acc[0][c], (W - Fv) * d[c]);
+            for (int c = 0; c < 3; ++c) tap(acc[0][c], (kAny ? e : W - Fv) * d[c]);
         }
     };
     Prep A = prep(0, dep(), I0{});

@@ -4,7 +4,9 @@ import numpy as np
 import pytest
 import torch
 
-from paper_1806_09907_amd import api
+import oracle as O
+from paper_1806_09907_amd import api, synth
+from parity import VAL_TOL, check_grad
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -123,3 +125,77 @@ def test_largest_volume_last_voxels():
     err = (got - want[:, -2:]).abs().max().item() / want.abs().max().item()
     print(f"largest error {err:.2e}", flush=True)
     assert err <= 1e-6
+
+
+def inputs(n, seed):
+    rng = np.random.default_rng(seed)
+    shape = tuple(reversed(n))
+    F = synth.blobs(shape, 10, rng) + rng.normal(0, 0.01, shape)
+    M = synth.blobs(shape, 10, rng) + rng.normal(0, 0.01, shape)
+    return F.astype(np.float32), (0.5 * M + 0.5 * F).astype(np.float32)
+
+
+def unused_voxels(n, u):
+    """Masks of the voxels whose sample point lies outside the volume and of
+    the moving image's voxels that no point inside reads; points within 1e-3
+    voxel of a decision count as inside, and as reading both cells."""
+    d = len(n)
+    out = np.zeros(tuple(reversed(n)), bool)
+    pts = []
+    for a in range(d):
+        x = np.arange(n[a], dtype=np.float64).reshape((-1,) + (1,) * a)
+        with np.errstate(invalid="ignore"):
+            p = x + u[a].astype(np.float64) * (n[a] - 1) / 2
+            out |= ~((p >= -1e-3) & (p <= n[a] - 1 + 1e-3))
+        pts.append(p)
+    read = np.zeros(tuple(reversed(n)), bool)
+    inside = [p[~out] for p in pts]
+    for c in range(4 ** d):                   # floor(p - 1e-3), floor(p + 1e-3), and the next ones
+        idx = []
+        for a in range(d):
+            k = (c >> (2 * a)) & 3
+            j = np.floor(inside[a] + (1e-3 if k & 1 else -1e-3)).astype(np.int64) + (k >> 1)
+            idx.append(np.clip(j, 0, n[a] - 1))
+        read[tuple(reversed(idx))] = True
+    return out, ~read
+
+
+# What lies outside the mask does not count, whatever it holds: NaN and
+# infinities in the fixed image there and in the moving image where no sample
+# inside reads, and displacements so large that the sample overflows. 16 x 16
+# and other tiles, odd and even cells, and a grid too fine for the pipelined
+# kernel.
+@pytest.mark.parametrize("n,sp,tiling", [((45, 38, 41), (10, 10, 10), None),
+                                         ((45, 38, 41), (5, 5, 5), None),
+                                         ((70, 37, 44), (6, 7, 5), 2), ((70, 37, 44), (6, 7, 5), 3),
+                                         ((40, 36, 33), (20, 16, 33), None),
+                                         ((40, 24, 33), (3, 1, 6), None)])
+@pytest.mark.parametrize("sim", [api.SIM_MSE, api.SIM_NCC])
+def test_non_finite_outside_the_mask_3d(n, sp, tiling, sim):
+    check_non_finite_outside(n, sp, sim, tiling)
+
+
+def check_non_finite_outside(n, sp, sim, tiling=None):
+    d = len(n)
+    kw = dict(n=n, spacing=sp, similarity=sim, lambda_diff=0.0)
+    p = api.Problem(**kw)
+    F, M = inputs(n, 31)
+    th = synth.random_theta(n, sp, 4.0, 32)
+    th[(slice(None),) + (-1,) * d] = 1e25
+    th[(slice(None),) + (-2,) * d] = -1e30
+    print(f"case non-finite outside {n} {sp} sim={sim} tiling={tiling}", flush=True)
+    plan = api.Plan(p) if tiling is None else api.Plan(p, tiling=tiling)
+    u = api.displacement(plan, gpu(th)).cpu().numpy()
+    out, unread = unused_voxels(n, u)
+    assert out.sum() > 50 and unread.sum() > 50
+    vo, go, _ = O.objective_and_grad(O.Problem(**kw), F, M, th)
+    assert np.isfinite(vo) and np.all(np.isfinite(go))
+    rng = np.random.default_rng(33)
+    bad = np.array([np.nan, np.inf, -np.inf], np.float32)
+    Fb, Mb = F.copy(), M.copy()
+    Fb[out] = bad[rng.integers(0, 3, int(out.sum()))]
+    Mb[unread] = bad[rng.integers(0, 3, int(unread.sum()))]
+    v, g = api.objective_and_grad(plan, gpu(Fb), gpu(Mb), gpu(th))
+    assert api.get_flags(plan) == [0]
+    assert abs(float(v) - vo) <= VAL_TOL * abs(vo), (float(v), vo)
+    check_grad(g.double().cpu().numpy(), go, f"non-finite outside {n} {sp}")
