@@ -1128,8 +1128,8 @@ k_fused2(const LaunchCtx C) {
     if (SIM == AIR_SIM_NCC) {
         const int xs = min(x0 + TX / 2, nx - 1);
         const int ys = min((cy_b * sy + min(cy_e * sy, ny)) / 2, ny - 1);
-        shF = F[(long long)ys * nx + xs];
-        shW = M[(long long)ys * nx + xs];
+        shF = finite_or_0(F[(long long)ys * nx + xs]);
+        shW = finite_or_0(M[(long long)ys * nx + xs]);
     }
     __syncthreads();
     float V[2][4];
@@ -1773,7 +1773,8 @@ k_whole2(const LaunchCtx C) {
         mv[i] = M[q];
     }
     const int qc = (ny / 2) * nx + nx / 2;
-    const float shF = SIM == AIR_SIM_NCC ? F[qc] : 0.f, shW = SIM == AIR_SIM_NCC ? M[qc] : 0.f;
+    const float shF = SIM == AIR_SIM_NCC ? finite_or_0(F[qc]) : 0.f;
+    const float shW = SIM == AIR_SIM_NCC ? finite_or_0(M[qc]) : 0.f;
     for (int i = tid; i < 2 * ctl; i += NT) TH[i] = theta[i];
     const int gx = 14 * ncx, gy = 14 * ncy;
     for (int i = tid; i < gx + gy; i += NT)

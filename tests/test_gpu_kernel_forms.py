@@ -199,3 +199,37 @@ def check_non_finite_outside(n, sp, sim, tiling=None):
     assert api.get_flags(plan) == [0]
     assert abs(float(v) - vo) <= VAL_TOL * abs(vo), (float(v), vo)
     check_grad(g.double().cpu().numpy(), go, f"non-finite outside {n} {sp}")
+
+
+# the same in 2D: one block per small pair, and tiles (whose NCC shift may come
+# from a voxel outside the mask too)
+@pytest.mark.parametrize("n,sp,tiles", [((64, 64), (8, 8), False), ((64, 64), (8, 8), True),
+                                        ((41, 50), (4, 5), False), ((41, 50), (4, 5), True),
+                                        ((150, 131), (16, 16), False)])
+@pytest.mark.parametrize("sim", [api.SIM_MSE, api.SIM_NCC])
+def test_non_finite_outside_the_mask_2d(n, sp, tiles, sim):
+    p = api.Problem(n=n, spacing=sp, similarity=sim, lambda_diff=0.0)
+    check_non_finite_outside(n, sp, sim, api.Plan(p).tiling if tiles else None)
+
+
+def test_non_finite_image_centre_outside_the_mask():
+    """The voxel that the one-block kernel takes its NCC shift from lies
+    outside the mask and holds a NaN."""
+    n = (48, 40)
+    kw = dict(n=n, spacing=(8, 8), similarity=api.SIM_NCC, lambda_diff=0.0)
+    F, M = inputs(n, 41)
+    nc = api.Problem(**kw).ncontrol()
+    th = np.zeros((2, nc[1], nc[0]), np.float32)
+    # the middle columns leave the image; no sample lands on a voxel, where the
+    # gradient jumps (a sixth of the displacement is no whole number)
+    th[0, :, 3:6] = 61.3 * 2.0 / (n[0] - 1)
+    plan = api.Plan(api.Problem(**kw))
+    out, _ = unused_voxels(n, api.displacement(plan, gpu(th)).cpu().numpy())
+    c = (n[1] // 2, n[0] // 2)
+    assert out[c] and not out.all()
+    vo, go, _ = O.objective_and_grad(O.Problem(**kw), F, M, th)
+    F[c] = np.nan
+    print("case centre", flush=True)
+    v, g = api.objective_and_grad(plan, gpu(F), gpu(M), gpu(th))
+    assert abs(float(v) - vo) <= VAL_TOL * abs(vo), (float(v), vo)
+    check_grad(g.double().cpu().numpy(), go, "centre")
