@@ -1693,9 +1693,10 @@ k_finalize(const LaunchCtx C) {
 // few dozen single waves, each a chain of dependent loads, and need the
 // finalize as a second launch. Same displacements, cells and mask as
 // k_fused2; NCC's coefficients are known before the transposes, so one field
-// per component is transposed instead of three. Bound by the one CU's VALU
-// issue (about 1000 instructions per thread): 64^2 MSE 16.7 us of kernels ->
-// 9.5.
+// per component is transposed instead of three, in FP64 sums (the tiles' parts
+// of a control are added in FP64 too; 32-bit sums took 0.6 us less). Bound by
+// the one CU's VALU issue (about 1000 instructions per thread): 64^2 MSE per
+// evaluation 16.0 us on tiles, 11.8 here.
 constexpr int kWholeThreads = 1024;
 constexpr size_t kWholeMaxLds = 150 * 1024;
 struct WholeLds {   // float offsets; G (2 npix) shares the space of M and T
@@ -1910,15 +1911,15 @@ k_whole2(const LaunchCtx C) {
         const int row = div_small(o, inx), x = o - row * nx;
         const int c = row >= ncy ? 1 : 0, jy = row - c * ncy;
         const float* g = G + c * np + x;
-        float s = 0.f;
+        double s = 0.0;
 #pragma unroll
         for (int kk = 3; kk >= 0; --kk) {                  // rows in increasing order
             const int y0 = (jy - kk) * sy, y1 = min(y0 + sy, ny);
             if (y0 < 0) continue;
 #pragma unroll 4
-            for (int y = y0; y < y1; ++y) s += WY[(y - y0) * 4 + kk] * g[y * nx];
+            for (int y = y0; y < y1; ++y) s += (double)WY[(y - y0) * 4 + kk] * (double)g[y * nx];
         }
-        T1[o] = s;
+        T1[o] = (float)s;
     }
     __syncthreads();
     // x: four lanes per control, a cell each
@@ -1928,17 +1929,17 @@ k_whole2(const LaunchCtx C) {
         const int kk = o % KT, j = o / KT, row = div_small(j, incx), jx = j - row * ncx;
         const float* g = T1 + row * nx;
         const int x0 = (jx - kk) * sx, x1 = min(x0 + sx, nx);
-        float s = 0.f;
+        double s = 0.0;
         if (x0 >= 0)
 #pragma unroll 4
-            for (int x = x0; x < x1; ++x) s += WX[(x - x0) * 4 + kk] * g[x];
+            for (int x = x0; x < x1; ++x) s += (double)WX[(x - x0) * 4 + kk] * (double)g[x];
         s += __shfl_xor(s, 1, KT);
         s += __shfl_xor(s, 2, KT);
         if (kk == 0) {
             const double a = SIM == AIR_SIM_NCC ? 1.0 : k.alpha;
             const int c = row >= ncy ? 1 : 0;
             const float out =
-                (k.degenerate ? 0.f : (float)(a * (double)s * (double)P.s[c])) + TH[j];
+                (k.degenerate ? 0.f : (float)(a * s * (double)P.s[c])) + TH[j];
             grad[j] = out;
             bad = bad || !isfinite(out);
         }

@@ -233,3 +233,45 @@ def test_non_finite_image_centre_outside_the_mask():
     v, g = api.objective_and_grad(plan, gpu(F), gpu(M), gpu(th))
     assert abs(float(v) - vo) <= VAL_TOL * abs(vo), (float(v), vo)
     check_grad(g.double().cpu().numpy(), go, "centre")
+
+
+# The one-block kernel sums a control's support in 64 bits. No displacement, a
+# ramp for the moving image and differences that are exact in FP32: each pixel's
+# term is known, and a control's value is off by the rounding of its columns'
+# sums (2^-24 of each) and of the result. The rows' terms nearly cancel, so a
+# 32-bit sum is off by 2^-24 of the much larger terms.
+@pytest.mark.parametrize("n,sp", [((64, 64), 8), ((48, 51), 16), ((100, 40), 12)])
+def test_small_2d_sums_in_64_bits(n, sp):
+    shape = tuple(reversed(n))
+    rng = np.random.default_rng(51)
+    x = np.broadcast_to(np.arange(n[0], dtype=np.float64), shape)
+    sign = np.where(np.arange(n[1]) % 2 == 0, 1.0, -1.0)[:, None]
+    r = sign * 2000.0 + rng.integers(-1023, 1024, shape) / 1024.0
+    F = x - r                                        # exact: 23 bits
+    assert np.all(F.astype(np.float32) == F)
+    p = api.Problem(n=n, spacing=(sp, sp), similarity=api.SIM_MSE, lambda_diff=0.0)
+    plan = api.Plan(p)
+    nc = p.ncontrol()
+    print(f"case 64-bit sums {n} {sp}", flush=True)
+    _, g = api.objective_and_grad(plan, gpu(F), gpu(x), gpu(np.zeros((2, nc[1], nc[0]))))
+    got = g[0].double().cpu().numpy()
+
+    def weights(m, c):                               # [c][m], the FP32 weights
+        w = np.zeros((c, m))
+        for v in range(m):
+            t = (v % sp) / sp
+            b = [(1 - t) ** 3 / 6, (3 * t ** 3 - 6 * t * t + 4) / 6,
+                 (-3 * t ** 3 + 3 * t * t + 3 * t + 1) / 6, t ** 3 / 6]
+            w[v // sp:v // sp + 4, v] = np.float32(b)
+        return w
+
+    wx, wy = weights(n[0], nc[0]), weights(n[1], nc[1])
+    dx = np.ones(shape)
+    dx[:, -1] = -(n[0] - 1)                          # right of the last voxel is zero
+    cols = wy @ (r * dx).astype(np.float32).astype(np.float64)   # FP32 terms
+    want = cols @ wx.T
+    scale = 2.0 / (n[0] * n[1]) * (n[0] - 1) / 2
+    bound = scale * (2.0 ** -24 * (np.abs(cols) @ wx.T) + 2.0 ** -23 * np.abs(want))
+    worst = np.max(np.abs(got - scale * want) / bound)
+    print(f"largest error over its bound {worst:.2f}", flush=True)
+    assert worst <= 1.0
