@@ -107,11 +107,29 @@ constexpr int kLongWalk = 48, kLongTiles = 800;
 // the same for 2D B-spline plans (64-lane columns of 16, 8, 4, 2, 1 cells)
 static const int kCfg2Fill[] = {3, 2, 1, 0, 4};
 constexpr int kFillTiles2 = 2048;
-// 2D pairs of up to this many pixels are evaluated by one block each: 64^2 MSE
-// 16.3 -> 11.2 us per evaluation, 48 x 51 NCC 17.9 -> 13.3; at 90^2 both ways
-// take 16.6 (spacing 8) and 21.8 us (spacing 6, NCC), at 60 x 270 the tiles
-// 18.6 and one block 23.8
-constexpr long long kWholeMaxPixels = 7168;
+// Which 2D pairs are evaluated by one block each (us per evaluation on tiles
+// and in one block, one pair unless stated):
+// - up to kWholePixels: 64^2 MSE 16.1 and 11.8, 48 x 51 NCC 17.8 and 13.9; of
+//   coarse grids (spacing kWholeCoarse and more, where a tile's serial flushes
+//   weigh) up to kWholeMaxPixels: 80^2 with spacing 12 19.4 and 15.6, but with
+//   spacing 8 16.3 and 16.6
+// - no side longer than kWholeMaxSide, and no more than kWholeMaxRows values
+//   of the controls' rows interpolated along x (2 ncy nx; dense grids): 1000 x
+//   7 with spacing 8 18.5 and 24.4, 50^2 with spacing 1 31.2 and 35.3
+// - a launch of at most kWholeMaxPairs pairs, two per CU (beyond kWholePixels
+//   half of that): a CU takes one pair after the other, the tiles share it.
+//   64^2 MSE with spacing 16, 512 pairs 25.2 and 22, 1024 pairs 41.7 and 44,
+//   4096 pairs 94 and 171; 80^2 with spacing 16, 300 pairs 27.6 and 29.8
+constexpr long long kWholePixels = 4096, kWholeMaxPixels = 7168;
+constexpr int kWholeCoarse = 12, kWholeMaxSide = 256, kWholeMaxRows = 4096;
+constexpr int kWholeMaxPairs = 512;
+static bool whole_pays(const PairDesc& D, int npairs) {
+    if (D.n[0] > kWholeMaxSide || D.n[1] > kWholeMaxSide) return false;
+    if (2LL * D.nc[1] * D.n[0] > kWholeMaxRows) return false;
+    if (D.nvox <= kWholePixels) return npairs <= kWholeMaxPairs;
+    return D.nvox <= kWholeMaxPixels && std::min(D.sp[0], D.sp[1]) >= kWholeCoarse &&
+           npairs <= kWholeMaxPairs / 2;
+}
 
 // kernel variant ids understood by launch_bspline (3D): 3, 4 the spacing-8
 // kernels, 5 - 7 the pipelined kernel of any spacing whose tiles see at most
@@ -561,7 +579,8 @@ static air_status build_tables(air_plan* P, int dense_zc, bool pipelined) {
         int px = 1;
         for (const PairDesc& D : P->pd) {
             size_t lds = 0;
-            const int q = D.nvox <= kWholeMaxPixels ? whole2_pixels(D.n, D.nc, D.sp, &lds) : 0;
+            const int q =
+                whole_pays(D, P->npairs) ? whole2_pixels(D.n, D.nc, D.sp, &lds) : 0;
             px = q == 0 ? 0 : std::max(px, q);
             if (px == 0) break;
             P->fused.whole_lds = std::max(P->fused.whole_lds, lds);

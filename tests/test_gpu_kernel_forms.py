@@ -275,3 +275,27 @@ def test_small_2d_sums_in_64_bits(n, sp):
     worst = np.max(np.abs(got - scale * want) / bound)
     print(f"largest error over its bound {worst:.2f}", flush=True)
     assert worst <= 1.0
+
+
+# The last batch of one block per pair and the first on tiles, the largest pairs
+# of either size class and one pixel row more, the longest side, the most
+# control rows.
+@pytest.mark.parametrize("n,sp,pairs", [((32, 32), 8, 512), ((32, 32), 8, 513),
+                                        ((64, 64), 8, 1), ((64, 65), 8, 1), ((64, 112), 12, 1),
+                                        ((64, 113), 12, 1), ((80, 80), 16, 256),
+                                        ((80, 80), 16, 257), ((256, 16), 16, 1), ((257, 15), 16, 1),
+                                        ((64, 57), 2, 1), ((64, 59), 2, 1)])
+def test_one_block_or_tiles(n, sp, pairs):
+    kw = dict(n=n, spacing=(sp, sp), similarity=api.SIM_NCC, lambda_diff=0.1)
+    data = [inputs(n, 60 + i) for i in range(3)]
+    ths = [synth.random_theta(n, (sp, sp), 0.8, 70 + i) for i in range(3)]
+    pick = [0] * pairs
+    pick[pairs // 2], pick[-1] = 1, 2
+    dev = [tuple(gpu(a) for a in (f, m, t)) for (f, m), t in zip(data, ths)]
+    print(f"case one block or tiles {n} {sp} x {pairs}", flush=True)
+    vals, grads, _ = api.objective_and_grad_batched(
+        api.Plan([api.Problem(**kw)] * pairs), *([dev[k][j] for k in pick] for j in range(3)))
+    for i in sorted({0, pairs // 2, pairs - 1}):
+        vo, go, _ = O.objective_and_grad(O.Problem(**kw), *data[pick[i]], ths[pick[i]])
+        assert abs(float(vals[i]) - vo) <= VAL_TOL * abs(vo)
+        check_grad(grads[i].double().cpu().numpy(), go, f"pair {i} of {pairs}")
