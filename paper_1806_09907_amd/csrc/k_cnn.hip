@@ -1546,6 +1546,36 @@ bool conv3d_fwd_in2(const uint16_t* x, const int32_t dims[3], int32_t batch,
     return true;
 }
 
+// Voxels per block of the linear form, 0 where another form is faster (us of
+// one layer, other form and linear, 8 x 16^3 voxels unless stated):
+// - a wave's products have to outweigh its share of the staging: 24 input
+//   channels and more (112 -> 48 channels 62 and 27; 8 -> 16 at 50^3 x 4 28
+//   and 50), 48 beyond 2^18 voxels unless there are 32 output channels (32 ->
+//   8 at 8 x 60^3 210 and 236); 16 -> 32 .. 64 channels between 1.5 2^15 and
+//   2^17 voxels, where the other forms have one 16-voxel tile per wave (16 ->
+//   32 at 2 x 40^3 25 and 20, at 3 x 40^3 26 and 28)
+// - short rows: a block of M voxels stages three runs of M + 2 nx + 2 (32 ->
+//   16 at 200 x 100 x 50 133 and 292)
+// - a block per CU, of 128 voxels, but no second round of blocks that is less
+//   than half full (112 -> 48 at 2 x 28^3, 343 blocks, 43 and 47); for fewer
+//   voxels 64 or 32, where the weights are so large that their re-reads and
+//   latency are what the other forms spend: one layer's three directions, 112
+//   -> 48, 3 x 16^3 95 and 69 with 64 (128: 81, 32: 75), 16^3 84 and 56 with
+//   32 (64: 63); but 32 -> 48 at 3 x 16 x 18 x 20 11.4 and 13.8 with 64
+static int lin_voxels(const ConvDims& D, int cout) {
+    const long long N = (long long)D.nx * D.ny * D.nz, wk = (long long)cout * D.K;
+    const long long halo = 2LL * D.nx + 2;   // voxels beside a run's own
+    if (N >= 25600) {
+        const long long nb = (N + 127) / 128;
+        const bool deep = D.cin >= 24 && (D.cin >= 48 || cout >= 32 || N < (1 << 18));
+        const bool wide = D.cin == 16 && cout >= 32 && cout <= 64 && N >= 3 << 14 && N < 1 << 17;
+        return (deep || wide) && halo <= 153 && !(nb > 256 && nb < 384) ? 128 : 0;
+    }
+    if (D.cin < 48) return 0;
+    if (N >= 11520 && wk >= 40000) return halo <= 112 ? 64 : 0;
+    return wk >= 65536 && halo <= 136 ? 32 : 0;
+}
+
 static int grid1(long long n) {
     long long b = (n + kBlock - 1) / kBlock;
     return (int)(b < 16384 ? b : 16384);
@@ -1600,15 +1630,7 @@ air_status air_conv3d_fwd(const uint16_t* x, const int32_t dims[3], int32_t batc
         }
         return hipGetLastError() == hipSuccess ? AIR_OK : AIR_ERR_LAUNCH;
     }
-    // the linear form on 128-voxel blocks where they give about one per CU,
-    // on 64- and 32-voxel blocks where the weights are large (their re-reads
-    // and latency are what the other forms spend). One layer's three
-    // directions, 112 -> 48 channels: 8 x 16^3 142.8 -> 104.2 us (64: 114.5,
-    // 32: 127.8), 3 x 16^3 95.2 -> 69.1 with 64 (128: 80.7, 32: 74.7), 16^3
-    // 84.1 -> 56.1 with 32 (64: 62.7); 32 -> 48 channels at 16^3 34.5 us on
-    // the split-K form, 35.3 on 32-voxel blocks
-    const long long wk = (long long)cout * D.K;
-    const int lin = N >= 25600 ? 128 : (N >= 11520 && wk >= 40000) ? 64 : wk >= 65536 ? 32 : 0;
+    const int lin = lin_voxels(D, cout);
     if (lin) {
         const LinShape L = lin_shape(D, nt, lin, lin == 128 ? 4 : 8);
         const long long nb = (N + lin - 1) / lin;

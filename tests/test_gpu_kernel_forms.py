@@ -7,6 +7,7 @@ import torch
 import oracle as O
 from paper_1806_09907_amd import api, synth
 from parity import VAL_TOL, check_grad
+from test_gpu_walk_edges import test_conv_linear_blocks as check_conv
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -299,3 +300,17 @@ def test_one_block_or_tiles(n, sp, pairs):
         vo, go, _ = O.objective_and_grad(O.Problem(**kw), *data[pick[i]], ths[pick[i]])
         assert abs(float(vals[i]) - vo) <= VAL_TOL * abs(vo)
         check_grad(grads[i].double().cpu().numpy(), go, f"pair {i} of {pairs}")
+
+
+# The edges of the linear convolution form's rule: its channels (1.5 channel
+# tiles, no vector epilogue, 16 channels in), the longest rows of 128-, 64- and
+# 32-voxel blocks and one more, the smallest launch of 128-voxel blocks and one
+# less, a round of blocks and a second one too short.
+@pytest.mark.parametrize("cin,cout,dims,batch", [
+    (24, 24, (33, 29, 27), 1), (32, 20, (40, 40, 17), 1), (16, 48, (33, 33, 46), 1),
+    (16, 80, (33, 33, 46), 1), (48, 32, (75, 19, 18), 1), (48, 32, (76, 19, 18), 1),
+    (64, 32, (55, 15, 14), 1), (64, 32, (56, 15, 14), 1), (96, 48, (67, 5, 6), 1),
+    (96, 48, (68, 5, 6), 1), (32, 16, (25, 32, 32), 1), (32, 16, (25, 31, 33), 1),
+    (32, 16, (31, 31, 34), 1), (32, 16, (31, 32, 34), 1)])
+def test_conv_form_edges(cin, cout, dims, batch):
+    check_conv(cin, cout, dims, batch)
