@@ -577,12 +577,34 @@ k_cell_gather4(const PairDesc P, const float* __restrict__ Hx, float scale, int 
     }
 }
 
-// Whether the kernels above take the plan: 3D, four controls per axis, byte
-// offsets in 32 bits, and at least three cells along x (with fewer, Hx would
-// not fit in the workspace of H).
+// Whether the kernels above can take the plan: 3D, four controls per axis,
+// byte offsets in 32 bits, and at least three cells along x (with fewer, Hx
+// would not fit in the workspace of H).
 __host__ inline bool cells4(const PairDesc& P, int dim) {
     return dim == 3 && P.wK[0] == 4 && P.wK[1] == 4 && P.wK[2] == 4 && P.wncell[0] >= 3 &&
            (long long)P.nc[0] * P.nc[1] * P.nc[2] <= kMaxVoxels;
+}
+
+// Where they are the faster ones (general kernels, these; us with the padded
+// copy and the gather). Phases along x that are no multiple of 4 are loaded
+// and stored one by one, which only pays while the launch does not fill the
+// chip's queues: up to kCells4Voxels (spacing 10 at 128^3 29 and 15, at 200^3
+// 97 and 103). The transpose gives a 16-cell group to one block, so coarse
+// grids of few groups leave the chip idle longer than the general kernel's two
+// blocks (spacing 16 at 64^3 67 and 71, 32 at 128^3 408 and 510, but 12 at 64^3
+// 37 and 36): up to 12^3 phases, or at least 128 groups (16 at 180^3 97 and
+// 77); up to 10^3 where phases go one by one (10 at 64^3 28 and 27, 13 at 64^3
+// 44 and 51).
+constexpr long long kCells4Voxels = 1LL << 22;
+__host__ inline bool cells4_expand_pays(const PairDesc& P) {
+    return P.sp[0] % 4 == 0 || P.nvox <= kCells4Voxels;
+}
+__host__ inline bool cells4_transpose_pays(const PairDesc& P) {
+    const int phases = P.sp[0] * P.sp[1] * P.sp[2];
+    if (P.sp[0] % 4) return phases <= 1000 && P.nvox <= kCells4Voxels;
+    const long long groups =
+        (long long)cdiv(P.wncell[0], kWCells) * P.wncell[1] * P.wncell[2];
+    return phases <= 1728 || groups >= 128;
 }
 
 __host__ inline int wend_grid(long long n) {
@@ -602,7 +624,7 @@ hipError_t launch_wendland_expand(const PairDesc& P, const float* consts_dev, in
     const int ngx = cdiv(P.wncell[0], kWCells);
     const long long waves = (long long)ngx * P.wncell[1] * P.wncell[2] * (P.wpad[0] / 64);
     const int blocks = (int)((waves + kWaves - 1) / kWaves);
-    if (cells4(P, dim)) {
+    if (cells4(P, dim) && cells4_expand_pays(P)) {
         if (P.sp[0] % 4 == 0)
             hipLaunchKernelGGL(k_cell_expand4<true>, dim3(blocks), dim3(kBlock), 0, s, P, W,
                                theta, scale, u);
@@ -631,7 +653,7 @@ hipError_t launch_wendland_adjoint(const PairDesc& P, const float* consts_dev, i
     const int blocks = ngx * P.wncell[1] * P.wncell[2] * (P.wpad[1] / 64) * kTSplit;
     const long long NC = (long long)dim * P.nc[0] * P.nc[1] * P.nc[2];
     const int gblocks = (int)((NC + 63) / 64);
-    if (cells4(P, dim)) {
+    if (cells4(P, dim) && cells4_transpose_pays(P)) {
         const int groups = ngx * P.wncell[1] * P.wncell[2];
         if (P.sp[0] % 4 == 0)
             hipLaunchKernelGGL(k_cell_t4<true>, dim3(groups), dim3(kCellTBlock), 0, s, P, WT, g, H);

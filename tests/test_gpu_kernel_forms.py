@@ -8,6 +8,7 @@ import oracle as O
 from paper_1806_09907_amd import api, synth
 from parity import VAL_TOL, check_grad
 from test_gpu_walk_edges import test_conv_linear_blocks as check_conv
+from test_gpu_walk_edges import test_field_contractions as check_contraction
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -314,3 +315,32 @@ def test_one_block_or_tiles(n, sp, pairs):
     (32, 16, (31, 31, 34), 1), (32, 16, (31, 32, 34), 1)])
 def test_conv_form_edges(cin, cout, dims, batch):
     check_conv(cin, cout, dims, batch)
+
+
+# The edges of the cell contractions' rules: coarse grids of few and of enough
+# 16-cell groups, the most phases that go one by one and the next, and both in
+# one plan (a volume past the expansion's limit is compared below).
+@pytest.mark.parametrize("n,sp", [((50, 47, 49), (16, 16, 16)), ((48, 192, 176), (16, 16, 16)),
+                                  ((48, 40, 30), (12, 12, 12)), ((60, 44, 40), (16, 12, 12)),
+                                  ((42, 31, 30), (10, 10, 10)), ((45, 31, 30), (11, 10, 10))])
+@pytest.mark.parametrize("kind", ["tv", "wendland"])
+def test_contraction_form_edges(n, sp, kind):
+    check_contraction(n, sp, kind)
+
+
+def test_contraction_past_the_voxel_limit():
+    """Phases along x that are no multiple of 4: the expansion by the general
+    kernel (2^22 voxels and more) gives the bits of the other one, row by row."""
+    sp = (10, 9, 7)
+    us = []
+    rng = np.random.default_rng(91)
+    th = None
+    for nz in (150, 126):                  # 4.33 and 3.64 million voxels, both sides of 2^22
+        n = (170, 170, nz)
+        p = api.Problem(n=n, spacing=sp, similarity=api.SIM_LCC, lambda_diff=0.1, lcc_radius=1)
+        nc = p.ncontrol()
+        if th is None:
+            th = rng.normal(0.0, 0.01, (3, nc[2], nc[1], nc[0])).astype(np.float32)
+        us.append(api.displacement(api.Plan(p), gpu(th[:, :nc[2]])))
+    print("case expansion past the voxel limit", flush=True)
+    assert torch.equal(us[0][:, :126], us[1])
