@@ -40,10 +40,11 @@ constexpr int kBlock = 256;          // threads per block of every kernel
 constexpr int kStatWords = 8;        // doubles per tile statistics slot
 // dense-field passes: a block owns kDenseTX x kDenseTY voxels of (x, y) and
 // walks kDenseMinZc..kDenseZc planes of z (2D: 1..kDenseRows2 row groups); a
-// launch of kDenseFill blocks fills the chip (dense_walk in capi.hip)
+// launch of kDenseFill (2D: kDenseFill2) blocks is enough (dense_walk in
+// capi.hip)
 constexpr int kDenseTX = 64, kDenseTY = 4;
 constexpr int kDenseZc = 32, kDenseMinZc = 8, kDenseRows2 = 8;
-constexpr int kDenseFill = 2048;
+constexpr int kDenseFill = 2048, kDenseFill2 = 512;
 
 // Per-pair constants, uploaded once per plan and device.
 struct PairDesc {

@@ -385,22 +385,26 @@ static air_status validate_problem(const air_problem& p) {
 
 // Walk length of the dense passes' blocks: the longest (3D 32, 16, 8 planes;
 // 2D 8, 4, 2, 1 row groups) whose launch still has kDenseFill blocks, which
-// is what the 256 CUs hold at eight 256-thread blocks each; else the
-// shortest. With 32 planes always, one 128^3 pair had 256 blocks, one wave
+// is what the 256 CUs hold at eight 256-thread blocks each, in 2D kDenseFill2;
+// else the shortest. With 32 planes always, one 128^3 pair had 256 blocks, one wave
 // per SIMD: dense NCC at 149 x 181 x 127 95.5 -> 81.1 us, 163 x 104 x 82 MSE
 // 54.3 -> 34.4 us, 128^3 Wendland NCC 132 -> 97.7 us, a 2683 x 90 image 24.7
 // -> 19.9 us. Shorter walks cost more than they fill: four planes 102.6 us
 // for the Wendland pair, and 256^3 (2048 blocks with 32 planes, 265 us) runs
-// at 276 us with 16 planes and 294 us with eight. The results do not depend
+// at 276 us with 16 planes and 294 us with eight. A 2D block's walk is short
+// and its partial sums are many for the single blocks that add them: 1024^2
+// MSE 23.9 us with 8 row groups (512 blocks), 25.6 with 2 (2048 blocks); 512^2
+// 21.3 with 8 (128 blocks), 17.3 with 2 (512). The results do not depend
 // on it beyond the order of the partial sums.
 static int dense_walk(const air_plan* P) {
     const int longest = P->dim == 3 ? kDenseZc : kDenseRows2;
     const int shortest = P->dim == 3 ? kDenseMinZc : 1;
+    const int fill = P->dim == 3 ? kDenseFill : kDenseFill2;
     int zc = longest;
     for (; zc > shortest; zc /= 2) {
         long long blocks = 0;
         for (const air_problem& p : P->probs) blocks += dense_blocks(P->dim, p.n, zc);
-        if (blocks >= kDenseFill) break;
+        if (blocks >= fill) break;
     }
     return zc;
 }
