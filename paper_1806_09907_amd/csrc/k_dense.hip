@@ -221,7 +221,7 @@ k_dense_coef(const LaunchCtx C) {
     out[4] = -rho;
 }
 
-template <int DIM, int SIM>
+template <int DIM, int SIM, bool GMAX>
 __global__ void __launch_bounds__(DTX* DTY)
 k_dense_main(const LaunchCtx C, int zc, int reg_only, float* reg_grad_out) {
     constexpr int NT = DTX * DTY;
@@ -260,7 +260,7 @@ k_dense_main(const LaunchCtx C, int zc, int reg_only, float* reg_grad_out) {
     const __amdgpu_buffer_rsrc_t rM = make_rsrc(M, (uint32_t)(N * 4));
     // per-lane sums over the z chunk in FP32, widened once per chunk
     float sq = 0.f, rr = 0.f;   // MSE sum of squares, regulariser sum
-    float gm = 0.f;             // largest |gradient| (only where C.gmax asks for it)
+    float gm = 0.f;             // largest |gradient| (GMAX: into C.gmax)
     if (T.act) {
         const int x = T.x;
         int y = T.y;
@@ -352,13 +352,13 @@ k_dense_main(const LaunchCtx C, int zc, int reg_only, float* reg_grad_out) {
             for (int c = 0; c < DIM; ++c) {
                 const float gv = gi[c] + gr[c];
                 grad[c * N + vi] = gv;
-                if (C.gmax) gm = max_or_nan(gm, fabsf(gv));
+                if constexpr (GMAX) gm = max_or_nan(gm, fabsf(gv));
                 um[c] = u0[c];
                 u0[c] = up[c];
             }
         }
     }
-    if (C.gmax) block_max_to(gm, reinterpret_cast<unsigned int*>(red), C.gmax);
+    if constexpr (GMAX) block_max_to(gm, reinterpret_cast<unsigned int*>(red), C.gmax);
     double acc[2] = {(double)sq, (double)rr};
     block_sum<NT, 2>(acc, red);
     if (threadIdx.x == 0) {
@@ -376,7 +376,7 @@ k_dense_main(const LaunchCtx C, int zc, int reg_only, float* reg_grad_out) {
 // registers. The next plane (own voxel and halo) is loaded one step ahead.
 // Consecutive tiles share one XCD, so halo rows and the displaced gathers of
 // neighbouring tiles hit the same L2.
-template <int SIM>
+template <int SIM, bool GMAX>
 __global__ void __launch_bounds__(kDenseTX* kDenseTY)
 k_dense_main3(const LaunchCtx C, int zc, int reg_only, float* reg_grad_out) {
     constexpr int TX = kDenseTX, TY = kDenseTY;
@@ -460,7 +460,7 @@ k_dense_main3(const LaunchCtx C, int zc, int reg_only, float* reg_grad_out) {
         G = sample3_issue(rM, x, y, z0, disp_of(u0[0], s0), disp_of(u0[1], s1),
                           disp_of(u0[2], s2), nx, ny, nz);
     float sq = 0.f, rr = 0.f;   // per-lane MSE and regulariser sums over the chunk
-    float gm = 0.f;             // largest |gradient| (only where C.gmax asks for it)
+    float gm = 0.f;             // largest |gradient| (GMAX: into C.gmax)
     for (int z = z0; z < z1; ++z) {
         const int bsel = (z - z0) & 1;
 #pragma unroll
@@ -517,7 +517,7 @@ k_dense_main3(const LaunchCtx C, int zc, int reg_only, float* reg_grad_out) {
             for (int c = 0; c < 3; ++c) {
                 const float gv = gi[c] + gr[c];
                 grad[c * N + vi] = gv;
-                if (C.gmax) gm = max_or_nan(gm, fabsf(gv));
+                if constexpr (GMAX) gm = max_or_nan(gm, fabsf(gv));
             }
         }
 #pragma unroll
@@ -530,7 +530,7 @@ k_dense_main3(const LaunchCtx C, int zc, int reg_only, float* reg_grad_out) {
         G = Gn;
         Fv = Fn;
     }
-    if (C.gmax) block_max_to(gm, reinterpret_cast<unsigned int*>(red), C.gmax);
+    if constexpr (GMAX) block_max_to(gm, reinterpret_cast<unsigned int*>(red), C.gmax);
     double acc[2] = {(double)sq, (double)rr};
     block_sum<NT, 2>(acc, red);
     if (tid == 0) {
@@ -583,12 +583,14 @@ static hipError_t dense_run(const LaunchCtx& C, int zc, int max_blk, hipStream_t
     hipLaunchKernelGGL((k_dense_coef<SIM>), dim3(C.npairs), dim3(kBlock), 0, s, C);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (ev0) (void)hipEventRecord(ev0, s);
-    if (DIM == 3)
-        hipLaunchKernelGGL((k_dense_main3<SIM>), grid, dim3(DTX * DTY), 0, s, C, zc, 0,
-                           (float*)nullptr);
+    // (the maximum costs a 2D pass 2 %, so only where it is asked for)
+    auto run = [&](auto k) {
+        hipLaunchKernelGGL(k, grid, dim3(DTX * DTY), 0, s, C, zc, 0, (float*)nullptr);
+    };
+    if constexpr (DIM == 3)
+        run(C.gmax ? k_dense_main3<SIM, true> : k_dense_main3<SIM, false>);
     else
-        hipLaunchKernelGGL((k_dense_main<DIM, SIM>), grid, dim3(DTX * DTY), 0, s, C, zc, 0,
-                           (float*)nullptr);
+        run(C.gmax ? k_dense_main<DIM, SIM, true> : k_dense_main<DIM, SIM, false>);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (ev1) (void)hipEventRecord(ev1, s);
     hipLaunchKernelGGL((k_dense_fin<SIM>), dim3(C.npairs), dim3(kBlock), 0, s, C, 0,
@@ -612,9 +614,9 @@ hipError_t launch_reg_dense(const LaunchCtx& C, int pair_blocks, int zc, float* 
                             float* value_out, hipStream_t s) {
     dim3 grid(xcd_grid(pair_blocks, 0), 1);
     if (C.dim == 3)
-        hipLaunchKernelGGL((k_dense_main3<0>), grid, dim3(DTX * DTY), 0, s, C, zc, 1, grad_out);
+        hipLaunchKernelGGL((k_dense_main3<0, false>), grid, dim3(DTX * DTY), 0, s, C, zc, 1, grad_out);
     else
-        hipLaunchKernelGGL((k_dense_main<2, 0>), grid, dim3(DTX * DTY), 0, s, C, zc, 1, grad_out);
+        hipLaunchKernelGGL((k_dense_main<2, 0, false>), grid, dim3(DTX * DTY), 0, s, C, zc, 1, grad_out);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_dense_fin<0>), dim3(1), dim3(kBlock), 0, s, C, 1, value_out);
