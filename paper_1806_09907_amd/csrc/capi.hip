@@ -882,11 +882,19 @@ static hipError_t run_diffeo(const air_plan* P, const DeviceTables* T, void* ws,
     }
     if (e != hipSuccess) return e;
     TraceRange r_eval("air.stage.field_evaluation");
-    // dL/du_K; for a dense field without the exponential that is the gradient
-    const bool plain_dense = P->transform == AIR_TF_DENSE && P->diffeo == 0;
+    // dL/du_K; for a dense field without the exponential that is the gradient.
+    // A dense gradient is written while its inputs are still read, so one that
+    // shares memory with them is made in the workspace and copied at the end
+    auto shares = [&](const float* a, long long n) {
+        return a && grad < a + n && a < grad + dN;
+    };
+    const bool dense = P->transform == AIR_TF_DENSE;
+    const bool direct = dense && grad && !shares(theta, dN) && !shares(fixed, hp.nvox) &&
+                        !shares(moving, hp.nvox);
+    const bool plain_dense = direct && P->diffeo == 0;
     float* g = reinterpret_cast<float*>(w + P->L.gfield);
     float* o = g + dN;
-    if (plain_dense && grad) g = grad;
+    if (plain_dense) g = grad;
     unsigned int* reach = reinterpret_cast<unsigned int*>(w + P->L.reach);   // from the forward pass
     unsigned int* gmax = reach + P->diffeo;   // gmax[j]: max |gradient| entering adjoint j
     bool measured = false;                    // gmax[0] left by the dense main pass
@@ -933,12 +941,11 @@ static hipError_t run_diffeo(const air_plan* P, const DeviceTables* T, void* ws,
     }
     if (e != hipSuccess || !grad || plain_dense) return e;
     TraceRange r_adj("air.stage.squaring_adjoints_and_field_adjoint");
-    const bool dense = P->transform == AIR_TF_DENSE;
     const float vscale = ldexpf(1.f, -P->diffeo);
     if (P->diffeo > 0 && !measured) e = launch_field_absmax(hp, P->dim, g, gmax, s);
     for (int k = P->diffeo - 1, j = 0; k >= 0 && e == hipSuccess; --k, ++j) {
         // the last adjoint of a dense velocity writes dL/dtheta = 2^-K dL/du_0
-        const bool last = dense && k == 0;
+        const bool last = direct && k == 0;
         const ScaledField f = diffeo_field(P, w, theta, k);
         e = launch_compose_adjoint(hp, P->dim, f.u, f.scale, g, reach + k, gmax + j, gmax + j + 1,
                                    last ? grad : o, last ? vscale : 1.f, s);
@@ -946,7 +953,7 @@ static hipError_t run_diffeo(const air_plan* P, const DeviceTables* T, void* ws,
         g = o;
         o = t;
     }
-    if (e != hipSuccess || dense) return e;
+    if (e != hipSuccess || direct) return e;
     return field_adjoint(P, T, w, g, vscale, grad, false, s);
 }
 

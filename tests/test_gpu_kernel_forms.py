@@ -344,3 +344,34 @@ def test_contraction_past_the_voxel_limit():
         us.append(api.displacement(api.Plan(p), gpu(th[:, :nc[2]])))
     print("case expansion past the voxel limit", flush=True)
     assert torch.equal(us[0][:, :126], us[1])
+
+
+# A dense gradient may be written over its parameters (and the images): the
+# kernels that write it still read them.
+@pytest.mark.parametrize("kw", [dict(similarity=api.SIM_MSE, diffeo_steps=3),
+                                dict(similarity=api.SIM_NCC, diffeo_steps=1),
+                                dict(similarity=api.SIM_LCC, lcc_radius=2),
+                                dict(similarity=api.SIM_LCC, lcc_radius=2, diffeo_steps=2),
+                                dict(similarity=api.SIM_LCC, lcc_radius=2,
+                                     regulariser=api.REG_ISO_TV)])
+@pytest.mark.parametrize("n", [(70, 40, 33), (130, 90)])
+def test_dense_gradient_over_its_inputs(n, kw):
+    d = len(n)
+    p = api.Problem(n=n, transform=api.TF_DENSE, spacing=(1,) * d, lambda_diff=0.2, **kw)
+    F, M = inputs(n, 95)
+    th = synth.smooth_dense(n, 1.0, 96)
+    print(f"case gradient over its inputs {n} {kw}", flush=True)
+    plan = api.Plan(p)
+    v, g = api.objective_and_grad(plan, gpu(F), gpu(M), gpu(th))
+    both = gpu(th)
+    v2, g2 = api.objective_and_grad(plan, gpu(F), gpu(M), both, grad=both)
+    assert torch.equal(v, v2) and torch.equal(g, g2)
+    # theta, then the images, in one array; the gradient ends inside the images
+    N = int(np.prod(n))
+    arr = torch.cat([gpu(th).flatten(), gpu(F).flatten(), gpu(M).flatten()])
+    shape = tuple(reversed(n))
+    out = arr[N + 8:N + 8 + d * N].view((d,) + shape)
+    v3, g3 = api.objective_and_grad(plan, arr[d * N:(d + 1) * N].view(shape),
+                                    arr[(d + 1) * N:].view(shape),
+                                    arr[:d * N].view((d,) + shape), grad=out)
+    assert torch.equal(v, v3) and torch.equal(g, g3)
