@@ -1575,6 +1575,9 @@ bool conv3d_fwd_in2(const uint16_t* x, const int32_t dims[3], int32_t batch,
 static int lin_voxels(const ConvDims& D, int cout) {
     const long long N = (long long)D.nx * D.ny * D.nz, wk = (long long)cout * D.K;
     const long long halo = 2LL * D.nx + 2;   // voxels beside a run's own
+    // (runs of 32 voxels and more channels than this never fit in LDS, and
+    // lin_shape's sizes stay within an int)
+    if (D.cin > kLinMaxLds / (3 * 32 * 2)) return 0;
     if (N >= 25600) {
         const long long nb = (N + 127) / 128;
         const bool deep = D.cin >= 24 && (D.cin >= 48 || cout >= 32 || N < (1 << 18));

@@ -375,3 +375,23 @@ def test_dense_gradient_over_its_inputs(n, kw):
                                     arr[(d + 1) * N:].view(shape),
                                     arr[:d * N].view((d,) + shape), grad=out)
     assert torch.equal(v, v3) and torch.equal(g, g3)
+
+
+def test_conv_more_channels_than_lds_sizes_hold():
+    """Staged runs of more than 2^31 bytes: another form takes the layer. A few
+    non-zero operands, small whole numbers, so the result is exact."""
+    from paper_1806_09907_amd import cnn
+    nx, cin = 67, 2130448
+    x = torch.zeros((nx, cin), dtype=torch.bfloat16, device=DEV)
+    w = torch.zeros((1, 27 * cin), dtype=torch.bfloat16, device=DEV)
+    want = np.zeros(nx)
+    for v, c, val in [(0, 0, 2.0), (10, cin - 1, 3.0), (33, 1000003, -1.0), (66, 8, 5.0)]:
+        x[v, c] = val
+        for dx in range(3):
+            w[0, (9 + 3 + dx) * cin + c] = dx + 1
+            if 0 <= v + 1 - dx < nx:
+                want[v + 1 - dx] += val * (dx + 1)
+    y = torch.empty((nx, 1), dtype=torch.float32, device=DEV)
+    print("case channels past the LDS sizes", flush=True)
+    cnn.conv_fwd(x, (nx, 1, 1), cin, w, None, 1, 0, y_f32=y, batch=1)
+    assert np.array_equal(y.double().cpu().numpy().ravel(), want)
