@@ -149,8 +149,9 @@ int32_t air_tiling_count(int32_t dim);
 air_status air_tiling_describe(int32_t dim, int32_t id, int32_t* tile_x, int32_t* tile_y,
                                int32_t* column_cells);
 /* Select a tile configuration; changes the workspace size and re-uploads. (2D
- * plans of small pairs that keep the default evaluate each pair in one block
- * instead of tiles; selecting a configuration selects the tiles.) */
+ * plans of few small pairs that keep the default may evaluate each pair in
+ * one block instead of tiles; selecting a configuration selects the tiles, also
+ * the one that air_plan_get_tiling names.) */
 air_status air_plan_set_tiling(air_plan* plan, int32_t id);
 air_status air_plan_get_tiling(const air_plan* plan, int32_t* id);
 
@@ -233,7 +234,9 @@ air_status air_objective_and_grad_batched(const air_plan* plan,
  * every agreeing configuration in two rounds, each one upload call and two
  * warm-up launches then `reps` launches between two HIP events on `stream`,
  * keeping each configuration's faster reading; keeps the fastest one in
- * the plan (*chosen, *kernel_ms per launch) and, when cache_path is not NULL,
+ * the plan (*chosen, *kernel_ms per launch; a plan whose default is one block
+ * per pair times that too, and keeps it, with the default's id, where it wins;
+ * a failed call leaves the plan as it was) and, when cache_path is not NULL,
  * writes it into that JSON file under the plan's key (GPU architecture,
  * dimension, transform, similarity, spacing and size buckets of the batch),
  * keeping the file's other entries. Synchronises the host; B-spline plans

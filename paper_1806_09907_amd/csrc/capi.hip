@@ -171,6 +171,7 @@ struct air_plan {
     int reg = AIR_REG_DIFFUSION;  // regulariser kind
     float reg_weight = 0.f;       // its weight (TV plans; diffusion weights live per pair)
     int tiling = 0;
+    int default_tiling = 0;   // of the new plan
     bool tiling_set = false;  // chosen by the caller (no one-block kernel then)
     std::vector<air_problem> probs;
     std::vector<PairDesc> pd;
@@ -1166,6 +1167,7 @@ air_status air_plan_create(const air_problem* probs, int32_t npairs, air_plan** 
             return st;
         }
     }
+    P->default_tiling = P->tiling;
     *out = P;
     return AIR_OK;
 }
@@ -1210,14 +1212,14 @@ air_status air_tiling_describe(int32_t dim, int32_t id, int32_t* tile_x, int32_t
     return AIR_OK;
 }
 
-air_status air_plan_set_tiling(air_plan* plan, int32_t id) {
-    if (!plan) return AIR_ERR_INVALID_ARG;
-    if (id < 0 || id >= air_tiling_count(plan->dim)) return AIR_ERR_INVALID_ARG;
+// The configuration `id`, chosen by the caller (`set`) or as a default, which
+// may be the one-block kernel; on failure the plan keeps what it has.
+static air_status select_tiling(air_plan* plan, int id, bool set) {
     std::lock_guard<std::mutex> g(plan->mu);
     const int old = plan->tiling;
     const bool old_set = plan->tiling_set;
     plan->tiling = id;
-    plan->tiling_set = true;
+    plan->tiling_set = set;
     air_status st = build_tables(plan);
     if (st != AIR_OK) {
         plan->tiling = old;
@@ -1227,6 +1229,12 @@ air_status air_plan_set_tiling(air_plan* plan, int32_t id) {
     }
     release_device(plan);
     return AIR_OK;
+}
+
+air_status air_plan_set_tiling(air_plan* plan, int32_t id) {
+    if (!plan) return AIR_ERR_INVALID_ARG;
+    if (id < 0 || id >= air_tiling_count(plan->dim)) return AIR_ERR_INVALID_ARG;
+    return select_tiling(plan, id, true);
 }
 
 air_status air_plan_get_tiling(const air_plan* plan, int32_t* id) {
@@ -1547,7 +1555,17 @@ air_status air_autotune_cached(air_plan* plan, const char* cache_path, int32_t* 
     if (it == c.end()) return AIR_OK;
     const int t = entry_tiling(it->second);
     if (t < 0 || t >= air_tiling_count(plan->dim)) return AIR_OK;
-    const air_status st = air_plan_set_tiling(plan, t);
+    // an entry whose fastest was the one-block kernel: the plan's default, where
+    // that is the one-block kernel too
+    air_status st = AIR_OK;
+    if (it->second.find("\"one_block\"") != std::string::npos) {
+        st = select_tiling(plan, plan->default_tiling, false);
+        if (st == AIR_OK && plan->fused.whole > 0) {
+            *tiling = plan->tiling;
+            return AIR_OK;
+        }
+    }
+    st = select_tiling(plan, t, true);
     if (st == AIR_OK) *tiling = t;
     return st;
 }
@@ -1575,7 +1593,17 @@ air_status air_autotune(air_plan* plan, const float* const* fixed, const float* 
     }
     std::vector<float> v_ref(np), v_cur(np), g_ref(ntot), g_cur(ntot);
     const int old = plan->tiling;
-    const int ntl = air_tiling_count(plan->dim);
+    const bool old_set = plan->tiling_set;
+    // the tile configurations, and last the one-block kernel where it is the
+    // plan's default
+    const int ntiles = air_tiling_count(plan->dim);
+    const bool one_block = select_tiling(plan, plan->default_tiling, false) == AIR_OK &&
+                           plan->fused.whole > 0;
+    const int ntl = ntiles + (one_block ? 1 : 0);
+    auto choose = [&](int t) {
+        return t < ntiles ? select_tiling(plan, t, true)
+                          : select_tiling(plan, plan->default_tiling, false);
+    };
     std::vector<char> valid(ntl, 0);
     int first = -1;
     air_status st = AIR_OK;
@@ -1585,7 +1613,7 @@ air_status air_autotune(air_plan* plan, const float* const* fixed, const float* 
     // bound 1e-5 is above them and far below any wrong result.
     constexpr double kAgree = 1e-5;
     for (int t = 0; t < ntl && st == AIR_OK; ++t) {
-        if (air_plan_set_tiling(plan, t) != AIR_OK) continue;   // not valid for these sizes
+        if (choose(t) != AIR_OK) continue;   // not valid for these sizes
         if (ws_bytes < plan->L.total) {
             st = AIR_ERR_WORKSPACE;
             break;
@@ -1635,7 +1663,7 @@ air_status air_autotune(air_plan* plan, const float* const* fixed, const float* 
     // the events are read after the round), and its faster reading counts.
     std::vector<double> per_ms(ntl, -1.0);
     if (st == AIR_OK && first >= 0) {
-        (void)air_plan_set_tiling(plan, first);
+        (void)choose(first);
         const auto t0 = std::chrono::steady_clock::now();
         while (st == AIR_OK && std::chrono::steady_clock::now() - t0 < std::chrono::milliseconds(100)) {
             for (int w = 0; w < 10 && st == AIR_OK; ++w)
@@ -1650,7 +1678,7 @@ air_status air_autotune(air_plan* plan, const float* const* fixed, const float* 
             st = AIR_ERR_DEVICE;
     for (int round = 0; round < 2 && st == AIR_OK; ++round) {
         for (int t = 0; t < ntl && st == AIR_OK; ++t) {
-            if (!valid[t] || air_plan_set_tiling(plan, t) != AIR_OK) continue;
+            if (!valid[t] || choose(t) != AIR_OK) continue;
             // one call (tables upload) and two warm-up launches, then `reps` timed
             for (int w = 0; w < 3 && st == AIR_OK; ++w)
                 st = air_objective_and_grad_batched(plan, fixed, moving, theta, values, grads, ws,
@@ -1682,22 +1710,24 @@ air_status air_autotune(air_plan* plan, const float* const* fixed, const float* 
             best_ms = per_ms[t];
         }
     if (st != AIR_OK || best < 0) {
-        air_plan_set_tiling(plan, old);
+        select_tiling(plan, old, old_set);
         return st != AIR_OK ? st : AIR_ERR_UNSUPPORTED;
     }
-    st = air_plan_set_tiling(plan, best);
+    st = choose(best);
     if (st != AIR_OK) return st;
+    const bool whole = best >= ntiles;
+    best = plan->tiling;
     *chosen = best;
     if (kernel_ms) *kernel_ms = best_ms;
     if (cache_path) {
         std::map<std::string, std::string> c = read_tune_cache(cache_path);
         int tx = 0, ty = 0, cells = 0;
         (void)air_tiling_describe(plan->dim, best, &tx, &ty, &cells);
-        char obj[256];
+        char obj[320];
         snprintf(obj, sizeof(obj),
-                 "{\n  \"kernel_ms\": %.10g,\n  \"shape\": [\n   %d,\n   %d,\n   %d\n  ],\n  "
+                 "{\n  \"kernel_ms\": %.10g,\n  %s\"shape\": [\n   %d,\n   %d,\n   %d\n  ],\n  "
                  "\"tiling\": %d\n }",
-                 best_ms, tx, ty, cells, best);
+                 best_ms, whole ? "\"one_block\": 1,\n  " : "", tx, ty, cells, best);
         c[tune_key(plan)] = obj;
         FILE* f = fopen(cache_path, "wb");
         if (!f) return AIR_ERR_INVALID_ARG;

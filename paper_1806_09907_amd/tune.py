@@ -5,8 +5,8 @@ once on the caller's own batch and checks that it reproduces the first
 configuration's values and gradients to 1e-5 relative (the tile shape only
 changes the summation order, which moves them by up to ~1.3e-6); it then
 warms the GPU up on that batch for about 0.1 s and times every agreeing
-configuration with HIP events in two rounds (the faster reading counts),
-keeps the fastest, and records it in a JSON cache keyed by GPU architecture,
+configuration with HIP events in two rounds (the faster reading counts; one
+block per pair among them, where that is the plan's default), keeps the fastest, and records it in a JSON cache keyed by GPU architecture,
 dimension, transform, similarity, spacing and size buckets of the batch.
 air_autotune_cached applies a cached choice.
 """

@@ -1,11 +1,14 @@
 """Two forms of one kernel that a rule chooses between have to agree where the
 rule may choose either, and keep what the general form accepts."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
 import oracle as O
-from paper_1806_09907_amd import api, synth
+from paper_1806_09907_amd import api, synth, tune
+from paper_1806_09907_amd._lib import lib
 from parity import VAL_TOL, check_grad
 from test_gpu_walk_edges import test_conv_linear_blocks as check_conv
 from test_gpu_walk_edges import test_field_contractions as check_contraction
@@ -395,3 +398,43 @@ def test_conv_more_channels_than_lds_sizes_hold():
     print("case channels past the LDS sizes", flush=True)
     cnn.conv_fwd(x, (nx, 1, 1), cin, w, None, 1, 0, y_f32=y, batch=1)
     assert np.array_equal(y.double().cpu().numpy().ravel(), want)
+
+
+# The one-block kernel and the autotuner: a call that fails leaves the plan on
+# it, a call that finds it fastest keeps it, and the cache brings it back. The
+# forms differ in their last bits, which tells them apart.
+def test_autotune_knows_the_one_block_kernel(tmp_path):
+    n, sp = (64, 61), (8, 8)
+    F, M = inputs(n, 97)
+    th = synth.random_theta(n, sp, 0.8, 98)
+    args = [gpu(F)], [gpu(M)], [gpu(th)]
+    prob = api.Problem(n=n, spacing=sp, similarity=api.SIM_NCC, lambda_diff=0.05)
+
+    def grad(plan):
+        return api.objective_and_grad(plan, args[0][0], args[1][0], args[2][0])[1]
+
+    plan = api.Plan(prob)
+    whole = grad(plan)
+    tiles = grad(api.Plan(prob, tiling=plan.tiling))
+    assert not torch.equal(whole, tiles)
+    print("case autotune, workspace too small", flush=True)
+    out = torch.empty_like(args[2][0])
+    table = api.PointerTable(*args, [out], DEV)
+    values = torch.empty(1, device=DEV)
+    chosen, ms = ctypes.c_int32(-1), ctypes.c_double(0.0)
+    st = lib().air_autotune(plan.handle, api._ptr(table.fixed), api._ptr(table.moving),
+                            api._ptr(table.theta), api._ptr(values), api._ptr(table.grads), None, 0,
+                            2, None, ctypes.byref(chosen), ctypes.byref(ms), api._stream())
+    assert st != 0
+    assert torch.equal(grad(plan), whole)
+    print("case autotune", flush=True)
+    cache = str(tmp_path / "tune.json")
+    rep = tune.autotune(plan, *args, reps=20, cache_path=cache)
+    assert rep["tiling"] == plan.tiling
+    assert torch.equal(grad(plan), whole)
+    fresh = api.Plan(prob)
+    assert tune.cached_tiling(fresh, cache) == rep["tiling"]
+    assert torch.equal(grad(fresh), whole)
+    # a caller's choice of tiles stays one
+    tiled = api.Plan(prob, tiling=rep["tiling"])
+    assert torch.equal(grad(tiled), tiles)
