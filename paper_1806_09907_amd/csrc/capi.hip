@@ -271,9 +271,10 @@ static int round64(long long x) { return (int)((x + 63) / 64 * 64); }
 // The cell-contraction tables of an interpolating basis whose lattice is
 // aligned with voxel cells (see k_wendland.hip): wK and wncell must be set;
 // weight(qi, ri) is the weight between phase ri of a cell and its control
-// qi. Writes W[qq][r] and W^T to the constants; false if they are too big.
+// qi. Writes W[qq][r] and W^T to the constants (`fill`; else only the sizes
+// that the workspace depends on are set); false if they are too big.
 template <typename Weight>
-static bool cell_tables(int d, PairDesc& D, std::vector<float>& consts, Weight weight) {
+static bool cell_tables(PairDesc& D, std::vector<float>& consts, bool fill, Weight weight) {
     const int cw = wendland_cells_per_wave();
     D.wncp[0] = std::max(D.nc[0], cdiv(D.wncell[0], cw) * cw + D.wK[0] - 1);
     for (int a = 1; a < 3; ++a) D.wncp[a] = std::max(D.nc[a], D.wncell[a] + D.wK[a] - 1);
@@ -281,6 +282,9 @@ static bool cell_tables(int d, PairDesc& D, std::vector<float>& consts, Weight w
     const long long Q = (long long)D.wK[0] * D.wK[1] * D.wK[2];
     const long long Ppad = round64(P3), Qpad = round64(Q);
     if (Ppad * Qpad > kMaxWendTable) return false;
+    D.wpad[0] = (int)Ppad;
+    D.wpad[1] = (int)Qpad;
+    if (!fill) return true;
     std::vector<float> W((size_t)(Qpad * Ppad), 0.f);  // rows Q .. Qpad - 1 stay 0
     for (long long qq = 0; qq < Q; ++qq) {
         const int qi[3] = {(int)(qq % D.wK[0]), (int)((qq / D.wK[0]) % D.wK[1]),
@@ -291,9 +295,6 @@ static bool cell_tables(int d, PairDesc& D, std::vector<float>& consts, Weight w
             W[(size_t)(qq * Ppad + r)] = (float)weight(qi, ri);
         }
     }
-    (void)d;
-    D.wpad[0] = (int)Ppad;
-    D.wpad[1] = (int)Qpad;
     while (consts.size() % 4) consts.push_back(0.f);
     D.wend_off[0] = (int)consts.size();
     consts.insert(consts.end(), W.begin(), W.end());
@@ -306,7 +307,8 @@ static bool cell_tables(int d, PairDesc& D, std::vector<float>& consts, Weight w
 }
 
 // Wendland: weight psi(||(r - (qq - m) sp) / sigma||).
-static bool wendland_tables(const air_problem& p, PairDesc& D, std::vector<float>& consts) {
+static bool wendland_tables(const air_problem& p, PairDesc& D, std::vector<float>& consts,
+                            bool fill) {
     const int d = p.dim;
     int m[3] = {0, 0, 0};
     for (int a = 0; a < 3; ++a) {
@@ -319,7 +321,7 @@ static bool wendland_tables(const air_problem& p, PairDesc& D, std::vector<float
         D.wK[a] = K;
         D.wncell[a] = ncell;
     }
-    return cell_tables(d, D, consts, [&](const int* qi, const int* ri) {
+    return cell_tables(D, consts, fill, [&](const int* qi, const int* ri) {
         double r2 = 0.0;
         for (int a = 0; a < d; ++a) {
             const double o = (double)ri[a] - (double)(qi[a] - m[a]) * D.sp[a];
@@ -332,7 +334,7 @@ static bool wendland_tables(const air_problem& p, PairDesc& D, std::vector<float
 
 // Cubic B-spline: a cell sees its controls c .. c + 3 (control j at (j - 1)
 // sp); the weight is the product over axes of beta3 at the phase.
-static bool bspline_cell_tables(int d, PairDesc& D, std::vector<float>& consts) {
+static bool bspline_cell_tables(int d, PairDesc& D, std::vector<float>& consts, bool fill) {
     for (int a = 0; a < 3; ++a) {
         D.wK[a] = a < d ? 4 : 1;
         D.wncell[a] = a < d ? cdiv(D.n[a], D.sp[a]) : 1;
@@ -346,7 +348,7 @@ static bool bspline_cell_tables(int d, PairDesc& D, std::vector<float>& consts) 
             default: return t * t * t / 6.0;
         }
     };
-    return cell_tables(d, D, consts, [&](const int* qi, const int* ri) {
+    return cell_tables(D, consts, fill, [&](const int* qi, const int* ri) {
         double w = 1.0;
         for (int a = 0; a < d; ++a) w *= beta(D.sp[a], ri[a], qi[a]);
         return w;
@@ -410,7 +412,9 @@ static int dense_walk(const air_plan* P) {
     return zc;
 }
 
-static air_status build_tables(air_plan* P, int dense_zc, bool pipelined) {
+// `fill`: false while configurations are compared, whose sizes matter but not
+// the cell-contraction tables (up to 2^21 weights, the same for all of them)
+static air_status build_tables(air_plan* P, int dense_zc, bool pipelined, bool fill) {
     const int d = P->dim;
     P->dense_zc = dense_zc;
     const bool bs = P->transform == AIR_TF_BSPLINE3;
@@ -461,7 +465,7 @@ static air_status build_tables(air_plan* P, int dense_zc, bool pipelined) {
         }
         D.nvox = N;
         D.nparam = (long long)d * ((bs || wend) ? NC : N);
-        if (wend && !wendland_tables(p, D, P->consts)) return AIR_ERR_UNSUPPORTED;
+        if (wend && !wendland_tables(p, D, P->consts, fill)) return AIR_ERR_UNSUPPORTED;
         D.param_off = (long long)param_n;
         param_n += (size_t)D.nparam;
         D.inv_xr = (float)(1.0 / xr);
@@ -559,7 +563,7 @@ static air_status build_tables(air_plan* P, int dense_zc, bool pipelined) {
         // the cell contraction when its table fits (wpad[0] == 0: it does not)
         if (!wend) D.wpad[0] = D.wpad[1] = 0;
         if (bs && (P->field_route() || P->reg != AIR_REG_DIFFUSION))
-            (void)bspline_cell_tables(d, D, P->consts);
+            (void)bspline_cell_tables(d, D, P->consts, fill);
         // dense passes: dense models, and the objective at exp(v) or with LCC
         if (!bs || P->field_route()) {
             D.dense_nblk = dense_blocks(d, D.n, P->dense_zc);
@@ -640,15 +644,15 @@ static air_status build_tables(air_plan* P, int dense_zc, bool pipelined) {
     return AIR_OK;
 }
 
-static air_status build_tables(air_plan* P) {
+static air_status build_tables(air_plan* P, bool fill = true) {
     const int zc = dense_walk(P);
     const int longest = P->dim == 3 ? kDenseZc : kDenseRows2;
     auto fits = [&](size_t total) { return total <= AIR_NOALLOC_SCRATCH_BYTES; };
-    air_status st = build_tables(P, zc, true);
+    air_status st = build_tables(P, zc, true, fill);
     // the pipelined kernel of any spacing pads its LDS: where that is too
     // much, the general kernel
     const bool pipelined = !(st == AIR_ERR_UNSUPPORTED && P->variant >= 5 && P->dim == 3);
-    if (!pipelined) st = build_tables(P, zc, false);
+    if (!pipelined) st = build_tables(P, zc, false, fill);
     // more blocks need more partial sums: a plan that fits the scratch array
     // of air_objective_and_grad_noalloc with the longest walk keeps that walk
     // when the shorter one takes it past the array
@@ -661,33 +665,36 @@ static air_status build_tables(air_plan* P) {
         auto stats = [](size_t n) {
             return align256(std::max<size_t>(n, 1) * kStatWords * sizeof(double));
         };
-        if (fits(P->L.total - stats(now) + stats(then))) st = build_tables(P, longest, pipelined);
+        if (fits(P->L.total - stats(now) + stats(then))) st = build_tables(P, longest, pipelined, fill);
     }
     return st;
 }
 
-// Default tile configuration of a B-spline plan; the tables are built with
-// configuration 0. 3D: 16 x 16 columns, the longest (16, 8, 4, 2 cells) whose
-// launch has kFillTiles tiles, else the longest with about two per CU
-// (kTwoTilesPerCu; of another spacing than 8, a walk of more than kLongWalk
-// planes asks for kLongTiles), else the one with the most tiles; 2D: the longest column (16 .. 1 cells)
-// with kFillTiles2 tiles, else the most tiles. A configuration that cannot be
-// built, or that takes a plan past the scratch array of
-// air_objective_and_grad_noalloc which configuration 0 keeps it within, is
-// passed over.
+// Chooses the default tile configuration of a B-spline plan (sized with
+// configuration 0) and builds its tables. 3D: 16 x 16 columns, the longest (16,
+// 8, 4, 2 cells) whose launch has kFillTiles tiles, else the longest with about
+// two per CU (kTwoTilesPerCu; of another spacing than 8, a walk of more than
+// kLongWalk planes asks for kLongTiles), else the one with the most tiles; 2D:
+// the longest column (16 .. 1 cells) with kFillTiles2 tiles, else the most
+// tiles. A configuration that cannot be built is passed over, and so is, for
+// another 3D spacing than 8, one that takes a plan past the scratch array of
+// air_objective_and_grad_noalloc which configuration 0 keeps it within.
 static air_status default_tiling(air_plan* P) {
     const bool two = P->dim == 2;
     const int* cand = two ? kCfg2Fill : kCfg3Fill;
     const int ncand = two ? 5 : 4;
     const int fill = two ? kFillTiles2 : kFillTiles;
-    const bool scratch = P->L.total <= AIR_NOALLOC_SCRATCH_BYTES;
+    const bool scratch =
+        !two && P->variant != 3 && P->L.total <= AIR_NOALLOC_SCRATCH_BYTES;
     int chosen = -1, per_cu = -1;
+    bool filled = false;
     for (int k = 0; k < ncand; ++k) {
         P->tiling = cand[k];
-        if (build_tables(P) != AIR_OK) continue;
+        if (build_tables(P, false) != AIR_OK) continue;
         if (scratch && P->L.total > AIR_NOALLOC_SCRATCH_BYTES) continue;
         chosen = cand[k];
-        if (P->ntiles_total >= fill) break;
+        filled = P->ntiles_total >= fill;
+        if (filled) break;
         if (!two && per_cu < 0) {
             int walk = 0;   // planes of the longest column (not of spacing 8)
             for (const PairDesc& D : P->pd)
@@ -696,10 +703,8 @@ static air_status default_tiling(air_plan* P) {
                 per_cu = cand[k];
         }
     }
-    if (P->ntiles_total < fill && per_cu >= 0) chosen = per_cu;
-    if (chosen < 0) chosen = 0;
-    if (chosen == P->tiling) return AIR_OK;   // built last
-    P->tiling = chosen;
+    if (!filled && per_cu >= 0) chosen = per_cu;
+    P->tiling = chosen < 0 ? 0 : chosen;
     return build_tables(P);
 }
 
@@ -1153,7 +1158,7 @@ air_status air_plan_create(const air_problem* probs, int32_t npairs, air_plan** 
     P->lcc_radius = probs[0].similarity == AIR_SIM_LCC ? probs[0].lcc_radius : 0;
     P->probs.assign(probs, probs + npairs);
     P->tiling = 0;
-    air_status st = build_tables(P);
+    air_status st = build_tables(P, P->transform != AIR_TF_BSPLINE3);
     if (st != AIR_OK) {
         delete P;
         return st;
