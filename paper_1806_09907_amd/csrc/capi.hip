@@ -99,10 +99,14 @@ constexpr int kFillTiles = 4096;
 // (1000)
 constexpr int kTwoTilesPerCu = 448;
 // another spacing: a walk longer than this many planes is cut further, until
-// the launch has kLongTiles:
-// 181 x 217 x 181 with spacing 10 61.6 us with 4-cell columns (40 planes, 840
-// tiles) against 67.3 with 8-cell (80 planes, 504); 150 x 190 x 128 with
-// spacing 4 62.8 with 8-cell (32 planes, 480) against 67.4 with 4-cell (840)
+// the launch has kLongTiles. NCC, us (planes, tiles): 181 x 217 x 181, spacing
+// 10: 63 (40, 840) and 69 (80, 504); spacing 32: 48 (64, 504) and 73 (128, 336);
+// 200 x 240 x 240, spacing 14: 72 (56, 975) and 94 (112, 585); but 300^3, spacing
+// 20: 118 (80, 1444) and 117 (160, 722), 150 x 190 x 128, spacing 4: 68 (16, 960)
+// and 63 (32, 480). kFillTiles, the aim of spacing 8, cuts too far here: 256^3,
+// spacing 6: 137 (48, 1536) and 217 (12, 5632). Of 82 shapes with spacings 4 to
+// 32 the rule's choice is within 9 % of the best column, but for one (240 x 200 x
+// 110, spacing 12, 24 %: three columns of 48, 48 and 14 planes)
 constexpr int kLongWalk = 48, kLongTiles = 800;
 // the same for 2D B-spline plans (64-lane columns of 16, 8, 4, 2, 1 cells)
 static const int kCfg2Fill[] = {3, 2, 1, 0, 4};
@@ -671,12 +675,12 @@ static air_status build_tables(air_plan* P, bool fill = true) {
 }
 
 // Chooses the default tile configuration of a B-spline plan (sized with
-// configuration 0) and builds its tables. 3D: 16 x 16 columns, the longest (16,
-// 8, 4, 2 cells) whose launch has kFillTiles tiles, else the longest with about
-// two per CU (kTwoTilesPerCu; of another spacing than 8, a walk of more than
-// kLongWalk planes asks for kLongTiles), else the one with the most tiles; 2D:
-// the longest column (16 .. 1 cells) with kFillTiles2 tiles, else the most
-// tiles. A configuration that cannot be built is passed over, and so is, for
+// configuration 0) and builds its tables. 3D: 16 x 16 columns, with spacing 8
+// the longest (16, 8, 4, 2 cells) whose launch has kFillTiles tiles, else the
+// longest with about two per CU (kTwoTilesPerCu; of another spacing, a walk of
+// more than kLongWalk planes asks for kLongTiles), else the one with the most
+// tiles; 2D: the longest column (16 .. 1 cells) with kFillTiles2 tiles, else the
+// most tiles. A configuration that cannot be built is passed over, and so is, for
 // another 3D spacing than 8, one that takes a plan past the scratch array of
 // air_objective_and_grad_noalloc which configuration 0 keeps it within.
 static air_status default_tiling(air_plan* P) {
@@ -684,8 +688,8 @@ static air_status default_tiling(air_plan* P) {
     const int* cand = two ? kCfg2Fill : kCfg3Fill;
     const int ncand = two ? 5 : 4;
     const int fill = two ? kFillTiles2 : kFillTiles;
-    const bool scratch =
-        !two && P->variant != 3 && P->L.total <= AIR_NOALLOC_SCRATCH_BYTES;
+    const bool s8 = !two && P->variant == 3;   // (configuration 0's kernel)
+    const bool scratch = !two && !s8 && P->L.total <= AIR_NOALLOC_SCRATCH_BYTES;
     int chosen = -1, per_cu = -1;
     bool filled = false;
     for (int k = 0; k < ncand; ++k) {
@@ -693,12 +697,12 @@ static air_status default_tiling(air_plan* P) {
         if (build_tables(P, false) != AIR_OK) continue;
         if (scratch && P->L.total > AIR_NOALLOC_SCRATCH_BYTES) continue;
         chosen = cand[k];
-        filled = P->ntiles_total >= fill;
+        filled = (two || s8) && P->ntiles_total >= fill;
         if (filled) break;
         if (!two && per_cu < 0) {
             int walk = 0;   // planes of the longest column (not of spacing 8)
             for (const PairDesc& D : P->pd)
-                if (P->variant >= 5) walk = std::max(walk, D.col_cells * D.sp[2]);
+                if (!s8) walk = std::max(walk, D.col_cells * D.sp[2]);
             if (P->ntiles_total >= (walk > kLongWalk ? kLongTiles : kTwoTilesPerCu))
                 per_cu = cand[k];
         }
