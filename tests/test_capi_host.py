@@ -337,3 +337,19 @@ def test_default_columns_of_other_spacings(n, sp, cells):
     assert _lib.lib().air_tiling_describe(3, plan.tiling, ctypes.byref(tx), ctypes.byref(ty),
                                           ctypes.byref(cc)) == 0
     assert (tx.value, ty.value, cc.value) == (16, 16, cells)
+
+
+@pytest.mark.parametrize("sp", [(6, 6, 6), (3, 3, 5)])
+def test_tilings_that_must_build(sp):
+    """Every 3D configuration but one takes these plans (64 x 4 tiles of 16 cells need
+    more LDS than a block may have), so the GPU's comparison of the tilings of
+    any spacing runs for all the others."""
+    def builds(t):
+        try:
+            Plan(Problem(n=(70, 37, 44), spacing=sp, similarity=SIM_NCC), tiling=t)
+        except _lib.AirError as e:
+            assert e.status == 5
+            return False
+        return True
+
+    assert [t for t in range(_lib.lib().air_tiling_count(3)) if not builds(t)] == [4]
