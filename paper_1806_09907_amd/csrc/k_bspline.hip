@@ -862,12 +862,15 @@ k_fused3_tile(const LaunchCtx C) {
         const float dx = dd[0], dy = dd[1], dz = dd[2];
         const float zf = (float)z;
         // cell [x + c, x + c + 1] with c = floor(d) clamped to [-x, n - 2 - x]
-        // so that every load is in range. Then f = d - c is exact (c is an
-        // integer no larger in magnitude than d's integer part), and it lies
-        // in [0, 1] iff x + d lies in [0, n - 1]: below the range c is
-        // clamped up and f < 0; above it c is clamped down ("e") and f > 1,
-        // except for d the integer n - 1 - x (f == 1), the last voxel, whose
-        // derivative is right-sided (zero padding)
+        // so that every load is in range. Then f = d - c lies in [0, 1] iff x + d
+        // lies in [0, n - 1]: below the range c is clamped up and f < 0; above
+        // it c is clamped down ("e") and f > 1, except for d the integer
+        // n - 1 - x (f == 1), the last voxel, whose derivative is right-sided
+        // (zero padding). f is exact (c is an integer no larger in magnitude
+        // than d's integer part) but on the last voxel itself, x = n - 1: there
+        // c = -1, and a d of at most 2^-24 rounds to f == 1. SP = 0 therefore
+        // compares d with n - 1 - x, as axis_cell does; SP = 8 counts such a
+        // point as lying on the last voxel.
         const float flx = floorf(dx), fly = floorf(dy), flz = floorf(dz);
         const float clx = __builtin_amdgcn_fmed3f(flx, lox, hcx);
         const float cly = __builtin_amdgcn_fmed3f(fly, loy, hcy);
@@ -881,9 +884,15 @@ k_fused3_tile(const LaunchCtx C) {
         constexpr uint32_t kOne = 0x3f800000u;   // bits of 1.0f: f in [0, 1]
         // (bitwise, not short-circuit: every test is a compare, no branch;
         // a negative f has its sign bit set and fails like f > 1)
-        const bool in = (int)(__float_as_uint(q.fx) <= kOne) &
-                        (int)(__float_as_uint(q.fy) <= kOne) &
-                        (int)(__float_as_uint(q.fz) <= kOne) & (int)act & (int)(z < nz);
+        bool in;
+        if constexpr (kAny)
+            in = (int)((int)(__float_as_uint(q.fx) | __float_as_uint(q.fy) |
+                             __float_as_uint(q.fz)) >= 0) &
+                 (int)(dx <= hcx + 1.f) & (int)(dy <= hcy + 1.f) &
+                 (int)(dz <= nzm2 + 1.f - zf) & (int)act & (int)(z < nz);
+        else
+            in = (int)(__float_as_uint(q.fx) <= kOne) & (int)(__float_as_uint(q.fy) <= kOne) &
+                 (int)(__float_as_uint(q.fz) <= kOne) & (int)act & (int)(z < nz);
         q.m = in ? (kAny ? __uint_as_float(~0u) : 1.f) : 0.f;
         // byte offset of the cell's first corner: the row step clz ny + cly
         // is an exact float (|.| < 2^24), the rest 24-bit integer arithmetic

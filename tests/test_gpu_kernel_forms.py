@@ -438,3 +438,25 @@ def test_autotune_knows_the_one_block_kernel(tmp_path):
     # a caller's choice of tiles stays one
     tiled = api.Plan(prob, tiling=rep["tiling"])
     assert torch.equal(grad(tiled), tiles)
+
+
+# The mask is decided on the exact point: a displacement far below the rounding
+# of the point itself puts the last voxels of an axis outside (positive) or
+# leaves them inside (negative), the first ones the other way round.
+@pytest.mark.parametrize("n,sp", [((33, 21, 30), 10), ((33, 21, 30), 5), ((40, 36, 33), 16),
+                                  ((40, 24, 33), (3, 1, 6)), ((50, 41), 8), ((150, 131), 12)])
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_mask_a_hair_past_the_last_voxel(n, sp, sign):
+    d = len(n)
+    sp = (sp,) * d if isinstance(sp, int) else sp
+    kw = dict(n=n, spacing=sp, similarity=api.SIM_MSE, lambda_diff=0.0)
+    p = api.Problem(**kw)
+    F, M = inputs(n, 101)
+    plan = api.Plan(p)
+    for a in range(d):
+        th = np.zeros(p.param_shape(), np.float32)
+        th[a] = sign * 3e-8 * 2.0 / (n[a] - 1)
+        print(f"case hair {n} {sp} axis {a} sign {sign}", flush=True)
+        v, _ = api.objective_and_grad(plan, gpu(F), gpu(M), gpu(th))
+        vo, _, _ = O.objective_and_grad(O.Problem(**kw), F, M, th)
+        assert abs(float(v) - vo) <= VAL_TOL * abs(vo), (a, float(v), vo)
