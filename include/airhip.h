@@ -143,8 +143,8 @@ air_status air_plan_param_count(const air_plan* plan, int32_t pair, int64_t* cou
  * new 3D B-spline plan starts with 16 x 16 columns: with spacing 8 on every
  * axis the longest column (16, 8, 4, 2 cells) that gives the launch 4096 tiles,
  * else the longest with about two tiles per CU, else the one with the most
- * tiles; with other spacings the longest with about two tiles per CU (three
- * for columns of more than 48 planes), else the one with the most tiles; a 2D
+ * tiles; with other spacings columns of 4 cells where they give about two
+ * tiles per CU (three for columns of more than 48 planes), else of 2; a 2D
  * B-spline plan with the longest column (16, 8, 4, 2, 1 cells) that gives 2048
  * tiles, else the most tiles; other plans start with configuration 0. */
 int32_t air_tiling_count(int32_t dim);

@@ -91,6 +91,7 @@ static const TileCfg kCfg2[] = {{64, 1, 2}, {64, 1, 4}, {64, 1, 8}, {64, 1, 16},
 // candidates of the default 3D configuration, longest column first
 // (16 x 16 with 16, 8, 4, 2 cells), and the tile count that fills the chip
 static const int kCfg3Fill[] = {6, 8, 5, 9};
+static const int kCfg3Any[] = {5, 9};   // the same of other spacings than 8
 constexpr int kFillTiles = 4096;
 // a launch with fewer tiles takes the longest column that still gives the
 // CUs about two tiles each: one 128^3 pair 26.3 us per evaluation with 2-cell
@@ -98,15 +99,16 @@ constexpr int kFillTiles = 4096;
 // 4-cell (500 tiles) against 46.1 with 8-cell (300) and 39.3 with 2-cell
 // (1000)
 constexpr int kTwoTilesPerCu = 448;
-// another spacing: a walk longer than this many planes is cut further, until
-// the launch has kLongTiles. NCC, us (planes, tiles): 181 x 217 x 181, spacing
-// 10: 63 (40, 840) and 69 (80, 504); spacing 32: 48 (64, 504) and 73 (128, 336);
-// 200 x 240 x 240, spacing 14: 72 (56, 975) and 94 (112, 585); but 300^3, spacing
-// 20: 118 (80, 1444) and 117 (160, 722), 150 x 190 x 128, spacing 4: 68 (16, 960)
-// and 63 (32, 480). kFillTiles, the aim of spacing 8, cuts too far here: 256^3,
-// spacing 6: 137 (48, 1536) and 217 (12, 5632). Of 82 shapes with spacings 4 to
-// 32 the rule's choice is within 9 % of the best column, but for one (240 x 200 x
-// 110, spacing 12, 24 %: three columns of 48, 48 and 14 planes)
+// another spacing: 4-cell columns, 2-cell ones where they give too few tiles (a
+// walk of more than kLongWalk planes: fewer than kLongTiles). NCC, us (planes,
+// tiles): 181 x 217 x 181, spacing 10: 63 (40, 840) and 74 (20, 1680); spacing
+// 32: 73 (128, 336) and 48 (64, 504); 200 x 240 x 240, spacing 14: 72 (56, 975)
+// and 76 (28, 1755); 128^3, spacing 6: 39.7 (24, 384) and 38.7 (12, 704). Longer
+// columns would be up to 15 % faster on large volumes (256^3, spacing 4: 143 us
+// with 8 cells, 169 with 4), but their gradients are further from 64 bits (200 x
+// 160 x 180 with spacings 4 to 10: 1.06 to 1.16 times the error of 32 x 8 x 4
+// cells, the former default, with 8 cells, 1.17 to 1.41 with 16; 0.88 to 0.95
+// with 4)
 constexpr int kLongWalk = 48, kLongTiles = 800;
 // the same for 2D B-spline plans (64-lane columns of 16, 8, 4, 2, 1 cells)
 static const int kCfg2Fill[] = {3, 2, 1, 0, 4};
@@ -677,18 +679,19 @@ static air_status build_tables(air_plan* P, bool fill = true) {
 // Chooses the default tile configuration of a B-spline plan (sized with
 // configuration 0) and builds its tables. 3D: 16 x 16 columns, with spacing 8
 // the longest (16, 8, 4, 2 cells) whose launch has kFillTiles tiles, else the
-// longest with about two per CU (kTwoTilesPerCu; of another spacing, a walk of
-// more than kLongWalk planes asks for kLongTiles), else the one with the most
-// tiles; 2D: the longest column (16 .. 1 cells) with kFillTiles2 tiles, else the
+// longest with about two per CU (kTwoTilesPerCu), else the one with the most
+// tiles; with another spacing 4 cells with as many tiles (kLongTiles for a walk
+// of more than kLongWalk planes), else 2; 2D: the longest column (16 .. 1 cells)
+// with kFillTiles2 tiles, else the
 // most tiles. A configuration that cannot be built is passed over, and so is, for
 // another 3D spacing than 8, one that takes a plan past the scratch array of
 // air_objective_and_grad_noalloc which configuration 0 keeps it within.
 static air_status default_tiling(air_plan* P) {
     const bool two = P->dim == 2;
-    const int* cand = two ? kCfg2Fill : kCfg3Fill;
-    const int ncand = two ? 5 : 4;
-    const int fill = two ? kFillTiles2 : kFillTiles;
     const bool s8 = !two && P->variant == 3;   // (configuration 0's kernel)
+    const int* cand = two ? kCfg2Fill : s8 ? kCfg3Fill : kCfg3Any;
+    const int ncand = two ? 5 : s8 ? 4 : 2;
+    const int fill = two ? kFillTiles2 : kFillTiles;
     const bool scratch = !two && !s8 && P->L.total <= AIR_NOALLOC_SCRATCH_BYTES;
     int chosen = -1, per_cu = -1;
     bool filled = false;

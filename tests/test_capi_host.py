@@ -326,12 +326,12 @@ def test_plan_creation_builds_the_cell_tables_once(kw):
     assert create <= 2.5 * build
 
 
-@pytest.mark.parametrize("n,sp,cells", [((256, 256, 256), 6, 8), ((300, 300, 300), 10, 8),
-                                        ((256, 256, 256), 4, 16), ((181, 217, 181), 10, 4),
-                                        ((128, 128, 128), 16, 2)])
+@pytest.mark.parametrize("n,sp,cells", [((256, 256, 256), 6, 4), ((300, 300, 300), 10, 4),
+                                        ((256, 256, 256), 4, 4), ((181, 217, 181), 10, 4),
+                                        ((128, 128, 128), 16, 2), ((64, 64, 64), 5, 2)])
 def test_default_columns_of_other_spacings(n, sp, cells):
-    """16 x 16 columns, the longest with 448 tiles (800 if it has more than 48
-    planes), else the most tiles; not cut further until there are 4096."""
+    """16 x 16 columns of 4 cells with 448 tiles (800 if they have more than 48
+    planes), else of 2; not cut until there are 4096."""
     plan = Plan(Problem(n=n, spacing=(sp,) * 3, similarity=SIM_MSE))
     tx, ty, cc = (ctypes.c_int32() for _ in range(3))
     assert _lib.lib().air_tiling_describe(3, plan.tiling, ctypes.byref(tx), ctypes.byref(ty),
