@@ -115,7 +115,7 @@ static const int kCfg2Fill[] = {3, 2, 1, 0, 4};
 constexpr int kFillTiles2 = 2048;
 // Which 2D pairs are evaluated by one block each (us per evaluation on tiles
 // and in one block, one pair unless stated):
-// - up to kWholePixels: 64^2 MSE 16.1 and 11.8, 48 x 51 NCC 17.8 and 13.9; of
+// - up to kWholePixels: 64^2 MSE 16.1 and 11.8, 48 x 51 NCC 18.1 and 14.2; of
 //   coarse grids (spacing kWholeCoarse and more, where a tile's serial flushes
 //   weigh) up to kWholeMaxPixels: 80^2 with spacing 12 19.4 and 15.6, but with
 //   spacing 8 16.3 and 16.6
@@ -124,7 +124,7 @@ constexpr int kFillTiles2 = 2048;
 //   7 with spacing 8 18.5 and 24.4, 50^2 with spacing 1 31.2 and 35.3
 // - a launch of at most kWholeMaxPairs pairs, two per CU (beyond kWholePixels
 //   half of that): a CU takes one pair after the other, the tiles share it.
-//   64^2 MSE with spacing 16, 512 pairs 25.2 and 22, 1024 pairs 41.7 and 44,
+//   64^2 MSE with spacing 16, 512 pairs 25.0 and 22.5, 1024 pairs 41.7 and 44,
 //   4096 pairs 94 and 171; 80^2 with spacing 16, 300 pairs 27.6 and 29.8
 constexpr long long kWholePixels = 4096, kWholeMaxPixels = 7168;
 constexpr int kWholeCoarse = 12, kWholeMaxSide = 256, kWholeMaxRows = 4096;

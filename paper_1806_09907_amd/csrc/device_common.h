@@ -162,19 +162,20 @@ __host__ __device__ inline int xcd_grid(int T, int R) {
     return 8 * ((T + 7) / 8 + (R + 7) / 8);
 }
 
+// A product that is not contracted into a later addition: d - floor(d) would
+// otherwise become the fraction of the unrounded product in some kernels and
+// not in others.
+__device__ inline float mul_rounded(float u, float s) {
+#pragma clang fp contract(off)
+    return u * s;
+}
+
 // Displacement of a voxel along one axis in voxels, d = fl(u s), and the
 // exact rounding error e = u s - d (one fma returns it exactly). The sample
 // point x + u s is never formed in floating point: rounding it to FP32 would
 // move the interpolation weights by up to half an ulp of the point (4e-6
 // voxel at x ~ 100), while d carries an error below half an ulp of the
 // displacement itself. The cell and the mask are decided on x + d + e.
-// mul_rounded keeps the product from being contracted into a later addition:
-// d - floor(d) would otherwise become the fraction of the unrounded product in
-// some kernels and not in others.
-__device__ inline float mul_rounded(float u, float s) {
-#pragma clang fp contract(off)
-    return u * s;
-}
 struct Disp {
     float d, e;
 };

@@ -487,7 +487,7 @@ k_fused3(const LaunchCtx C) {
 // products with the tile's weight matrices. Against k_fused3 (which waits for
 // each layer's gathers and transposes with two LDS reads per term), same
 // tiling, 181 x 217 x 181 NCC with spacing 10: 102 -> 84 us per evaluation;
-// with the default tiling it allows (16 x 16, 4 cells) 61.6 us.
+// with the default tiling it allows (16 x 16, 4 cells) 63.5 us.
 struct W8 {
     float w[9][4];  // row 8 (t = 1) is the next cell's first layer
 };

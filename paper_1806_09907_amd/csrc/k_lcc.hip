@@ -723,9 +723,10 @@ __host__ inline int fused_tiles(const PairDesc& P) {
 // planes at a fixed rate, so the launch takes about ceil(blocks / 256) (zc +
 // 2r) plane steps, and 1.45 where a CU has a single block (nothing hides its
 // latency). The even split of z that takes the fewest is used, of kMinZc to
-// kMaxZc planes. Against 16 planes always, whole evaluations: 87 x 152 x 89
-// (r 3) 130 -> 120 us, 77 x 85 x 119 (r 2) 109 -> 93, 111 x 77 x 158 (r 4)
-// 112 -> 106; 128^3 has 16 from the rule (8: 149 us, 32: 149, 16: 134).
+// kMaxZc planes. Whole evaluations, the rule against 16 planes always: 87 x 152
+// x 89 (r 3) 120 and 131 us, 77 x 85 x 119 (r 2) 93 and 109, 111 x 77 x 158 (r 4)
+// 136 and 141, 64^3 (r 3) 76 and 100; 128^3 has 16 from the rule (the same
+// inputs over and over: 136 us; 8 planes 150, 32 151).
 constexpr int kMinZc = 4, kMaxZc = 64;
 __host__ inline int fused_zc(const PairDesc& P, int r) {
     const int tiles = fused_tiles(P), nz = P.n[2];
