@@ -419,7 +419,8 @@ static int dense_walk(const air_plan* P) {
 }
 
 // `fill`: false while configurations are compared, whose sizes matter but not
-// the cell-contraction tables (up to 2^21 weights, the same for all of them)
+// the Gram and cell-contraction tables, which are the same for all of them and
+// most of a build's time
 static air_status build_tables(air_plan* P, int dense_zc, bool pipelined, bool fill) {
     const int d = P->dim;
     P->dense_zc = dense_zc;
@@ -484,7 +485,7 @@ static air_status build_tables(air_plan* P, int dense_zc, bool pipelined, bool f
                 spline_weights(D.sp[a], P->consts);
                 while (P->consts.size() % 4) P->consts.push_back(0.f);
                 D.gram_off[a] = (int)P->consts.size();
-                gram_tables(D.n[a], D.sp[a], D.nc[a], P->consts);
+                if (fill) gram_tables(D.n[a], D.sp[a], D.nc[a], P->consts);
                 while (P->consts.size() % 4) P->consts.push_back(0.f);
             }
             const int col = d - 1;

@@ -326,6 +326,23 @@ def test_plan_creation_builds_the_cell_tables_once(kw):
     assert create <= 2.5 * build
 
 
+def test_plan_creation_builds_the_gram_tables_once():
+    """The same for the Gram tables of a batch, which are most of its build."""
+    probs = [Problem(n=(128, 128, 128))] * 64
+
+    def once(f):
+        t = time.perf_counter()
+        f()
+        return time.perf_counter() - t
+
+    plan = Plan(probs)
+    create = min(once(lambda: Plan(probs)) for _ in range(5))
+    build = min(once(lambda: _lib.lib().air_plan_set_tiling(plan.handle, plan.tiling))
+                for _ in range(5))
+    print(f"create {create * 1e3:.1f} ms, one build {build * 1e3:.1f} ms")
+    assert create <= 2 * build
+
+
 @pytest.mark.parametrize("n,sp,cells", [((256, 256, 256), 6, 4), ((300, 300, 300), 10, 4),
                                         ((256, 256, 256), 4, 4), ((181, 217, 181), 10, 4),
                                         ((128, 128, 128), 16, 2), ((64, 64, 64), 5, 2)])
